@@ -1,0 +1,282 @@
+"""The work that users of the tree-verification pass have it do, as timed cases.
+
+A case is one of four kinds of call sequence, each through the public entry points:
+
+  step   one verification step of `runner.VerifyPass` (all layers, head, acceptance)
+  layer  one decoder layer (`sv_verify_layer`), as a host runtime that walks the layers issues it
+  head   the final norm, LM head and greedy choice over the full vocabulary
+  turn   what stands between two steps: draft tree from the drafter's candidates, acceptance,
+         commit of the accepted path in every layer's cache, prefix advance
+
+Sizes are those of `workload.CONFIGS`, of the paper's draft trees (top 8, 50 nodes, depth 5) and
+odd ones between them.  Inputs are synthetic: matrices N(0, 0.02) in the three weight formats,
+prefix K/V N(0, 1).  A trained verifier is sure of most of its tokens; random weights are not, and
+their argmax would hang on the last bits.  So every hidden row carries one of 256 directions next
+to its noise and the head's rows carry the same directions: the choice is clear, as in use.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2507_22424_amd import binding as sv
+from paper_2507_22424_amd import workload as wl
+from paper_2507_22424_amd.runner import VerifyPass
+
+N_BINS = 256
+
+# (hidden, heads, head_dim, mlp, vocab): the 7B shape, the small bf16 model of the tests and the
+# float32 reference model
+MODELS = {"7b": (4096, 32, 128, 11008, 32000), "small": (512, 4, 128, 1536, 1024), "tiny": (256, 4, 64, 688, 512)}
+
+
+def _step(name, model="7b", dtype="bf16", layers=32, episodes=1, nodes=60, depth=7, children=4, prefix=(280, 280), r=4):
+    return {"name": name, "kind": "step", "model": model, "dtype": dtype, "layers": layers, "episodes": episodes,
+            "nodes": nodes, "depth": depth, "children": children, "prefix_lo": prefix[0], "prefix_hi": prefix[1], "r": r}
+
+
+def listed():
+    return [
+        # the float32 reference model, one layer: launches and latency only
+        _step("f32 model, 15 nodes", "tiny", "f32", 1, nodes=15, children=3, prefix=(64, 64), r=2),
+        # one layer driven from outside (pipelined hosts, layer-wise offload), a 26-node tree
+        dict(_step("one layer, 26 nodes", layers=1, nodes=26), kind="layer"),
+        # plain autoregressive decoding through the same path: a tree that is only its root
+        _step("autoregressive row", nodes=1, depth=7, prefix=(287, 287), r=0),
+        # the benchmark's workload: one camera frame and an instruction, a 60-node tree
+        _step("60 nodes"),
+        # the same with the weights in 8 bits, and the paper's 50-node tree with weights in 4 bits
+        _step("60 nodes, 8-bit weights", dtype="bf16_w8"),
+        _step("50 nodes, 4-bit weights", dtype="bf16_w4", nodes=50, depth=5, children=8, prefix=(277, 277), r=9),
+        # several robots served together: 3, 4 and 16 episodes with ragged prefixes
+        _step("3 episodes x 50 nodes", episodes=3, nodes=50, depth=5, children=8, prefix=(260, 300), r=9),
+        _step("4 episodes x 60, 8-bit", dtype="bf16_w8", episodes=4, prefix=(260, 300)),
+        _step("16 episodes x 60 nodes", episodes=16, prefix=(260, 300)),
+        # several frames of history and a wide tree
+        _step("128 nodes, prefix 2048", nodes=128, children=6, prefix=(2048, 2048), r=8),
+        # the greedy choice over the whole vocabulary (tokens other than actions allowed)
+        dict(_step("full-vocabulary head", layers=1), kind="head"),
+        # between two steps of 16 episodes
+        dict(_step("tree, accept and commit", episodes=16, nodes=50, depth=5, children=8, prefix=(260, 300)), kind="turn"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return max(lo, min(hi, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))))
+
+
+def draw(rng):
+    kind = rng.choices(("step", "layer", "head", "turn"), (14, 2, 2, 2))[0]
+    dtype = rng.choices(("bf16", "bf16_w8", "bf16_w4", "f32"), (10, 3, 3, 2))[0]
+    model = "tiny" if dtype == "f32" else rng.choices(("7b", "small"), (9, 1))[0]
+    if kind == "head":
+        dtype, model = "bf16", "7b"
+    rows = _log_int(rng, 1, 960 if dtype == "bf16" else 240)
+    episodes = rng.randint(max(1, -(-rows // 128)), max(1, -(-rows // 128), min(16, rows // 8)))
+    nodes = max(1, min(128, rows // episodes))
+    depth = min(7, rng.randint(4, 7))
+    children = rng.randint(4, 8)
+    # the cache rows of all episodes together stay within those of the largest listed cases
+    most = 2048 if episodes == 1 else max(40, min(2048, 5000 // episodes))
+    hi = _log_int(rng, 16, most)
+    lo = hi if episodes == 1 else max(1, hi - rng.randint(0, 40))
+    if model == "tiny":
+        hi, lo = min(hi, 200), min(lo, 200)
+    c = _step("", model, dtype, _log_int(rng, 1, 32) if kind in ("step", "turn") else 1, episodes, nodes, depth, children, (lo, hi),
+              rng.choice((0, 1, 2, 4, 5, 8, 9)))
+    del c["name"]
+    return dict(c, kind=kind)
+
+
+def _config(case):
+    H, nh, d, F, V = MODELS[case["model"]]
+    return wl.VerifyConfig(name="case", index=0, dtype=case["dtype"], n_layers=case["layers"], hidden=H, n_heads=nh, head_dim=d,
+                           mlp_dim=F, vocab=V, n_bins=N_BINS, n_episodes=case["episodes"], prefix_lo=case["prefix_lo"],
+                           prefix_hi=case["prefix_hi"], tree_nodes=case["nodes"], max_depth=case["depth"],
+                           max_children=case["children"], spine_lo=min(3, case["depth"]), r_values=(case["r"],))
+
+
+class _Draw:
+    """Seeded draws on the GPU (tensors) and on the host (trees, lengths, tokens)."""
+
+    def __init__(self, seed):
+        self.gen = torch.Generator(device="cuda").manual_seed(int(seed) * 7919 + 13)
+        self.rng = np.random.default_rng(int(seed) + 101)
+
+    def normal(self, shape, dtype, std=1.0, mean=0.0):
+        t = torch.empty(shape, dtype=dtype, device="cuda")
+        return t.normal_(mean, std, generator=self.gen)
+
+    def gain(self, n, dtype):
+        return self.normal((n,), torch.float32, 0.02, 1.0).to(dtype)
+
+    def scales(self, n, size):
+        return size * (0.75 + 0.5 * torch.rand(n, device="cuda", generator=self.gen))
+
+    def layer(self, cfg):
+        """The nine tensors of a layer in the format of cfg.dtype."""
+        H, F, D = cfg.hidden, cfg.mlp_dim, cfg.n_heads * cfg.head_dim
+        dt = cfg.torch_dtype
+        raw = {"g1": self.gain(H, dt), "g2": self.gain(H, dt)}
+        for n, shape in {"wq": (D, H), "wk": (D, H), "wv": (D, H), "wo": (H, D), "wg": (F, H), "wu": (F, H), "wd": (H, F)}.items():
+            if cfg.dtype == "bf16_w8":
+                raw[n] = self.normal(shape, torch.float32).to(torch.float8_e4m3fn).view(torch.uint8)
+                raw[n + "_scale"] = self.scales(shape[0], 0.02)
+            elif cfg.dtype == "bf16_w4":
+                code = (self.normal(shape, torch.float32, 2.5).round_().clamp_(-8, 7) + 8).to(torch.uint8)
+                raw[n] = code[:, 0::2] | (code[:, 1::2] << 4)
+                raw[n + "_scale"] = self.scales(shape[0], 0.008)
+            else:
+                raw[n] = self.normal(shape, dt, 0.02)
+        return raw
+
+    def directions(self, H):
+        return self.normal((N_BINS, H), torch.float32, H ** -0.5)
+
+    def trees(self, cfg):
+        T, out = cfg.tree_nodes, []
+        for _ in range(cfg.n_episodes):
+            spine = min(T - 1, int(self.rng.integers(cfg.spine_lo, cfg.max_depth + 1)))
+            out.append(wl.draft_tree(T, cfg.max_depth, cfg.max_children, spine, self.rng))
+        return out
+
+    def prefixes(self, cfg):
+        return self.rng.integers(cfg.prefix_lo, cfg.prefix_hi + 1, size=cfg.n_episodes).astype(np.int32)
+
+    def drafts_near(self, cfg, parents, choice, spread=8):
+        """Draft bins within +-spread of the bin chosen at the parent node (choice: bins, all episodes)."""
+        T, out = cfg.tree_nodes, []
+        for b, par in enumerate(parents):
+            near = choice[b * T + np.maximum(par, 0)] + self.rng.integers(-spread, spread + 1, size=T)
+            out.append(cfg.action_lo + np.clip(near, 0, N_BINS - 1))
+        return np.concatenate(out).astype(np.int32)
+
+
+def _pass(case, seed):
+    cfg, d = _config(case), _Draw(seed)
+    parents, plen = d.trees(cfg), d.prefixes(cfg)
+    vp = VerifyPass(cfg, plen, np.concatenate(parents), extra_capacity=cfg.prefix_hi - int(plen.max()))
+    for l in range(cfg.n_layers):
+        vp.load_layer(l, d.layer(cfg))
+        for b, p in enumerate(plen):
+            vp.load_prefix(l, b, *(d.normal((cfg.n_heads, int(p), cfg.head_dim), cfg.torch_dtype) for _ in "kv"))
+    H, root = cfg.hidden, cfg.hidden ** 0.5
+    e = d.directions(H)
+    choice = d.rng.integers(0, N_BINS, size=vp.M)
+    vp.load_head(d.gain(H, cfg.torch_dtype), (d.normal((N_BINS, H), torch.float32, 0.02) + 0.06 * root * e).to(cfg.torch_dtype))
+    vp.set_hidden(d.normal((vp.M, H), torch.float32) + 2 * root * e[torch.from_numpy(choice).cuda()])
+    vp.set_draft(d.drafts_near(cfg, parents, choice))
+    return {"case": case, "pass": vp}
+
+
+def _head(case, seed):
+    cfg, d = _config(case), _Draw(seed)
+    H, V, M = cfg.hidden, cfg.vocab, cfg.n_episodes * cfg.tree_nodes
+    mc = sv.model_cfg(cfg.dtype, H, cfg.n_heads, cfg.head_dim, cfg.mlp_dim, V)
+    w = d.normal((V, H), torch.bfloat16, 0.02)
+    pick = torch.from_numpy(d.rng.integers(0, V, size=M)).cuda()
+    x = d.normal((M, H), torch.float32) + w[pick].float() * 50.0
+    packed = torch.empty(sv.sv_packed_head_bytes(mc, 0, V), dtype=torch.uint8, device="cuda")
+    sv.sv_pack_head(mc, d.gain(H, torch.bfloat16), w, 0, V, packed)
+    ws = torch.empty(sv.sv_workspace_bytes(mc, cfg.n_episodes, cfg.tree_nodes, V), dtype=torch.uint8, device="cuda")
+    sv.sv_workspace_init(mc, cfg.n_episodes, cfg.tree_nodes, V, ws)
+    return {"case": case, "cfg": mc, "packed": packed, "x": x, "M": M, "V": V, "ws": ws,
+            "token": torch.zeros(M, dtype=torch.int32, device="cuda"), "logits": torch.zeros(M, V, dtype=torch.float32, device="cuda")}
+
+
+def _turn(case, seed):
+    cfg, d = _config(case), _Draw(seed)
+    B, T, L, cap, lo = cfg.n_episodes, cfg.tree_nodes, cfg.n_layers, cfg.max_depth, cfg.action_lo
+    mc = sv.model_cfg(cfg.dtype, cfg.hidden, cfg.n_heads, cfg.head_dim, cfg.mlp_dim, cfg.vocab)
+    forests = [wl.candidate_forest(8, cap, int(d.rng.integers(1 << 20)), N_BINS, lo) for _ in range(B)]
+    up = lambda name: torch.from_numpy(np.stack([f[name] for f in forests])).cuda()  # noqa: E731
+    z = lambda *shape, dt=torch.int32: torch.zeros(*shape, dtype=dt, device="cuda")  # noqa: E731
+    s = {"case": case, "cfg": mc, "B": B, "T": T, "L": L, "cap": cap, "lo": lo, "r": case["r"],
+         "cand": (up("parent"), up("logp"), up("token")),
+         "root": torch.from_numpy((lo + d.rng.integers(0, N_BINS, size=B)).astype(np.int32)).cuda(),
+         "parent": z(B, T), "depth": z(B, T), "anc": z(B, T, (T + 63) // 64, dt=torch.int64), "draft": z(B, T), "status": z(B),
+         "mask": z(B * T, dt=torch.uint8), "len": z(B), "best": z(B), "path": z(B, cap + 1), "tokens": z(B, cap + 1)}
+    s["tree"] = sv.Tree(s["parent"].data_ptr(), s["depth"].data_ptr(), s["anc"].data_ptr(), T, (T + 63) // 64)
+    _build(s)
+    # the verifier's choice after a node lies within 8 bins of one of the node's drafted children
+    par, dr = s["parent"].cpu().numpy(), s["draft"].cpu().numpy()
+    target = lo + d.rng.integers(0, N_BINS, size=(B, T))
+    for b in range(B):
+        for c in d.rng.permutation(np.arange(1, T)):
+            target[b, par[b, c]] = lo + np.clip(dr[b, c] - lo + d.rng.integers(-8, 9), 0, N_BINS - 1)
+    s["target"] = torch.from_numpy(target.astype(np.int32)).cuda()
+    plen = d.prefixes(cfg)
+    capacity = -(-(cfg.prefix_hi + T + cap + 1) // 64) * 64
+    s["plen0"] = torch.from_numpy(plen).cuda()
+    s["plen"] = s["plen0"].clone()
+    s["k"], s["v"] = (d.normal((L, B, cfg.n_heads, capacity, cfg.head_dim), cfg.torch_dtype) for _ in "kv")
+    s["views"] = [sv.KvView(s["k"][l].data_ptr(), s["v"][l].data_ptr(), s["plen"].data_ptr(), int(plen.max()), capacity) for l in range(L)]
+    return s
+
+
+def _build(s):
+    sv.sv_tree_build_device(*s["cand"], s["root"], s["B"], s["T"], s["cap"], s["parent"], s["depth"], s["anc"], s["draft"], s["status"])
+
+
+def prepare(case, seed):
+    return {"step": _pass, "layer": _pass, "head": _head, "turn": _turn}[case["kind"]](case, seed)
+
+
+def run(s):
+    kind = s["case"]["kind"]
+    if kind == "head":
+        sv.sv_action_head_argmax_packed(s["cfg"], s["packed"], s["x"], s["M"], 0, s["V"], s["token"], s["logits"], s["ws"])
+        return {"token": s["token"], "logits": s["logits"]}
+    if kind == "turn":
+        s["plen"].copy_(s["plen0"])                  # a new observation: the prefix starts over
+        _build(s)
+        sv.sv_relaxed_accept(s["tree"], s["draft"], s["target"], s["lo"], N_BINS, s["r"], s["B"], s["cap"], s["mask"], s["len"],
+                             s["best"], s["path"], s["tokens"])
+        for view in s["views"]:
+            sv.sv_commit_path(s["cfg"], view, s["T"], s["path"], s["len"], s["B"], s["cap"])
+        sv.sv_advance_prefix(s["plen"], s["len"], s["B"], s["cap"])
+        return {n: s[n] for n in ("parent", "depth", "anc", "draft", "status", "mask", "len", "best", "path", "tokens", "plen", "k", "v")}
+    vp = s["pass"]
+    if kind == "layer":
+        vp.x.copy_(vp.x0)
+        sv.sv_verify_layer(vp.cfg, vp.packed[0], vp.x, vp.kv[0].struct, vp.tree.struct, vp.B, vp.workspace)
+        return {"x": vp.x, "k": vp.kv[0].k, "v": vp.kv[0].v}
+    vp.step(s["case"]["r"], want_logits=True)
+    return {"x": vp.x, "logits": vp.logits, "token": vp.token, "mask": vp.accept_mask, "len": vp.accepted_len, "best": vp.best_node,
+            "path": vp.path, "tokens": vp.out_tokens, "k": vp.kv[-1].k, "v": vp.kv[-1].v}
+
+
+def work(case):
+    H, nh, d, F, V = MODELS[case["model"]]
+    D, L, M, B, T = nh * d, case["layers"], case["episodes"] * case["nodes"], case["episodes"], case["nodes"]
+    keys = (case["prefix_lo"] + case["prefix_hi"]) / 2 + T
+    elem = 4 if case["dtype"] == "f32" else 2
+    if case["kind"] == "head":
+        return {"bytes": V * H * 2 + M * H * 4 + M * V * 4, "flops": 2.0 * M * V * H}
+    if case["kind"] == "turn":
+        n_cand = 8 + 64 * (case["depth"] - 1)
+        moved = 2                                     # rows of K and of V per episode, head and layer
+        return {"bytes": B * (n_cand * 12 + T * 40) + L * B * nh * d * elem * moved * 2 * 2, "flops": 0.0}
+    weights = L * (4 * H * D + 3 * H * F)             # matrix elements
+    per = {"f32": 4, "bf16": 2, "bf16_w8": 1, "bf16_w4": 0.5}[case["dtype"]]
+    kv = L * B * nh * d * elem * 2 * (keys + T)       # prefix and tree rows read, tree rows written
+    bytes_ = weights * per + kv + 2 * M * H * 4
+    flops = 2.0 * M * weights + 4.0 * L * M * keys * D
+    if case["kind"] == "step":
+        bytes_ += N_BINS * H * elem + M * N_BINS * 4
+        flops += 2.0 * M * N_BINS * H
+    return {"bytes": bytes_, "flops": flops}
+
+
+def tolerance(case):
+    """Four times the distance (2-norm) of these outputs from a float64 evaluation of the same stored
+    values.  float32 model: sums in another order.  The others: activations in two bf16 parts, and
+    new K/V rows rounded to bf16, whose effect grows with the depth.  The choices are clear and the
+    integer work is exact."""
+    if case["kind"] == "turn":
+        return "exact"
+    if case["dtype"] == "f32":
+        return {"rel": 5e-6, "max": 1e-4}
+    if case["kind"] == "head":
+        return {"rel": 1e-3, "max": 1e-2}
+    return {"rel": 6e-3, "max": 0.06, "differ": 0.002}
