@@ -38,26 +38,26 @@ def _step(name, model="7b", dtype="bf16", layers=32, episodes=1, nodes=60, depth
 def listed():
     return [
         # the float32 reference model, one layer: launches and latency only
-        _step("f32 model, 15 nodes", "tiny", "f32", 1, nodes=15, children=3, prefix=(64, 64), r=2),
+        _step("f32 model 15 nodes", "tiny", "f32", 1, nodes=15, children=3, prefix=(64, 64), r=2),
         # one layer driven from outside (pipelined hosts, layer-wise offload), a 26-node tree
-        dict(_step("one layer, 26 nodes", layers=1, nodes=26), kind="layer"),
+        dict(_step("one layer 26 nodes", layers=1, nodes=26), kind="layer"),
         # plain autoregressive decoding through the same path: a tree that is only its root
         _step("autoregressive row", nodes=1, depth=7, prefix=(287, 287), r=0),
         # the benchmark's workload: one camera frame and an instruction, a 60-node tree
         _step("60 nodes"),
         # the same with the weights in 8 bits, and the paper's 50-node tree with weights in 4 bits
-        _step("60 nodes, 8-bit weights", dtype="bf16_w8"),
-        _step("50 nodes, 4-bit weights", dtype="bf16_w4", nodes=50, depth=5, children=8, prefix=(277, 277), r=9),
+        _step("60 nodes 8-bit", dtype="bf16_w8"),
+        _step("50 nodes 4-bit", dtype="bf16_w4", nodes=50, depth=5, children=8, prefix=(277, 277), r=9),
         # several robots served together: 3, 4 and 16 episodes with ragged prefixes
         _step("3 episodes x 50 nodes", episodes=3, nodes=50, depth=5, children=8, prefix=(260, 300), r=9),
-        _step("4 episodes x 60, 8-bit", dtype="bf16_w8", episodes=4, prefix=(260, 300)),
+        _step("4 episodes x 60 8-bit", dtype="bf16_w8", episodes=4, prefix=(260, 300)),
         _step("16 episodes x 60 nodes", episodes=16, prefix=(260, 300)),
         # several frames of history and a wide tree
-        _step("128 nodes, prefix 2048", nodes=128, children=6, prefix=(2048, 2048), r=8),
+        _step("128 nodes prefix 2048", nodes=128, children=6, prefix=(2048, 2048), r=8),
         # the greedy choice over the whole vocabulary (tokens other than actions allowed)
         dict(_step("full-vocabulary head", layers=1), kind="head"),
         # between two steps of 16 episodes
-        dict(_step("tree, accept and commit", episodes=16, nodes=50, depth=5, children=8, prefix=(260, 300)), kind="turn"),
+        dict(_step("tree accept and commit", episodes=16, nodes=50, depth=5, children=8, prefix=(260, 300)), kind="turn"),
     ]
 
 
