@@ -21,8 +21,7 @@ HBM_PEAK_GBS = 8000.0
 MFMA_PEAK_TFLOPS = 2500.0           # dense bf16
 # HBM-side bytes per launch of the dominant kernel, from the two rocprofv3 --pmc runs (FETCH_SIZE,
 # then WRITE_SIZE, each calibrated with a transfer of known size in the same run) whose summaries
-# are under profiles/: fetched + written bytes, averaged over the four products of a layer (for
-# the many-row kernels with the split / row-norm / reduction launches that belong to a product).
+# are under profiles/: fetched + written bytes, averaged over the four products of a layer.
 TRAFFIC_BYTES_PER_LAUNCH = {
     ("C3", "bf16"): 137.02e6,
     ("C3", "w8"): 86.46e6,
@@ -298,10 +297,8 @@ def main():
     gemm_ms_raw = sum(raw_ms[k] for k in gemm_bytes)
     gemm_gbs = sum(gemm_bytes.values()) * L / (gemm_ms_raw * 1e-3) / 1e9
     # matrix-core work as issued: every product is done on the hi and on the lo half of the
-    # float32 activations (2 x the algorithmic flops), on row tiles padded to 64 (128 for the
-    # many-row kernels)
-    rows_path = M > 64 and not w8        # what sv_verify_layer routes to the many-row kernels
-    m_issue = -(-M // 128) * 128 if rows_path else -(-M // 64) * 64
+    # float32 activations (2 x the algorithmic flops), on rows padded to blocks of 32
+    m_issue = -(-M // 32) * 32
     issued_flops = 2.0 * sum(gemm_flops.values()) * L * m_issue / M
     mfma_tflops = issued_flops / (gemm_ms_raw * 1e-3) / 1e12
     kv_bytes = sum(2 * cfg.n_heads * (int(p) + T) * cfg.head_dim * 2 for p in prefix_len)   # all episodes, one layer
@@ -312,21 +309,18 @@ def main():
     mfma_bound = M > 128                 # many rows: the products are bound by the matrix cores
     key = (args.config, args.weights)
     if mfma_bound:
-        roofline = {"bound": "mfma", "kernel": "gemm_rows_kernel (4 products per layer, with their split_rows / "
-                                               "rows_rstd / rows_reduce_resid launches)",
+        roofline = {"bound": "mfma", "kernel": "gemm_mid (4 launches per layer: q/k/v, o, gate/up, down)",
                     "achieved": mfma_tflops, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": mfma_tflops / MFMA_PEAK_TFLOPS,
                     "traffic": TRAFFIC_BYTES_PER_LAUNCH.get(key),
                     "traffic_source": TRAFFIC_SOURCE.get(key),
-                    "flops_counted": "matrix-core flops as issued: hi and lo halves of the activations, rows padded to 128",
+                    "flops_counted": "matrix-core flops as issued: hi and lo halves of the activations, rows padded to blocks of 32",
                     "algorithmic_frac": step_flops / (gemm_ms_raw * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS,
                     "flops_per_launch_avg": issued_flops / (4 * L),
                     "avg_launch_us": gemm_ms_raw * 1e3 / (4 * L)}
     else:
         roofline = {"bound": "hbm",
-                    "kernel": ("gemm_rows_kernel (4 products per layer, K split across workgroups, with their "
-                               "split_rows / rows_rstd / rows_reduce_* launches)" if rows_path else
-                               "gemm_stream_bf16 (4 launches per layer: q/k/v, o, gate/up, down)"),
+                    "kernel": "gemm_skinny (4 launches per layer: q/k/v, o, gate/up, down)",
                     "achieved": gemm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": gemm_gbs / HBM_PEAK_GBS,
                     "traffic": TRAFFIC_BYTES_PER_LAUNCH.get(key),

@@ -200,17 +200,13 @@ int sv_tree_build_device(const int32_t *cand_parent, const float *cand_logp,
  *   kv, tree:  [host] structs of [device] pointers, see above; tree->n_nodes = T
  *   workspace: [device], 256-byte aligned, ws_bytes >= sv_workspace_bytes(cfg, B, T, *),
  *              prepared once with sv_workspace_init; calls sharing a workspace must not overlap
- * bf16 models (also with 8-bit or 4-bit weights): up to 64 rows, and any number of rows with
- * 8-bit or 4-bit weights, the projections are split along K and their partial sums travel
- * in 16 bits with one scale per 64-row x 32-column tile (error <= 2^-14 of the tile's largest
- * partial sum, each row first brought to a common size); with more than 64 rows and bf16
- * weights the projections run on kernels bound by the matrix cores whose partial sums, where K
- * is split at all, are float32.  A partial sum that is not finite
- * travels as a code of its own and comes back as NaN: a NaN or infinity reaches exactly the
+ * bf16 models (also with 8-bit or 4-bit weights): the float32 activations enter the projections
+ * as the sum of two bf16 numbers (2^-16 of each value); the partial sums of workgroups that
+ * share a product along K are float32 and added in a fixed order.  A NaN or infinity reaches exactly the
  * outputs it reaches by the layer's own arithmetic, one exception aside - inside the tree
  * attention a NaN in the value row of a tree node also reaches the other nodes of that episode
  * and head, whether or not they attend to it (a probability of zero times NaN); other episodes
- * are never touched.  The workgroups of such a projection wait for each other (bounded) and
+ * are never touched.  The workgroups that share a product wait for each other (bounded) and
  * check where they ran; a wait that runs out or an unexpected placement leaves the outputs of
  * the call undefined and raises the status word (sv_workspace_region, SV_WS_STATUS), which
  * callers that cannot rule out a GPU shared with other work should read before they trust or

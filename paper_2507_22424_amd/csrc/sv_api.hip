@@ -11,10 +11,10 @@
 #include "specvla_verify_aux.h"
 #include "sv_accept.h"
 #include "sv_attention.h"
-#include "sv_gemm_mfma.h"
-#include "sv_gemm_rows.h"
 #include "sv_internal.h"
 #include "sv_kernels.h"
+#include "sv_pack.h"
+#include "sv_products.h"
 #include "sv_tree_build.h"
 
 namespace sv {
@@ -34,56 +34,6 @@ static int check_cfg(const sv_model_cfg* c) {
   return SV_OK;
 }
 
-// Shape of the work split of one streaming GEMM (bf16 path): K slices and tile groups per XCD.
-// A slice should be about one LDS chunk (4 K blocks); slices longer than a chunk need at most
-// one tile per wave (4 per group) because the accumulators then stay in registers.
-struct GemmPlan {
-  int S, gpx;
-  bool multi;                                // a K slice spans more than one LDS chunk
-};
-
-static GemmPlan plan_gemm(int n_rows, int k, int n_xcd) {
-  const int npair = k / (2 * kBlkK);         // pieces of 256 k-values
-  const int tiles_per_xcd = ceil_div(n_rows / kFragRows, n_xcd);
-  GemmPlan p;
-  p.S = npair / 2;                           // about one LDS chunk (2 pieces) per slice
-  if (p.S > 8) p.S = 8;
-  if (p.S < 1) p.S = 1;
-  if (p.S > 1) p.S &= ~1;                    // the reduction deals quads to waves for S = 1 or even
-  p.gpx = 32 / p.S;                          // aim at 32 units per XCD (one per CU)
-  if (p.gpx > tiles_per_xcd) p.gpx = tiles_per_xcd;
-  if (p.gpx < 1) p.gpx = 1;
-  // a slice that spans several LDS chunks keeps its accumulators in registers: one tile per wave
-  const int chunks = ceil_div(ceil_div(2 * npair, p.S), 4);     // LDS chunks of the longest slice
-  if (chunks > 1 && ceil_div(tiles_per_xcd, p.gpx) > 4) p.gpx = ceil_div(tiles_per_xcd, 4);
-  p.multi = chunks > 1;
-  return p;
-}
-
-// Fills the work split of one product into its argument block.
-static GemmPlan fill_plan(GemmArgs& a, int N, int K, int n_xcd) {
-  const GemmPlan p = plan_gemm(N, K, n_xcd);
-  a.N = N; a.K = K; a.S = p.S; a.gpx = p.gpx; a.n_xcd = n_xcd;
-  const int n_tiles = N / kFragRows, G = n_xcd * p.gpx, npieces = K / kBlkK;
-  a.tq = n_tiles / G; a.trem = n_tiles % G;
-  a.pq = npieces / p.S; a.prem = npieces % p.S;
-  a.inv_S = (65536u + p.S - 1) / p.S;      // exact for the unit numbers that occur (< 4096)
-  return p;
-}
-
-// Per-XCD extent of the split-K scratch regions for a product of N rows over K: units (gpx * S)
-// and partial tiles (gpx * (tiles per group, rounded up) * S), the largest over the XCD counts a
-// device can have.
-static void scratch_extent(int N, int K, int* ucap, int* tstride) {
-  for (int n_xcd = 1; n_xcd <= kXcds; n_xcd *= 2) {
-    GemmArgs a;
-    const GemmPlan p = fill_plan(a, N, K, n_xcd);
-    const int u = p.gpx * p.S, t = p.gpx * (a.tq + 1) * p.S;
-    if (u > *ucap) *ucap = u;
-    if (t > *tstride) *tstride = t;
-  }
-}
-
 // Workgroups that share the keys of one (episode, head, 16 queries) task of the tree attention:
 // more than one where the tasks alone would leave the chip short of waves (long prefix, one
 // episode), at least 8 key tiles each.
@@ -91,42 +41,6 @@ static int attention_splits(int n_tasks, int n_keys) {
   int s = 1;
   while (s < 8 && n_tasks * s < kAttSplitFill && (n_keys / kAttKeys) / (2 * s) >= 8) s *= 2;
   return s;
-}
-
-// Launch shape of one many-row product: columns per output block and workgroups per block
-// along K.  K is split (by powers of two, an even number of at least 8 k-steps each) while the
-// output blocks alone would fill less than about two thirds of the CUs.
-struct RowsPlan {
-  int tn, ksplit;
-};
-static RowsPlan rows_plan(int m_tiles, int N, int K, int n_xcd, bool may_widen) {
-  RowsPlan p;
-  p.tn = kRowsTN;
-  p.ksplit = 1;
-  const int cus = n_xcd * 32, nks = K / kFragK;
-  const int blocks = (N / kRowsTN) * m_tiles;
-  while (blocks * p.ksplit * 3 < cus * 2 && p.ksplit < kRowsMaxKsplit) {
-    const int s2 = p.ksplit * 2;
-    if (nks % s2 || (nks / s2) % 2 || nks / s2 < 8) break;
-    p.ksplit = s2;
-  }
-  // 384-column blocks where they give a whole number of rounds of the chip and 256-column blocks
-  // do not (q/k/v of the 7B shape with 8 row blocks: 256 workgroups instead of 384)
-  if (may_widen && p.ksplit == 1 && N % 384 == 0 && ((N / 384) * m_tiles) % cus == 0 && blocks % cus != 0)
-    p.tn = 384;
-  return p;
-}
-// bytes of float32 partial blocks the split products of a layer need at most (any XCD count)
-static size_t rows_part_bytes(int rows_pad, int H, int D, int F) {
-  size_t need = 0;
-  const int dims[4][2] = {{3 * D, H}, {H, D}, {2 * F, H}, {H, F}};
-  for (int n_xcd = 1; n_xcd <= kXcds; n_xcd *= 2)
-    for (int i = 0; i < 4; ++i) {
-      const RowsPlan p = rows_plan(rows_pad / kRowsTM, dims[i][0], dims[i][1], n_xcd, i == 0);
-      const size_t b = p.ksplit > 1 ? (size_t)p.ksplit * rows_pad * dims[i][0] * 4 : 0;
-      if (b > need) need = b;
-    }
-  return need;
 }
 
 static int device_xcds() {
@@ -142,73 +56,84 @@ static int device_xcds() {
   return cached[dev];
 }
 
+static int weight_format(const sv_model_cfg& c) { return c.dtype == SV_BF16_W8 ? 1 : (c.dtype == SV_BF16_W4 ? 2 : 0); }
+
+// The four products of a layer (bf16 models) and the head's, for one XCD count.
+struct LayerPlan {
+  ProductPlan qkv, o, gu, down;
+  int ucap;                    // workgroups per XCD, the largest of the four
+};
+static LayerPlan plan_layer(const sv_model_cfg& c, int m_rows, int n_xcd) {
+  const int H = c.hidden, D = c.n_heads * c.head_dim, F = c.mlp_dim, wf = weight_format(c);
+  LayerPlan p;
+  p.qkv = plan_product(m_rows, 3 * D, H, wf, n_xcd);
+  p.o = plan_product(m_rows, H, D, wf, n_xcd);
+  p.gu = plan_product(m_rows, 2 * F, H, wf, n_xcd);
+  p.down = plan_product(m_rows, H, F, wf, n_xcd);
+  p.ucap = 1;
+  for (const ProductPlan* q : {&p.qkv, &p.o, &p.gu, &p.down}) p.ucap = q->wg_x > p.ucap ? q->wg_x : p.ucap;
+  return p;
+}
+
 static WorkspaceLayout workspace_layout(const sv_model_cfg& c, int m_rows, int n_scored) {
   const size_t H = c.hidden, D = (size_t)c.n_heads * c.head_dim, F = c.mlp_dim;
   WorkspaceLayout L;
-  L.m_tiles = ceil_div(m_rows, kMTile);
-  L.m_pad = L.m_tiles * kMTile;
-  const size_t mp = L.m_pad, mt = L.m_tiles;
-  size_t n_max = 3 * D;
-  if (2 * F > n_max) n_max = 2 * F;
-  if (H > n_max) n_max = H;
+  memset(&L, 0, sizeof(L));
+  const size_t mp = (size_t)ceil_div(m_rows, kMTile) * kMTile;
+  L.n_rb = ceil_div(m_rows, 32);
+  L.m_pad = c.dtype == SV_F32 ? (int)mp : L.n_rb * 32;
   size_t o = 0;
   if (c.dtype != SV_F32) {
-    // sized for the worst split over the XCD counts a device can have
-    const int D_ = (int)D, H_ = (int)H, F_ = (int)F;
-    L.ucap = 1; L.tstride = 1;
-    scratch_extent(3 * D_, H_, &L.ucap, &L.tstride);
-    scratch_extent(H_, D_, &L.ucap, &L.tstride);
-    scratch_extent(2 * F_, H_, &L.ucap, &L.tstride);
-    scratch_extent(H_, F_, &L.ucap, &L.tstride);
-    L.counter_bytes = align_up((mt * kXcds * L.ucap * kCntStride + 64) * sizeof(int), kAlign);   // group counters + status word
+    // sized for the largest split over the XCD counts a device can have
+    const size_t mr = L.m_pad;
+    size_t wgs = 1, xch = 0, planes = H / 256;
+    for (int n_xcd = 1; n_xcd <= kXcds; n_xcd *= 2) {
+      const LayerPlan p = plan_layer(c, m_rows, n_xcd);
+      const size_t n = (size_t)n_xcd * p.ucap;
+      wgs = n > wgs ? n : wgs;
+      for (const ProductPlan* q : {&p.qkv, &p.o, &p.gu, &p.down}) {
+        const size_t x = n * q->unit_stride * 16;
+        xch = x > xch ? x : xch;
+      }
+      for (const ProductPlan* q : {&p.o, &p.down}) planes = (size_t)q->n_planes > planes ? q->n_planes : planes;
+    }
+    L.counter_bytes = align_up((wgs * kCntStride + 64) * sizeof(int), kAlign);   // group counters + status word
     L.counters = o; o += L.counter_bytes;
-    L.sumsq = o;    o = align_up(o + mt * kXcds * L.ucap * kMTile * 4, kAlign);
-    // partial tiles: 16-bit data (4 KiB each) in the first half of the region, one scale each behind it
-    L.part_bytes = align_up(mt * kXcds * L.tstride * (size_t)kTileFloats * 4, 2 * kAlign);
-    L.part = o;     o += L.part_bytes;
-    L.xhat = o;
+    L.xs_x = o;     o = align_up(o + mr * H * 4, kAlign);
+    L.xs_attn = o;  o = align_up(o + mr * D * 4, kAlign);
+    L.xs_act = o;   o = align_up(o + mr * F * 4, kAlign);
+    L.ssq = o;      o = align_up(o + mr * planes * 4, kAlign);
+    L.xch = o;      o = align_up(o + xch, kAlign);
+    L.q = o;        o = align_up(o + mr * D * 4, kAlign);
+    L.attn = o;     o = align_up(o + mr * D * 4, kAlign);
+    // partial results of the tree attention when the keys of a task are split
+    L.att_part = o; o = align_up(o + 8 * mr * c.n_heads * kAttPartStride * 4, kAlign);
   } else {
-    L.counter_bytes = 0;
-    L.ucap = L.tstride = 0;
-    L.counters = L.sumsq = o;
-    L.part_bytes = align_up(mp * n_max * 4, kAlign);
-    L.part = o;     o += L.part_bytes;
+    size_t n_max = 3 * D;
+    if (2 * F > n_max) n_max = 2 * F;
+    if (H > n_max) n_max = H;
+    L.part = o;     o = align_up(o + mp * n_max * 4, kAlign);
     L.xhat = o;     o = align_up(o + mp * H * 4, kAlign);
-  }
-  L.q = o;           o = align_up(o + mp * D * 4, kAlign);
-  L.attn = o;        o = align_up(o + mp * D * 4, kAlign);
-  L.act = o;         o = align_up(o + mp * F * 4, kAlign);
-  // many rows (bf16 weights, more than two row tiles): activation fragments of one product,
-  // 1 / rms of the rows, float32 partial blocks of the products that split K
-  L.rows_xs = L.rows_rstd = L.rows_part = 0;
-  L.rows_pad = 0;
-  if (c.dtype == SV_BF16 && mt > kRowsMinTiles) {
-    size_t k_max = H > D ? H : D;
-    if (F > k_max) k_max = F;
-    L.rows_pad = ceil_div(m_rows, kRowsTM) * kRowsTM;
-    L.rows_xs = o;   o = align_up(o + (size_t)L.rows_pad * k_max * 4, kAlign);
-    L.rows_rstd = o; o = align_up(o + (size_t)L.rows_pad * 4, kAlign);
-    L.rows_part = o; o = align_up(o + rows_part_bytes(L.rows_pad, (int)H, (int)(c.n_heads * c.head_dim), (int)F), kAlign);
-  }
-  // partial results of the tree attention when the keys of a task are split (bf16 models)
-  L.att_part = 0;
-  if (c.dtype != SV_F32) {
-    L.att_part = o;
-    o = align_up(o + (size_t)8 * mp * c.n_heads * kAttPartStride * 4, kAlign);
+    L.q = o;        o = align_up(o + mp * D * 4, kAlign);
+    L.attn = o;     o = align_up(o + mp * D * 4, kAlign);
+    L.act = o;      o = align_up(o + mp * F * 4, kAlign);
   }
   L.head_z = o;      o = align_up(o + mp * H * 4, kAlign);
   L.head_logits = o; o = align_up(o + mp * (size_t)(n_scored > 0 ? n_scored : 0) * 4 * 16, kAlign);   // up to 16 K-slice planes
   // (the regions above do not move with n_scored: a layer call finds them without knowing it)
-  L.head_cnt = L.head_cnt_bytes = L.head_sumsq = L.head_part = L.head_part_bytes = 0;
-  L.head_ucap = L.head_tstride = 0;
   if (c.dtype != SV_F32 && n_scored > 0 && n_scored % kFragRows == 0) {
-    L.head_ucap = 1; L.head_tstride = 1;
-    scratch_extent(n_scored, (int)H, &L.head_ucap, &L.head_tstride);
-    L.head_cnt_bytes = align_up(mt * kXcds * L.head_ucap * kCntStride * sizeof(int), kAlign);
-    L.head_cnt = o;   o += L.head_cnt_bytes;
-    L.head_sumsq = o; o = align_up(o + mt * kXcds * L.head_ucap * kMTile * 4, kAlign);
-    L.head_part_bytes = align_up(mt * kXcds * L.head_tstride * (size_t)kTileFloats * 4, 2 * kAlign);
-    L.head_part = o;  o += L.head_part_bytes;
+    size_t wgs = 1, xch = 0;
+    for (int n_xcd = 1; n_xcd <= kXcds; n_xcd *= 2) {
+      const ProductPlan p = plan_product(m_rows, n_scored, (int)H, 0, n_xcd);
+      const size_t n = (size_t)n_xcd * p.wg_x, x = n * p.unit_stride * 16;
+      wgs = n > wgs ? n : wgs;
+      xch = x > xch ? x : xch;
+    }
+    L.head_cnt_bytes = align_up(wgs * kCntStride * sizeof(int), kAlign);
+    L.head_cnt = o; o += L.head_cnt_bytes;
+    L.head_xs = o;  o = align_up(o + (size_t)L.m_pad * H * 4, kAlign);
+    L.head_ssq = o; o = align_up(o + (size_t)L.m_pad * (H / 256) * 4, kAlign);
+    L.head_xch = o; o = align_up(o + xch, kAlign);
   }
   L.total = o;
   return L;
@@ -250,7 +175,7 @@ __global__ void zero_ints(int* p, size_t n) {
 
 // ---- float32 models: plain kernels, one launch per step of the layer ----------------------
 
-static int verify_layer_f32(const sv_model_cfg& c, const char* packed, float* x,
+static int verify_layer_f32(const sv_model_cfg& c, const WorkspaceLayout& wl, const char* packed, float* x,
                             const sv_kv_view& kv, const sv_tree& tree, int B, char* ws,
                             hipStream_t st, hipEvent_t* ev) {
   const int T_ = tree.n_nodes, M = B * T_;
@@ -259,7 +184,6 @@ static int verify_layer_f32(const sv_model_cfg& c, const char* packed, float* x,
   };
   const int H = c.hidden, D = c.n_heads * c.head_dim, F = c.mlp_dim;
   const PackedLayout pl = packed_layout(c);
-  const WorkspaceLayout wl = workspace_layout(c, M, 0);
   const float* g1 = (const float*)(packed + pl.g1);
   const float* g2 = (const float*)(packed + pl.g2);
   float* xhat = (float*)(ws + wl.xhat);
@@ -301,172 +225,66 @@ static int verify_layer_f32(const sv_model_cfg& c, const char* packed, float* x,
 
 // ---- bf16 models: five launches per layer ---------------------------------------------------
 
-static int verify_layer_bf16(const sv_model_cfg& c, const char* packed, float* x,
-                             const sv_kv_view& kv, const sv_tree& tree, int B, char* ws,
-                             hipStream_t st, hipEvent_t* ev) {
-  const int T_ = tree.n_nodes, M = B * T_;
-  auto mark = [&](int i) {
-    if (ev) (void)hipEventRecord(ev[i], st);
-  };
-  const int H = c.hidden, D = c.n_heads * c.head_dim, F = c.mlp_dim;
-  const PackedLayout pl = packed_layout(c);
-  const WorkspaceLayout wl = workspace_layout(c, M, 0);
-  const int n_xcd = device_xcds();
-  size_t n_max = 3 * (size_t)D;
-  if (2 * (size_t)F > n_max) n_max = 2 * (size_t)F;
-  if ((size_t)H > n_max) n_max = H;
-  unsigned* counters = (unsigned*)(ws + wl.counters);
-  GemmArgs a;
-  memset(&a, 0, sizeof(a));
-  a.M = M;
-  a.n_xcd = n_xcd;
-  // partial tiles: packed data in the first half of the region, one inverse scale per tile behind it
-  a.part16 = (uint4*)(ws + wl.part);
-  a.pscale = (float*)(ws + wl.part + wl.part_bytes / 2);
-  a.sumsq = (float*)(ws + wl.sumsq);
-  a.group_cnt = counters;
-  a.status = (int*)(ws + wl.counters + wl.counter_bytes) - 1;   // last word of the counter region
-  a.eps = c.rms_eps;
-  float* q = (float*)(ws + wl.q);
-  float* attn = (float*)(ws + wl.attn);
-  float* act = (float*)(ws + wl.act);
-  dim3 grid(n_xcd, 1, 1);                    // workgroup (x, y) -> XCD x, unit (and row tile) y
-  const bool rows = wl.m_tiles > 1;
-  bool multi = false;
-  a.ucap = wl.ucap; a.tstride = wl.tstride;
-  auto shape = [&](int N, int K) {
-    const GemmPlan p = fill_plan(a, N, K, n_xcd);
-    grid.y = p.gpx * p.S * wl.m_tiles;
-    multi = p.multi;
-  };
-  // the kernel form for the shape just planned: single- or multi-chunk K slices
-#define SV_LAUNCH_GEMM2(PRO, EPI, WF, ROWS)                                             \
-  do {                                                                                 \
-    if (multi) gemm_stream_bf16<PRO, EPI, true, WF, ROWS><<<grid, 256, 0, st>>>(a);    \
-    else gemm_stream_bf16<PRO, EPI, false, WF, ROWS><<<grid, 256, 0, st>>>(a);         \
-  } while (0)
-#define SV_LAUNCH_GEMM(PRO, EPI)                                                       \
-  do {                                                                                 \
-    if (wf == 2 && rows) SV_LAUNCH_GEMM2(PRO, EPI, 2, true);                           \
-    else if (wf == 2) SV_LAUNCH_GEMM2(PRO, EPI, 2, false);                             \
-    else if (wf == 1 && rows) SV_LAUNCH_GEMM2(PRO, EPI, 1, true);                      \
-    else if (wf == 1) SV_LAUNCH_GEMM2(PRO, EPI, 1, false);                             \
-    else if (rows) SV_LAUNCH_GEMM2(PRO, EPI, 0, true);                                 \
-    else SV_LAUNCH_GEMM2(PRO, EPI, 0, false);                                          \
-  } while (0)
-
-  const int wf = c.dtype == SV_BF16_W8 ? 1 : (c.dtype == SV_BF16_W4 ? 2 : 0);   // weight format of the kernels
-  const bool w8 = wf != 0;                                                        // row scales present
-  a.X = x; a.gain = (const float*)(packed + pl.g1); a.Wp = (const uint4*)(packed + pl.wqkv);
-  a.wscale = w8 ? (const float*)(packed + pl.sqkv) : nullptr;
-  shape(3 * D, H);
-  a.q_out = q; a.kc = (bf16_t*)kv.k; a.vc = (bf16_t*)kv.v; a.depth = tree.depth;
-  a.prefix_len = kv.prefix_len; a.p_max = kv.prefix_len_max; a.cap = kv.capacity; a.T = T_;
-  a.nh = c.n_heads; a.theta = c.rope_theta;
-  mark(0);
-  SV_LAUNCH_GEMM(PRO_GAIN, EPI_QKV);
-  mark(1);
-  mark(2);
-  {
-    const int ns = attention_splits(B * ceil_div(T_, kAttQ) * c.n_heads, kv.prefix_len_max + T_);
-    float* apart = (float*)(ws + wl.att_part);
-    tree_attention_mfma<4><<<dim3(B * ceil_div(T_, kAttQ), c.n_heads, ns), 256, 0, st>>>(
-        q, (const bf16_t*)kv.k, (const bf16_t*)kv.v, kv.prefix_len, kv.prefix_len_max,
-        tree.anc_mask, tree.n_words, T_, c.n_heads, kv.capacity, attn, apart, M);
-    if (ns > 1) attention_merge_kernel<<<dim3(M, c.n_heads), 128, 0, st>>>(apart, ns, M, c.n_heads, attn);
+// What the layers of one call have in common.
+struct LayerCall {
+  WorkspaceLayout wl;
+  LayerPlan plan;
+  int n_xcd;
+};
+static LayerCall layer_call(const sv_model_cfg& c, int m_rows) {
+  LayerCall l;
+  l.wl = workspace_layout(c, m_rows, 0);
+  if (c.dtype != SV_F32) {
+    l.n_xcd = device_xcds();
+    l.plan = plan_layer(c, m_rows, l.n_xcd);
   }
-  mark(3);
-  a.X = attn; a.gain = nullptr; a.Wp = (const uint4*)(packed + pl.wo);
-  a.wscale = w8 ? (const float*)(packed + pl.so) : nullptr;
-  shape(H, D);
-  a.x_res = x; a.x_io = x;
-  SV_LAUNCH_GEMM(PRO_PLAIN, EPI_RESID);
-  mark(4);
-  a.X = x; a.gain = (const float*)(packed + pl.g2); a.Wp = (const uint4*)(packed + pl.wgu);
-  a.wscale = w8 ? (const float*)(packed + pl.sgu) : nullptr;
-  shape(2 * F, H);
-  a.act = act;
-  mark(5);
-  SV_LAUNCH_GEMM(PRO_GAIN, EPI_SWIGLU);
-  mark(6);
-  a.X = act; a.gain = nullptr; a.Wp = (const uint4*)(packed + pl.wd);
-  a.wscale = w8 ? (const float*)(packed + pl.sd) : nullptr;
-  shape(H, F);
-  a.x_res = x; a.x_io = x;
-  mark(7);
-  SV_LAUNCH_GEMM(PRO_PLAIN, EPI_RESID);
-  mark(8);
-#undef SV_LAUNCH_GEMM
-#undef SV_LAUNCH_GEMM2
-  return launch_status();
+  return l;
 }
 
-// ---- bf16 models, many rows: products bound by the matrix cores (sv_gemm_rows.h) -----------
-
-static int verify_layer_rows(const sv_model_cfg& c, const char* packed, float* x,
-                             const sv_kv_view& kv, const sv_tree& tree, int B, char* ws,
-                             hipStream_t st, hipEvent_t* ev) {
+// first: x has to be turned into fragments here (otherwise the layer before has left them in the
+// workspace); next_packed: the layer after this one, whose first gain goes into the fragments this layer
+// leaves (NULL: it leaves none).
+static int verify_layer_bf16(const sv_model_cfg& c, const LayerCall& lc, const char* packed, float* x,
+                             const sv_kv_view& kv, const sv_tree& tree, int B, char* ws, hipStream_t st,
+                             hipEvent_t* ev, bool first, const char* next_packed) {
   const int T_ = tree.n_nodes, M = B * T_;
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], st);
   };
-  const int H = c.hidden, D = c.n_heads * c.head_dim, F = c.mlp_dim;
+  const int H = c.hidden, D = c.n_heads * c.head_dim, F = c.mlp_dim, wf = weight_format(c);
   const PackedLayout pl = packed_layout(c);
-  const WorkspaceLayout wl = workspace_layout(c, M, 0);
-  const int n_xcd = device_xcds();
-  uint4* xs = (uint4*)(ws + wl.rows_xs);
-  float* rstd = (float*)(ws + wl.rows_rstd);
-  float* part = (float*)(ws + wl.rows_part);
+  const WorkspaceLayout& wl = lc.wl;
+  uint4* xs_x = (uint4*)(ws + wl.xs_x);
+  uint4* xs_attn = (uint4*)(ws + wl.xs_attn);
+  uint4* xs_act = (uint4*)(ws + wl.xs_act);
+  float* ssq = (float*)(ws + wl.ssq);
   float* q = (float*)(ws + wl.q);
   float* attn = (float*)(ws + wl.attn);
-  float* act = (float*)(ws + wl.act);
-  RowsArgs a;
-  memset(&a, 0, sizeof(a));
-  a.Xs = xs; a.M = M; a.m_tiles = wl.rows_pad / kRowsTM; a.n_xcd = n_xcd; a.part = part;
-  a.q_out = q; a.kc = (bf16_t*)kv.k; a.vc = (bf16_t*)kv.v; a.depth = tree.depth;
-  a.prefix_len = kv.prefix_len; a.p_max = kv.prefix_len_max; a.cap = kv.capacity; a.T = T_;
-  a.nh = c.n_heads; a.theta = c.rope_theta; a.act = act;
-  const int mb = wl.rows_pad / 32;
-  auto split = [&](const float* src, const float* gain, int K) {
-    if (gain) {
-      rows_rstd_kernel<<<M, 256, 0, st>>>(src, K, c.rms_eps, rstd);
-      split_rows_kernel<true><<<dim3(mb, K / 256), 256, 0, st>>>(src, gain, rstd, M, K, xs);
-    } else {
-      split_rows_kernel<false><<<dim3(mb, K / 256), 256, 0, st>>>(src, nullptr, nullptr, M, K, xs);
-    }
+  ProductScratch scratch;
+  scratch.xch = (f32x4_t*)(ws + wl.xch);
+  scratch.group_cnt = (unsigned*)(ws + wl.counters);
+  scratch.status = (int*)(ws + wl.counters + wl.counter_bytes) - 1;   // last word of the counter region
+  scratch.ucap = lc.plan.ucap;
+  auto epilogue = [&](int K, size_t scale_off) {
+    EpiArgs e;
+    memset(&e, 0, sizeof(e));
+    e.M = M; e.n_rb = wl.n_rb; e.m_pad = wl.m_pad; e.K = K; e.eps = c.rms_eps;
+    e.wscale = wf ? (const float*)(packed + scale_off) : nullptr;
+    return e;
   };
-  const size_t plane = (size_t)wl.rows_pad;       // rows of one partial block
-  // One product: the unsplit kernel with its fused epilogue, or the K-split kernel followed by the
-  // reduction that carries the same epilogue.
-  auto product = [&](int epi, size_t w_off, int N, int K) {
-    const RowsPlan p = rows_plan(a.m_tiles, N, K, n_xcd, epi == EPI_QKV);
-    a.Wp = (const uint4*)(packed + w_off); a.N = N; a.K = K; a.n_tiles = N / p.tn; a.ksplit = p.ksplit;
-    const dim3 grid(n_xcd, ceil_div(a.n_tiles, n_xcd) * a.m_tiles, p.ksplit);
-    if (p.ksplit == 1 && epi == EPI_QKV) {
-      if (p.tn == 384) gemm_rows_kernel<EPI_QKV, false, 6><<<grid, 256, 0, st>>>(a);
-      else gemm_rows_kernel<EPI_QKV, false, 4><<<grid, 256, 0, st>>>(a);
-      return;
-    }
-    if (p.ksplit == 1 && epi == EPI_SWIGLU) {
-      gemm_rows_kernel<EPI_SWIGLU, false, 4><<<grid, 256, 0, st>>>(a);
-      return;
-    }
-    if (a.m_tiles == 1) gemm_rows_kernel<EPI_RESID, true, 4, true><<<grid, 256, 0, st>>>(a);
-    else gemm_rows_kernel<EPI_RESID, true, 4><<<grid, 256, 0, st>>>(a);
-    if (epi == EPI_RESID) {
-      const size_t n4 = (size_t)M * N / 4;
-      rows_reduce_resid_kernel<<<(unsigned)((n4 + 255) / 256), 256, 0, st>>>(part, p.ksplit, plane * N, x, x, n4);
-    } else if (epi == EPI_SWIGLU) {
-      const size_t n = (size_t)M * (N / 32) * 4;
-      rows_reduce_swiglu_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(part, p.ksplit, plane * N, M, N, act);
-    } else {
-      const size_t n = (size_t)M * (N / 32) * 16;
-      rows_reduce_qkv_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(part, p.ksplit, plane * N, a);
-    }
+  auto product = [&](const ProductPlan& p, int epi, const uint4* xs, size_t w_off, int N, int K, const EpiArgs& e) {
+    launch_product(p, epi, wf, lc.n_xcd, xs, (const uint4*)(packed + w_off), N, K, scratch, e, st);
   };
+  if (first)
+    split_gain_kernel<<<dim3(wl.n_rb, H / 256), 256, 0, st>>>(x, (const float*)(packed + pl.g1), M, H, wl.m_pad, wl.n_rb, xs_x, ssq);
   mark(0);
-  split(x, (const float*)(packed + pl.g1), H);
-  product(EPI_QKV, pl.wqkv, 3 * D, H);
+  {
+    EpiArgs e = epilogue(H, pl.sqkv);
+    e.ssq = ssq; e.n_ssq = first ? H / 256 : lc.plan.down.n_planes;
+    e.q_out = q; e.kc = (bf16_t*)kv.k; e.vc = (bf16_t*)kv.v; e.depth = tree.depth; e.prefix_len = kv.prefix_len;
+    e.p_max = kv.prefix_len_max; e.cap = kv.capacity; e.T = T_; e.nh = c.n_heads; e.theta = c.rope_theta;
+    product(lc.plan.qkv, EPI_QKV, xs_x, pl.wqkv, 3 * D, H, e);
+  }
   mark(1);
   mark(2);
   {
@@ -474,20 +292,33 @@ static int verify_layer_rows(const sv_model_cfg& c, const char* packed, float* x
     float* apart = (float*)(ws + wl.att_part);
     tree_attention_mfma<4><<<dim3(B * ceil_div(T_, kAttQ), c.n_heads, ns), 256, 0, st>>>(
         q, (const bf16_t*)kv.k, (const bf16_t*)kv.v, kv.prefix_len, kv.prefix_len_max,
-        tree.anc_mask, tree.n_words, T_, c.n_heads, kv.capacity, attn, apart, M);
-    if (ns > 1) attention_merge_kernel<<<dim3(M, c.n_heads), 128, 0, st>>>(apart, ns, M, c.n_heads, attn);
+        tree.anc_mask, tree.n_words, T_, c.n_heads, kv.capacity, attn, xs_attn, wl.n_rb, apart, M);
+    if (ns > 1)
+      attention_merge_kernel<<<dim3(M, ceil_div(c.n_heads, 16)), 256, 0, st>>>(apart, ns, M, c.n_heads, attn, xs_attn, wl.n_rb);
   }
   mark(3);
-  split(attn, nullptr, D);
-  product(EPI_RESID, pl.wo, H, D);
+  {
+    EpiArgs e = epilogue(D, pl.so);
+    e.x = x; e.next_gain = (const float*)(packed + pl.g2); e.xs_out = xs_x; e.ssq_out = ssq;
+    product(lc.plan.o, EPI_RESID, xs_attn, pl.wo, H, D, e);
+  }
   mark(4);
   mark(5);
-  split(x, (const float*)(packed + pl.g2), H);
-  product(EPI_SWIGLU, pl.wgu, 2 * F, H);
+  {
+    EpiArgs e = epilogue(H, pl.sgu);
+    e.ssq = ssq; e.n_ssq = lc.plan.o.n_planes; e.xs_out = xs_act;
+    product(lc.plan.gu, EPI_SWIGLU, xs_x, pl.wgu, 2 * F, H, e);
+  }
   mark(6);
   mark(7);
-  split(act, nullptr, F);
-  product(EPI_RESID, pl.wd, H, F);
+  {
+    EpiArgs e = epilogue(F, pl.sd);
+    e.x = x;
+    if (next_packed) {
+      e.next_gain = (const float*)(next_packed + pl.g1); e.xs_out = xs_x; e.ssq_out = ssq;
+    }
+    product(lc.plan.down, EPI_RESID, xs_act, pl.wd, H, F, e);
+  }
   mark(8);
   return launch_status();
 }
@@ -504,25 +335,24 @@ static int pack_layer_t(const sv_model_cfg& c, const sv_layer_weights& w, char* 
   struct Piece {
     const void* src; size_t dst; int rows, k;
     int plain_off;                 // float32: first destination row
-    int mode, off;                 // bf16: see pack_rows_mfma
+    int mode, off, tiles;          // bf16: see pack_rows; tiles of the whole fused matrix
   };
   const Piece pieces[] = {
-      {w.wq, pl.wqkv, D, H, 0, PACK_PAIR16_HEAD, 0},
-      {w.wk, pl.wqkv, D, H, D, PACK_PAIR16_HEAD, D},
-      {w.wv, pl.wqkv, D, H, 2 * D, PACK_PAIR16_HEAD, 2 * D},
-      {w.wo, pl.wo, H, D, 0, PACK_PLAIN, 0},
-      {w.wg, pl.wgu, F, H, 0, PACK_PAIR16_GU, 0},
-      {w.wu, pl.wgu, F, H, F, PACK_PAIR16_GU, 16},
-      {w.wd, pl.wd, H, F, 0, PACK_PLAIN, 0}};
+      {w.wq, pl.wqkv, D, H, 0, PACK_PAIR16_HEAD, 0, 3 * D / 32},
+      {w.wk, pl.wqkv, D, H, D, PACK_PAIR16_HEAD, D, 3 * D / 32},
+      {w.wv, pl.wqkv, D, H, 2 * D, PACK_PAIR16_HEAD, 2 * D, 3 * D / 32},
+      {w.wo, pl.wo, H, D, 0, PACK_PLAIN, 0, H / 32},
+      {w.wg, pl.wgu, F, H, 0, PACK_PAIR16_GU, 0, F / 16},
+      {w.wu, pl.wgu, F, H, F, PACK_PAIR16_GU, 16, F / 16},
+      {w.wd, pl.wd, H, F, 0, PACK_PLAIN, 0, H / 32}};
   for (const Piece& p : pieces) {
     if (c.dtype == SV_F32) {
       const size_t n = (size_t)p.rows * p.k;
       pack_rows_plain<float><<<(unsigned)((n + 255) / 256), 256, 0, st>>>(
           (const float*)p.src, (float*)(packed + p.dst), n, (size_t)p.plain_off * p.k);
     } else {
-      const size_t chunks = (size_t)p.rows * (p.k / 8);
-      pack_rows_mfma<<<(unsigned)((chunks + 255) / 256), 256, 0, st>>>(
-          (const uint4*)p.src, (uint4*)(packed + p.dst), p.rows, p.k, p.mode, p.off);
+      pack_rows<uint4, 0><<<dim3(p.rows / 32, p.k / 256), 256, 0, st>>>(
+          (const uint4*)p.src, (uint4*)(packed + p.dst), p.k, p.tiles, p.mode, p.off);
     }
   }
   return launch_status();
@@ -568,8 +398,8 @@ static int scratch_address(unsigned char** out) {
   return SV_OK;
 }
 
-// Head on the streaming kernel: RMSNorm gain in the staging pass, 1 / rms after the reduction,
-// logits to the workspace, then the row argmax.
+// Packed head: the rows become fragments with the final gain, 1 / rms is applied to the sums, logits to
+// the workspace, then the row argmax.
 static int head_packed(const sv_model_cfg& c, const char* packed, const float* x, int n_rows,
                        int lo, int hi, int32_t* out_token, float* out_logits, char* ws,
                        hipStream_t st) {
@@ -578,26 +408,20 @@ static int head_packed(const sv_model_cfg& c, const char* packed, const float* x
   const HeadLayout hl = head_layout(c, n);
   const int n_xcd = device_xcds();
   float* logits = (float*)(ws + wl.head_logits);
-  GemmArgs a;
-  memset(&a, 0, sizeof(a));
-  const GemmPlan p = fill_plan(a, n, H, n_xcd);
-  a.X = x; a.gain = (const float*)(packed + hl.gain); a.Wp = (const uint4*)(packed + hl.w);
-  a.M = n_rows; a.ucap = wl.head_ucap; a.tstride = wl.head_tstride;
-  a.part16 = (uint4*)(ws + wl.head_part);
-  a.pscale = (float*)(ws + wl.head_part + wl.head_part_bytes / 2);
-  a.sumsq = (float*)(ws + wl.head_sumsq);
-  a.group_cnt = (unsigned*)(ws + wl.head_cnt);
-  a.status = (int*)(ws + wl.counters + wl.counter_bytes) - 1;   // the layers' status word
-  a.eps = c.rms_eps;
-  a.x_io = logits;
-  const dim3 grid(n_xcd, p.gpx * p.S * wl.m_tiles);
-  if (wl.m_tiles > 1) {
-    if (p.multi) gemm_stream_bf16<PRO_GAIN, EPI_OUT, true, false, true><<<grid, 256, 0, st>>>(a);
-    else gemm_stream_bf16<PRO_GAIN, EPI_OUT, false, false, true><<<grid, 256, 0, st>>>(a);
-  } else {
-    if (p.multi) gemm_stream_bf16<PRO_GAIN, EPI_OUT, true, false, false><<<grid, 256, 0, st>>>(a);
-    else gemm_stream_bf16<PRO_GAIN, EPI_OUT, false, false, false><<<grid, 256, 0, st>>>(a);
-  }
+  uint4* xs = (uint4*)(ws + wl.head_xs);
+  float* ssq = (float*)(ws + wl.head_ssq);
+  split_gain_kernel<<<dim3(wl.n_rb, H / 256), 256, 0, st>>>(x, (const float*)(packed + hl.gain), n_rows, H, wl.m_pad, wl.n_rb, xs, ssq);
+  const ProductPlan p = plan_product(n_rows, n, H, 0, n_xcd);
+  ProductScratch scratch;
+  scratch.xch = (f32x4_t*)(ws + wl.head_xch);
+  scratch.group_cnt = (unsigned*)(ws + wl.head_cnt);
+  scratch.status = (int*)(ws + wl.counters + wl.counter_bytes) - 1;   // the layers' status word
+  scratch.ucap = p.wg_x;
+  EpiArgs e;
+  memset(&e, 0, sizeof(e));
+  e.M = n_rows; e.n_rb = wl.n_rb; e.m_pad = wl.m_pad; e.K = H; e.eps = c.rms_eps;
+  e.ssq = ssq; e.n_ssq = H / 256; e.out = logits;
+  launch_product(p, EPI_OUT, 0, n_xcd, xs, (const uint4*)(packed + hl.w), n, H, scratch, e, st);
   argmax_rows_wide<<<n_rows, 256, 0, st>>>(logits, out_logits, n, lo, out_token);
   return launch_status();
 }
@@ -691,24 +515,22 @@ static int pack_layer_codes(const sv_model_cfg* cfg, const sv_layer_weights* raw
   pack_gain<bf16_t><<<ceil_div(H, 256), 256, 0, st>>>((const bf16_t*)raw->g1, (float*)(packed + pl.g1), H);
   pack_gain<bf16_t><<<ceil_div(H, 256), 256, 0, st>>>((const bf16_t*)raw->g2, (float*)(packed + pl.g2), H);
   struct Piece {
-    const void* src; const float* scale; size_t dst, sdst; int rows, k, mode, off;
+    const void* src; const float* scale; size_t dst, sdst; int rows, k, mode, off, tiles;
   };
   const Piece pieces[] = {
-      {raw->wq, sc->sq, pl.wqkv, pl.sqkv, D, H, PACK_PAIR16_HEAD, 0},
-      {raw->wk, sc->sk, pl.wqkv, pl.sqkv, D, H, PACK_PAIR16_HEAD, D},
-      {raw->wv, sc->sv, pl.wqkv, pl.sqkv, D, H, PACK_PAIR16_HEAD, 2 * D},
-      {raw->wo, sc->so, pl.wo, pl.so, H, D, PACK_PLAIN, 0},
-      {raw->wg, sc->sg, pl.wgu, pl.sgu, F, H, PACK_PAIR16_GU, 0},
-      {raw->wu, sc->su, pl.wgu, pl.sgu, F, H, PACK_PAIR16_GU, 16},
-      {raw->wd, sc->sd, pl.wd, pl.sd, H, F, PACK_PLAIN, 0}};
+      {raw->wq, sc->sq, pl.wqkv, pl.sqkv, D, H, PACK_PAIR16_HEAD, 0, 3 * D / 32},
+      {raw->wk, sc->sk, pl.wqkv, pl.sqkv, D, H, PACK_PAIR16_HEAD, D, 3 * D / 32},
+      {raw->wv, sc->sv, pl.wqkv, pl.sqkv, D, H, PACK_PAIR16_HEAD, 2 * D, 3 * D / 32},
+      {raw->wo, sc->so, pl.wo, pl.so, H, D, PACK_PLAIN, 0, H / 32},
+      {raw->wg, sc->sg, pl.wgu, pl.sgu, F, H, PACK_PAIR16_GU, 0, F / 16},
+      {raw->wu, sc->su, pl.wgu, pl.sgu, F, H, PACK_PAIR16_GU, 16, F / 16},
+      {raw->wd, sc->sd, pl.wd, pl.sd, H, F, PACK_PLAIN, 0, H / 32}};
   for (const Piece& p : pieces) {
-    const size_t n8 = (size_t)p.rows * (p.k / 8);
+    const dim3 grid(p.rows / 32, p.k / 256);
     if (dtype == SV_BF16_W4)
-      pack_rows_mfma_w4<<<(unsigned)((n8 + 255) / 256), 256, 0, st>>>(
-          (const uint32_t*)p.src, (uint32_t*)(packed + p.dst), p.rows, p.k, p.mode, p.off);
+      pack_rows<uint32_t, 2><<<grid, 256, 0, st>>>((const uint32_t*)p.src, (uint32_t*)(packed + p.dst), p.k, p.tiles, p.mode, p.off);
     else
-      pack_rows_mfma_w8<<<(unsigned)((n8 + 255) / 256), 256, 0, st>>>(
-          (const uint2*)p.src, (uint2*)(packed + p.dst), p.rows, p.k, p.mode, p.off);
+      pack_rows<uint2, 1><<<grid, 256, 0, st>>>((const uint2*)p.src, (uint2*)(packed + p.dst), p.k, p.tiles, p.mode, p.off);
     pack_row_scales<<<ceil_div(p.rows, 256), 256, 0, st>>>(p.scale, (float*)(packed + p.sdst), p.rows,
                                                            p.mode, p.off);
   }
@@ -780,6 +602,15 @@ int sv_workspace_region(const sv_model_cfg* cfg, int B, int T, int n_scored, int
   return SV_OK;
 }
 
+static int verify_layer_dispatch(const sv_model_cfg& c, const LayerCall& lc, const void* packed, float* x,
+                                 const sv_kv_view& kv, const sv_tree& tree, int B, void* workspace, void* stream,
+                                 hipEvent_t* ev, bool first, const void* next_packed) {
+  if (c.dtype == SV_F32)
+    return verify_layer_f32(c, lc.wl, (const char*)packed, x, kv, tree, B, (char*)workspace, (hipStream_t)stream, ev);
+  return verify_layer_bf16(c, lc, (const char*)packed, x, kv, tree, B, (char*)workspace, (hipStream_t)stream, ev, first,
+                           (const char*)next_packed);
+}
+
 static int verify_layer_checked(const sv_model_cfg* cfg, const void* packed, float* x,
                                 const sv_kv_view* kv, const sv_tree* tree, int B,
                                 void* workspace, size_t ws_bytes, void* stream,
@@ -796,17 +627,10 @@ static int verify_layer_checked(const sv_model_cfg* cfg, const void* packed, flo
   if (kv->prefix_len_max < 0 || (long long)kv->capacity < (long long)kv->prefix_len_max + T)
     return SV_ERR_SHAPE;
   if ((long long)B * cfg->n_heads * kv->capacity >= (1ll << 31)) return SV_ERR_SHAPE;   // cache rows are indexed in 32 bits
-  if (((uintptr_t)workspace % kAlign) || ((uintptr_t)packed % kAlign) ||
-      ws_bytes < workspace_layout(*cfg, B * T, 0).total)
-    return SV_ERR_WORKSPACE;
-  if (cfg->dtype == SV_F32)
-    return verify_layer_f32(*cfg, (const char*)packed, x, *kv, *tree, B, (char*)workspace,
-                            (hipStream_t)stream, ev);
-  if (cfg->dtype == SV_BF16 && ceil_div(B * T, kMTile) > kRowsMinTiles)
-    return verify_layer_rows(*cfg, (const char*)packed, x, *kv, *tree, B, (char*)workspace,
-                             (hipStream_t)stream, ev);
-  return verify_layer_bf16(*cfg, (const char*)packed, x, *kv, *tree, B, (char*)workspace,
-                           (hipStream_t)stream, ev);
+  if (((uintptr_t)workspace % kAlign) || ((uintptr_t)packed % kAlign)) return SV_ERR_WORKSPACE;
+  const LayerCall lc = layer_call(*cfg, B * T);
+  if (ws_bytes < lc.wl.total) return SV_ERR_WORKSPACE;
+  return verify_layer_dispatch(*cfg, lc, packed, x, *kv, *tree, B, workspace, stream, ev, true, nullptr);
 }
 
 int sv_verify_layer(const sv_model_cfg* cfg, const void* packed, float* x, const sv_kv_view* kv,
@@ -828,7 +652,7 @@ int sv_verify_layer_timed(const sv_model_cfg* cfg, const void* packed, float* x,
 
 static int verify_stack_args(const sv_model_cfg* cfg, int n_layers, const void* const* packed,
                              float* x, const sv_kv_view* kv, const sv_tree* tree, int B,
-                             void* workspace, size_t ws_bytes) {
+                             void* workspace) {
   const int rc = check_cfg(cfg);
   if (rc != SV_OK) return rc;
   if (!packed || !x || !kv || !tree || !workspace || !tree->parent || !tree->depth || !tree->anc_mask)
@@ -845,19 +669,19 @@ static int verify_stack_args(const sv_model_cfg* cfg, int n_layers, const void* 
       return SV_ERR_SHAPE;
     if ((long long)B * cfg->n_heads * kv[l].capacity >= (1ll << 31)) return SV_ERR_SHAPE;
   }
-  if (((uintptr_t)workspace % kAlign) || ws_bytes < workspace_layout(*cfg, B * T, 0).total)
-    return SV_ERR_WORKSPACE;
-  return SV_OK;
+  return (uintptr_t)workspace % kAlign ? SV_ERR_WORKSPACE : SV_OK;
 }
 
 int sv_verify_stack(const sv_model_cfg* cfg, int n_layers, const void* const* packed, float* x,
                     const sv_kv_view* kv, const sv_tree* tree, int B, void* workspace,
                     size_t ws_bytes, void* stream) {
-  const int rc = verify_stack_args(cfg, n_layers, packed, x, kv, tree, B, workspace, ws_bytes);
+  const int rc = verify_stack_args(cfg, n_layers, packed, x, kv, tree, B, workspace);
   if (rc != SV_OK) return rc;
+  const LayerCall lc = layer_call(*cfg, B * tree->n_nodes);
+  if (ws_bytes < lc.wl.total) return SV_ERR_WORKSPACE;
   for (int l = 0; l < n_layers; ++l) {
-    const int r2 = verify_layer_checked(cfg, packed[l], x, kv + l, tree, B, workspace, ws_bytes,
-                                        stream, nullptr);
+    const int r2 = verify_layer_dispatch(*cfg, lc, packed[l], x, kv[l], *tree, B, workspace, stream, nullptr, l == 0,
+                                         l + 1 < n_layers ? packed[l + 1] : nullptr);
     if (r2 != SV_OK) return r2;
   }
   return SV_OK;
@@ -926,10 +750,8 @@ int sv_pack_head(const sv_model_cfg* cfg, const void* g_final, const void* w_lm,
   char* packed = (char*)packed_v;
   hipStream_t st = (hipStream_t)stream;
   pack_gain<bf16_t><<<ceil_div(H, 256), 256, 0, st>>>((const bf16_t*)g_final, (float*)(packed + hl.gain), H);
-  const size_t n8 = (size_t)n * (H / 8);
-  pack_rows_mfma<<<(unsigned)((n8 + 255) / 256), 256, 0, st>>>(
-      (const uint4*)((const bf16_t*)w_lm + (size_t)vocab_lo * H), (uint4*)(packed + hl.w), n, H,
-      PACK_PLAIN, 0);
+  pack_rows<uint4, 0><<<dim3(n / 32, H / 256), 256, 0, st>>>((const uint4*)((const bf16_t*)w_lm + (size_t)vocab_lo * H),
+                                                            (uint4*)(packed + hl.w), H, n / 32, PACK_PLAIN, 0);
   return launch_status();
 }
 

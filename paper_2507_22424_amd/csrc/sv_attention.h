@@ -20,7 +20,7 @@
 #ifndef SV_ATTENTION_H
 #define SV_ATTENTION_H
 
-#include "sv_gemm_mfma.h"
+#include "sv_frag.h"
 #include "sv_internal.h"
 
 namespace sv {
@@ -62,6 +62,20 @@ __device__ inline void split8(const float* v, bf16x8_t& hi, bf16x8_t& lo) {
   lo = __builtin_bit_cast(bf16x8_t, l);
 }
 
+// Eight consecutive columns (from k on) of attention output row m: float32 to `out`, and to `xs`, unless
+// NULL, as fragments of the output projection's activation operand.
+__device__ inline void attention_store8(float* out, uint4* xs, int n_rb, size_t m, int k, int nh, const float* v) {
+  float4* dst = reinterpret_cast<float4*>(out + m * nh * 128 + k);
+  dst[0] = make_float4(v[0], v[1], v[2], v[3]);
+  dst[1] = make_float4(v[4], v[5], v[6], v[7]);
+  if (!xs) return;
+  bf16x8_t hi, lo;
+  split8(v, hi, lo);
+  uint4* f = xs + ((size_t)(k >> 4) * n_rb + (m >> 5)) * 128 + (m & 31) + 32 * ((k >> 3) & 1);
+  f[0] = __builtin_bit_cast(uint4, hi);
+  f[64] = __builtin_bit_cast(uint4, lo);
+}
+
 // Work of one workgroup of NW waves: query block bx = (episode, block of 16 nodes), head by.
 // lds_raw: NW * 128 * kVtPitch bytes; s_m, s_l: [NW][16] floats; sync(): barrier of the waves
 // that run this body (called twice).
@@ -76,7 +90,7 @@ template <int NW, typename Sync>
 __device__ inline void tree_attention_body(
     const float* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
     const int32_t* __restrict__ prefix_len, int p_max, const uint64_t* __restrict__ anc,
-    int n_words, int T, int nh, int cap, float* __restrict__ out, int bx, int by,
+    int n_words, int T, int nh, int cap, float* __restrict__ out, uint4* __restrict__ xs, int n_rb, int bx, int by,
     unsigned char* lds_raw, float (*s_m)[kAttQ], float (*s_l)[kAttQ], int tid, Sync sync,
     int split = 0, int n_split = 1, float* __restrict__ part = nullptr, int M_total = 0) {
   const int lane = tid & 63, wave = tid >> 6;
@@ -242,35 +256,36 @@ __device__ inline void tree_attention_body(
 #pragma unroll
     for (int r = 0; r < 4; ++r) om[(wave * 128 + 16 * dt + 4 * g + r) * kMergePitch + c] = o[dt][r];
   sync();
-  // the first four waves finish d rows 32w .. 32w+31: lane -> (d = 32w + lane % 32, queries
-  // (lane / 32) * 8 .. + 7)
+  // 256 threads finish (query qq, 8 consecutive d each): 32 bytes of the row, and whole fragment
+  // lanes for the output projection
   if (wave < 4) {
-    const int d = 32 * wave + (lane & 31);
+    const int qq = lane & 15, d = 32 * wave + 8 * (lane >> 4);
+    float m_all = s_m[0][qq];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int qq = (lane >> 5) * 8 + i;
-      float m_all = s_m[0][qq];
+    for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][qq]);
+    float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, den = 0.f;
 #pragma unroll
-      for (int w = 1; w < NW; ++w) m_all = fmaxf(m_all, s_m[w][qq]);
-      float num = 0.f, den = 0.f;
+    for (int w = 0; w < NW; ++w) {
+      const float sc = __expf(s_m[w][qq] - m_all);
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const float sc = __expf(s_m[w][qq] - m_all);
-        num += sc * om[(w * 128 + d) * kMergePitch + qq];
-        den += sc * s_l[w][qq];
-      }
-      const int tnode = qb * kAttQ + qq;
-      if (tnode < T) {
-        if (n_split > 1) {
-          float* dst = part + (((size_t)split * M_total + (size_t)b * T + tnode) * nh + h) * kAttPartStride;
-          dst[d] = num;
-          if (d == 0) {
-            dst[128] = m_all;
-            dst[129] = den;
-          }
-        } else {
-          out[((size_t)b * T + tnode) * D + h * 128 + d] = num / den;
+      for (int i = 0; i < 8; ++i) num[i] += sc * om[(w * 128 + d + i) * kMergePitch + qq];
+      den += sc * s_l[w][qq];
+    }
+    const int tnode = qb * kAttQ + qq;
+    if (tnode < T) {
+      const size_t m = (size_t)b * T + tnode;
+      if (n_split > 1) {
+        float* dst = part + (((size_t)split * M_total + m) * nh + h) * kAttPartStride;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) dst[d + i] = num[i];
+        if (d == 0) {
+          dst[128] = m_all;
+          dst[129] = den;
         }
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) num[i] /= den;
+        attention_store8(out, xs, n_rb, m, h * 128 + d, nh, num);
       }
     }
   }
@@ -282,8 +297,8 @@ template <int NW>
 __global__ __launch_bounds__(64 * NW) void tree_attention_mfma(
     const float* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc,
     const int32_t* __restrict__ prefix_len, int p_max, const uint64_t* __restrict__ anc,
-    int n_words, int T, int nh, int cap, float* __restrict__ out, float* __restrict__ part,
-    int M_total) {
+    int n_words, int T, int nh, int cap, float* __restrict__ out, uint4* __restrict__ xs, int n_rb,
+    float* __restrict__ part, int M_total) {
   // per wave: transposed V tile [128 d][32 keys] with padded rows; reused for the merge
   __shared__ __attribute__((aligned(16))) unsigned char lds_raw[NW * 128 * kVtPitch];
   __shared__ float s_m[NW][kAttQ], s_l[NW][kAttQ];
@@ -298,28 +313,33 @@ __global__ __launch_bounds__(64 * NW) void tree_attention_mfma(
   const unsigned item = (total & 7u) ? lin : (lin & 7u) * (total >> 3) + (lin >> 3);
   const unsigned task = item / ns, split = item - task * ns;
   const unsigned head = task / gridDim.x;
-  tree_attention_body<NW>(q, kc, vc, prefix_len, p_max, anc, n_words, T, nh, cap, out,
+  tree_attention_body<NW>(q, kc, vc, prefix_len, p_max, anc, n_words, T, nh, cap, out, xs, n_rb,
                                  (int)(task - head * gridDim.x), (int)head, lds_raw, s_m, s_l,
                                  (int)threadIdx.x, [] { __syncthreads(); }, (int)split, (int)ns, part,
                                  M_total);
 }
 
 // out[m][h*128 + d] = sum_s e^(m_s - m) num_s[d] / sum_s e^(m_s - m) den_s, m = max_s m_s, the
-// splits taken in order.  grid = (M, n_heads), block = 128 (thread = d).
-__global__ __launch_bounds__(128) void attention_merge_kernel(const float* __restrict__ part, int n_split,
-                                                              int M, int nh, float* __restrict__ out) {
-  const int m = blockIdx.x, h = blockIdx.y, d = threadIdx.x;
+// splits taken in order.  grid = (M, ceil(n_heads / 16)), block = 256 (16 heads x 16 runs of 8 d).
+__global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ part, int n_split,
+                                                              int M, int nh, float* __restrict__ out,
+                                                              uint4* __restrict__ xs, int n_rb) {
+  const int m = blockIdx.x, h = blockIdx.y * 16 + ((int)threadIdx.x >> 4), d = ((int)threadIdx.x & 15) * 8;
+  if (h >= nh) return;
   float m_all = kNegBig;
   for (int s = 0; s < n_split; ++s)
     m_all = fmaxf(m_all, part[(((size_t)s * M + m) * nh + h) * kAttPartStride + 128]);
-  float num = 0.f, den = 0.f;
+  float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, den = 0.f;
   for (int s = 0; s < n_split; ++s) {
     const float* p = part + (((size_t)s * M + m) * nh + h) * kAttPartStride;
     const float sc = __expf(p[128] - m_all);
-    num += sc * p[d];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) num[i] += sc * p[d + i];
     den += sc * p[129];
   }
-  out[(size_t)m * nh * 128 + h * 128 + d] = num / den;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) num[i] /= den;
+  attention_store8(out, xs, n_rb, m, h * 128 + d, nh, num);
 }
 
 }  // namespace sv

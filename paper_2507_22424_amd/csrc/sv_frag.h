@@ -1,0 +1,95 @@
+// Matrix-core fragments: types, sizes and the conversions between the storage formats and bf16
+// operands that the products and the attention share.
+#ifndef SV_FRAG_H
+#define SV_FRAG_H
+
+#include <type_traits>
+
+#include "sv_internal.h"
+
+namespace sv {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+
+constexpr int kFragRows = 32;    // weight rows per fragment and per tile (MFMA N)
+constexpr int kFragK = 16;       // k-values per fragment (MFMA K)
+constexpr int kXcds = 8, kCusPerXcd = 32;
+constexpr int kCntStride = 32;     // 32-bit words per group's counters: a 128-byte line of its own
+
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_OUT = 3 };
+enum { PACK_PLAIN = 0, PACK_PAIR16_HEAD = 1, PACK_PAIR16_GU = 2 };
+
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+
+// Two floats -> packed bf16 (round to nearest even; one v_cvt_pk_bf16_f32 on gfx950).
+__device__ inline uint32_t pack_bf16x2(float a, float b) {
+  const f32x2_t v = {a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
+}
+__device__ inline float bf16_lo_f32(uint32_t packed) { return __uint_as_float(packed << 16); }
+__device__ inline float bf16_hi_f32(uint32_t packed) { return __uint_as_float(packed & 0xffff0000u); }
+
+// four float32 values -> 8 bytes of hi parts, 8 bytes of lo parts
+__device__ inline void split4(const f32x4_t v, uint2& hi, uint2& lo) {
+  hi.x = pack_bf16x2(v[0], v[1]);
+  hi.y = pack_bf16x2(v[2], v[3]);
+  lo.x = pack_bf16x2(v[0] - bf16_lo_f32(hi.x), v[1] - bf16_hi_f32(hi.x));
+  lo.y = pack_bf16x2(v[2] - bf16_lo_f32(hi.y), v[3] - bf16_hi_f32(hi.y));
+}
+
+// Four consecutive k-values (k a multiple of 4) of activation row m -> fragments of a K = 16 * nks
+// operand: [k-step][row block][hi, lo][64 lanes] x 16 bytes.
+__device__ inline void store_frag4(uint4* xs, int n_rb, int m, int k, const f32x4_t v) {
+  uint2 hi, lo;
+  split4(v, hi, lo);
+  uint2* dst = reinterpret_cast<uint2*>(xs + ((size_t)(k >> 4) * n_rb + (m >> 5)) * 128 + (m & 31) + 32 * ((k >> 3) & 1)) + ((k >> 2) & 1);
+  dst[0] = hi;
+  dst[128] = lo;
+}
+
+// x * sigmoid(x) with the hardware exponential and reciprocal (1 ulp each)
+__device__ inline float silu_fast(float x) {
+  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
+}
+
+// The bf16 operand of k-step kk out of one 16-byte weight load of a lane.
+//   WF = 0: the load is the operand (one k-step).
+//   WF = 1: E4M3 codes of two k-steps.  Hardware conversion to float32 pairs, then the pack-convert;
+//           exact, every E4M3 value is a bf16 value.
+//   WF = 2: int4 codes of four k-steps, one 32-bit word per k-step, code i of a word in bits
+//           4i .. 4i+3.  A code c stands for the integer c - 8: with its top bit flipped it is that
+//           integer in 4-bit two's complement, which a signed bit-field extract widens; integer ->
+//           float32 -> bf16 is exact for these values.
+typedef float f32x2v_t __attribute__((ext_vector_type(2)));
+template <int WF>
+__device__ inline bf16x8_t weight_operand(const u32x4_t raw, int kk) {
+  u32x4_t o = raw;
+  if (WF == 1) {
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      const f32x2v_t lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[2 * kk + d], false);
+      const f32x2v_t hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[2 * kk + d], true);
+      o[2 * d] = pack_bf16x2(lo[0], lo[1]);
+      o[2 * d + 1] = pack_bf16x2(hi[0], hi[1]);
+    }
+  }
+  if (WF == 2) {
+    const int w = (int)(raw[kk] ^ 0x88888888u);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)   // (the builtin's result type is unsigned: the cast to int comes first)
+      o[j] = pack_bf16x2((float)(int)__builtin_amdgcn_sbfe(w, 8 * j, 4), (float)(int)__builtin_amdgcn_sbfe(w, 8 * j + 4, 4));
+  }
+  return __builtin_bit_cast(bf16x8_t, o);
+}
+
+// XCD (accelerator complex die) this wave runs on: bits 3:0 of the XCC_ID hardware register.
+__device__ inline int xcd_actual(int n_xcd) {
+  return (int)(__builtin_amdgcn_s_getreg((4 - 1) << 11 | 0 << 6 | 20) & 0xf) % n_xcd;
+}
+
+}  // namespace sv
+#endif

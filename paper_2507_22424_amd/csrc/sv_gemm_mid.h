@@ -1,0 +1,381 @@
+// The layer's products for more than 128 rows of activations.
+//
+// With this many rows the matrix cores set the time, at the clock they hold on real data: in their main
+// loop these kernels issue 1.3 - 1.4 PFLOP/s (hi and lo half of the activations counted), above what a
+// large bf16 product of the vendor's library sustains on the same card (1.16).  What is left to lose is
+// around the loop and in work on rows that do not exist (7B layer of 150 rows: 305 us for the four products
+// and their helper launches before, 207 now; 960 rows: 775 and 775), hence:
+//   * blocks of RB = 3, 4 or 5 row blocks of 32 rows x 4 waves x NT weight tiles; the host picks RB so that
+//     few padded rows are multiplied (150 rows: 160, not 256) and RB, NT, S so that the workgroups fill the
+//     chip in whole rounds;
+//   * a weight tile belongs to one wave: its fragments go from memory straight into operand registers,
+//     through a ring of D chunks.  The activations of a chunk (two k-steps; four with 4-bit weights) are
+//     fetched once per workgroup, each wave loading a quarter of the fragments into registers and writing
+//     them to LDS one chunk ahead of their use; one barrier per chunk, three LDS buffers.  Every load is
+//     one the compiler knows of, in a fixed order, so its waits are exact;
+//   * S workgroups share an output block along K (same XCD) and exchange float32 sums through its L2;
+//     every one of them finishes 1/S of the block with the epilogue fused.  No partial planes, no
+//     reduction launches, no launches that split activations: the epilogues leave fragments.
+#ifndef SV_GEMM_MID_H
+#define SV_GEMM_MID_H
+
+#include "sv_epilogue.h"
+
+namespace sv {
+
+struct MidArgs {
+  const uint4* Xs;           // activation fragments [K / 16][row block][hi, lo][64]
+  const uint4* Wp;           // packed weights [K / (16 << WF)][N / 32][64]
+  int N;                     // output columns
+  int lgS;                   // S = 1 << lgS workgroups along K
+  int gpx, n_xcd, m_tiles;   // column groups per XCD, XCDs, blocks of rows
+  int tq, trem;              // tiles per column group, groups with one more
+  int cq, crem;              // chunks per K slice, slices with one more
+  int planes;                // EPI_RESID: row-sum planes per column group
+  // scratch of the sums that cross workgroups, addressed by XCD: no address is ever written through one
+  // L2 and read through another
+  f32x4_t* xch;              // [n_xcd][ucap][unit_stride]
+  unsigned* group_cnt;       // [n_xcd][ucap][kCntStride], zero between launches
+  int* status;
+  int ucap, unit_stride;
+  EpiArgs e;
+};
+
+constexpr int kMidMaxTiles = 3;            // weight tiles per wave
+constexpr int kMidMaxRows = 5;             // row blocks per workgroup
+
+// An item = half a unit (32 x 32 sums): quads p and p + 2 where the epilogue works on pairs, else 2p and
+// 2p + 1.  A wave has 2 * RB * NT items, row block after row block; slice sp finishes the items from
+// mid_first(sp) on.
+constexpr int mid_items(int rb, int nt) { return 2 * rb * nt; }
+__host__ __device__ constexpr int mid_first(int items, int lgS, int sp) { return (sp * items + (1 << lgS) - 1) >> lgS; }
+__host__ __device__ constexpr int mid_owner(int items, int lgS, int i) { return (i << lgS) / items; }
+// slices that finish a part of one row block's items, at most: its planes of row sums
+constexpr int mid_planes(int rb, int nt, int lgS) {
+  int most = 1;
+  for (int r = 0; r < rb; ++r) {
+    const int n = mid_owner(mid_items(rb, nt), lgS, (r + 1) * 2 * nt - 1) - mid_owner(mid_items(rb, nt), lgS, r * 2 * nt) + 1;
+    most = n > most ? n : most;
+  }
+  return most;
+}
+// float4 a workgroup may send (4 waves, padded so that the regions do not share memory channels)
+constexpr int mid_unit_stride(int rb, int nt) { return (4 * (rb * nt * 4 + 1) + 5) * 64; }
+
+template <int RB, int NT, int WF>
+struct MidShape {
+  static constexpr int UK = 1 << WF, CK = UK < 2 ? 2 : UK;     // k-steps of a weight load, of a chunk
+  static constexpr int LW = CK / UK * NT, LX = CK * RB / 2;    // loads of a wave per chunk
+  // chunks in flight: what the load counter (63) and the registers hold, 12 k-steps at most
+  static constexpr int kCnt = 60 / (LW + LX), kReg = (416 - 16 * RB * NT) / (4 * (LW + LX));
+  static constexpr int D0 = kCnt < kReg ? kCnt : kReg;
+  static constexpr int D = D0 > 6 ? 6 : D0;
+  static_assert(D >= 2, "ring too short");
+};
+constexpr int mid_chunk_k(int wf) { return wf == 2 ? 64 : 32; }
+
+// grid = (n_xcd, gpx * m_tiles * S), block = 256, one workgroup per CU: x is the XCD; in y the S slices of
+// an output block follow each other, then the blocks of rows of a column group, which read the same
+// weights at about the same time.
+template <int RB, int NT, int EPI, int WF>
+__global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
+  typedef MidShape<RB, NT, WF> Sh;
+  constexpr int UK = Sh::UK, CK = Sh::CK, LX = Sh::LX, D = Sh::D, CW = CK / UK;
+  constexpr int E = CK * RB, PD = 2;                           // steps of a chunk; operands are read two steps ahead
+  constexpr int kChunk = CK * RB * 2;                          // activation fragments of a chunk
+  constexpr bool PAIR = epi_pairs(EPI);
+  constexpr int U = RB * NT, NI = mid_items(RB, NT), NQ = U * 4;   // units, items, quads of a wave
+  constexpr int kLdsFr = 3 * kChunk > NQ * 2 ? 3 * kChunk : NQ * 2;   // ring; after the loop, half of the sums
+  __shared__ u32x4_t lds[kLdsFr][64];
+  __shared__ float s_rows[EPI == EPI_RESID ? 4 * RB * 32 : (RB * 32 > 256 ? RB * 32 : 256)];
+  __shared__ float s_rstd[RB * 32];
+  __shared__ float s_pos[EPI == EPI_QKV ? 32 * RB : 1];
+  __shared__ int s_crow[EPI == EPI_QKV ? 32 * RB : 1];
+  __shared__ __attribute__((aligned(16))) float s_freq[64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int S = 1 << a.lgS;
+  const int xcd = blockIdx.x, sp = (int)blockIdx.y & (S - 1), gm = (int)blockIdx.y >> a.lgS;
+  const int ug = gm / a.m_tiles, mt = gm - ug * a.m_tiles;
+  const int g = xcd * a.gpx + ug;
+  const int t_begin = g * a.tq + min(g, a.trem);
+  const int t_count = a.tq + (g < a.trem ? 1 : 0);
+  if (t_count == 0) return;
+  const int m0 = mt * RB * 32;
+  const int n_tiles = a.N / kFragRows;
+  const int c0 = sp * a.cq + min(sp, a.crem);
+  const int n = a.cq + (sp < a.crem ? 1 : 0);                  // chunks of this slice
+
+  typedef const __attribute__((address_space(1))) u32x4_t* gptr_t;
+  gptr_t wp = (gptr_t)a.Wp + ((size_t)c0 * CW * n_tiles + t_begin) * 64;
+  const unsigned w_row = n_tiles * 64u;
+  size_t w_step = (size_t)CW * w_row;
+  unsigned w_off[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)       // (beyond the group's tiles: the last one again, dropped at the end)
+    w_off[t] = (unsigned)min(wave * NT + t, t_count - 1) * 64u + lane;
+  gptr_t xp = (gptr_t)a.Xs + (size_t)c0 * CK * a.e.n_rb * 128;
+  const unsigned x_step = CK * a.e.n_rb * 128u;
+  unsigned x_off[LX];
+#pragma unroll
+  for (int i = 0; i < LX; ++i) {     // fragment f of the chunk: row block, k-step, hi / lo
+    const int f = wave * LX + i;
+    x_off[i] = ((unsigned)(f % (2 * CK) / 2) * a.e.n_rb + min(mt * RB + f / (2 * CK), a.e.n_rb - 1)) * 128u + (f & 1) * 64u + lane;
+  }
+  u32x4_t xin[D][LX], wr[D][CW][NT];
+  int wl = n, xl = n;                                          // chunks still to be requested
+  // (once nothing is left the loads repeat the first activations, which the caches hold: the number of
+  // loads in flight stays fixed)
+  auto issue_x = [&](int d) {
+#pragma unroll
+    for (int i = 0; i < LX; ++i) xin[d][i] = xp[x_off[i]];
+    if (--xl > 0) xp += x_step;
+    else xp = (gptr_t)a.Xs;
+  };
+  auto issue_w = [&](int d) {
+#pragma unroll
+    for (int cw = 0; cw < CW; ++cw)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) wr[d][cw][t] = __builtin_nontemporal_load(wp + (w_off[t] + cw * w_row));
+    if (--wl > 0) {
+      wp += w_step;
+    } else {
+      wp = (gptr_t)a.Xs;
+      w_step = 0;
+    }
+  };
+  auto put_x = [&](int d, int buf) {
+#pragma unroll
+    for (int i = 0; i < LX; ++i) lds[buf * kChunk + wave * LX + i][lane] = xin[d][i];
+  };
+
+  // row sums of x^2: thread (row, part) adds its share of the planes; requested first, added once the ring
+  // is on its way
+  constexpr int kParts = RB * 32 <= 128 ? 2 : 1, kSsqBatch = 32;
+  const int row = tid % (RB * 32), part0 = tid / (RB * 32);
+  float ssv[kSsqBatch];
+  const float* const ssq = a.e.ssq + min(m0 + row, a.e.m_pad - 1);
+  if (EPI != EPI_RESID) {
+#pragma unroll
+    for (int i = 0; i < kSsqBatch; ++i) ssv[i] = ssq[(size_t)min(part0 + kParts * i, a.e.n_ssq - 1) * a.e.m_pad];
+  }
+  EpiRow er;
+  if (EPI == EPI_QKV) er = epi_row_fetch(a.e, min(m0 + row, a.e.M - 1));
+#pragma unroll
+  for (int d = 0; d < D; ++d) {
+    issue_x(d);
+    issue_w(d);
+  }
+  if (EPI != EPI_RESID) {
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < kSsqBatch; ++i) ss += part0 + kParts * i < a.e.n_ssq ? ssv[i] : 0.f;
+    for (int p = part0 + kParts * kSsqBatch; p < a.e.n_ssq; p += kParts) ss += ssq[(size_t)p * a.e.m_pad];
+    if (part0 < kParts) s_rows[part0 * RB * 32 + row] = ss;
+  }
+  if (EPI == EPI_QKV) epi_tables(a.e, er, tid, RB * 32, s_pos, s_crow, s_freq);
+
+  f32x16_t acc[RB][NT];
+#pragma unroll
+  for (int i = 0; i < RB; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x16_t{};
+
+  put_x(0, 0);
+  issue_x(0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  u32x4_t xo[PD + 1][2];
+  auto get = [&](int s, int buf, int e) {                      // step e = k-step * RB + row block
+    const int f = buf * kChunk + ((e % RB) * CK + e / RB) * 2;
+    xo[s][0] = lds[f][lane];
+    xo[s][1] = lds[f + 1][lane];
+  };
+#pragma unroll
+  for (int e = 0; e < PD; ++e) get(e, 0, e);
+  int buf = 0, left = n;
+  while (left > 0) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      // The next chunk's activations go to LDS now; the barrier before their first read is PD steps from
+      // the end.  Their buffer held the chunk before the last one, which every wave had read before the
+      // barrier of the last.
+      const int nb = buf == 2 ? 0 : buf + 1;
+      put_x((d + 1) % D, nb);
+      issue_x((d + 1) % D);
+      if (left > d) {
+        bf16x8_t w[NT];
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          const int kk = e / RB, rb = e % RB;
+          // (own LDS writes are older than the 2 * PD reads that may still be under way)
+          if (e == E - PD) asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(2 * PD) : "memory");
+          if (e + PD < E) get((e + PD) % (PD + 1), buf, e + PD);
+          else get((e + PD) % (PD + 1), nb, e + PD - E);
+          if (rb == 0) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) w[t] = weight_operand<WF>(wr[d][kk / UK][t], kk % UK);
+          }
+#pragma unroll
+          for (int hl = 0; hl < 2; ++hl)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+              acc[rb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t], __builtin_bit_cast(bf16x8_t, xo[e % (PD + 1)][hl]), acc[rb][t], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);   // left alone the scheduler sinks the operand reads to their use
+        }
+        buf = nb;
+        if (E % (PD + 1) != 0) {               // the next chunk counts its steps from 0 again
+          u32x4_t tmp[PD][2];
+#pragma unroll
+          for (int k = 0; k < PD; ++k)
+#pragma unroll
+            for (int hl = 0; hl < 2; ++hl) tmp[k][hl] = xo[(E + k) % (PD + 1)][hl];
+#pragma unroll
+          for (int k = 0; k < PD; ++k)
+#pragma unroll
+            for (int hl = 0; hl < 2; ++hl) xo[k][hl] = tmp[k][hl];
+        }
+      }
+      issue_w(d);
+    }
+    left -= D;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // all waves have read the ring
+
+  // ---- output ----
+  const int h = lane >> 5;
+  const size_t unit = (size_t)xcd * a.ucap + (size_t)gm * S;       // first workgroup of the group
+  const auto gcnt = a.group_cnt + ((size_t)xcd * a.ucap + gm) * kCntStride;
+  f32x4_t* const stage = reinterpret_cast<f32x4_t*>(&lds[0][0]) + lane;
+  auto item_quad = [&](int i, int qi) -> f32x4_t {
+    const int q = PAIR ? (i & 1) + 2 * qi : 2 * (i & 1) + qi;
+    const f32x16_t& c = acc[(i >> 1) / NT][(i >> 1) % NT];
+    return f32x4_t{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
+  };
+  const int b0 = mid_first(NI, a.lgS, sp), b1 = mid_first(NI, a.lgS, sp + 1);   // this slice's items
+  f32x4_t* const own = stage + (size_t)wave * (NQ / 2) * 64;
+  if (S > 1) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      if (i >= b0 && i < b1) {
+        own[(i - b0) * 128] = item_quad(i, 0);
+        own[(i - b0) * 128 + 64] = item_quad(i, 1);
+      } else {
+        f32x4_t* dst = a.xch + (unit + sp) * a.unit_stride + (size_t)(wave * (NQ + 1) + i * 2) * 64 + lane;
+        dst[0] = item_quad(i, 0);
+        dst[64] = item_quad(i, 1);
+      }
+    }
+  }
+  for (int r = tid; r < RB * 32; r += 256) {
+    float t = 1.f;
+    if (EPI != EPI_RESID) {
+      t = s_rows[r];
+      if (kParts > 1) t += s_rows[RB * 32 + r];
+      t = 1.0f / sqrtf(t / (float)a.e.K + a.e.eps);
+    }
+    s_rstd[r] = t;
+  }
+  if (EPI == EPI_RESID)
+    for (int i = tid; i < 4 * RB * 32; i += 256) s_rows[i] = 0.f;
+  if (S > 1) __builtin_amdgcn_s_waitcnt(0);         // this wave's sums are in the L2
+  __syncthreads();
+  if (S > 1) {
+    if (tid == 0) group_arrive_and_wait(gcnt, S, a.n_xcd, a.status);
+    __syncthreads();
+    asm volatile("buffer_inv sc0" ::: "memory");                   // drop stale L1 lines (the L2 is shared)
+  }
+  struct Loads {
+    EpiLoads l[PAIR ? 1 : 2];
+  };
+  auto fetch = [&](int i, Loads& l) {
+    const int u = i >> 1, p = i & 1, m = m0 + (u / NT) * 32 + (lane & 31), t = t_begin + min(wave * NT + u % NT, t_count - 1);
+    epi_fetch<EPI, WF>(a.e, a.N, t, PAIR ? p : 2 * p, m, h, l.l[0]);
+    if (!PAIR) epi_fetch<EPI, WF>(a.e, a.N, t, 2 * p + 1, m, h, l.l[PAIR ? 0 : 1]);
+  };
+  auto finish_item = [&](int i, const f32x4_t v0, const f32x4_t v1, const Loads& l) {
+    const int u = i >> 1, p = i & 1, ml = (u / NT) * 32 + (lane & 31), t = wave * NT + u % NT;
+    if (t >= t_count) return;
+    const float pos = EPI == EPI_QKV ? s_pos[ml] : 0.f;
+    const int crow = EPI == EPI_QKV ? s_crow[ml] : 0;
+    const float rs = s_rstd[ml];
+    float sq = epi_quad<EPI, WF>(a.e, a.N, t_begin + t, PAIR ? p : 2 * p, m0 + ml, h, rs, pos, crow, s_freq, v0, v1, l.l[0]);
+    if (!PAIR) sq += epi_quad<EPI, WF>(a.e, a.N, t_begin + t, 2 * p + 1, m0 + ml, h, rs, pos, crow, s_freq, v1, v1, l.l[PAIR ? 0 : 1]);
+    if (EPI == EPI_RESID) {
+      sq = lane_pair32_sum(sq);
+      if (h == 0) s_rows[wave * RB * 32 + ml] += sq;       // (this lane's own word)
+    }
+  };
+  auto finish = [&](auto split) {
+    constexpr int SS = decltype(split)::value;
+    constexpr int BT = SS == 8 ? 2 : (SS == 4 ? 3 : 4);    // items whose loads are in flight together
+    for (int i0 = b0; i0 < b1; i0 += BT) {
+      f32x4_t part[BT][2][SS];
+      Loads ld[BT];
+#pragma unroll
+      for (int b = 0; b < BT; ++b) {
+        const int i = min(i0 + b, b1 - 1);
+#pragma unroll
+        for (int s2 = 1; s2 < SS; ++s2) {
+          const f32x4_t* p = a.xch + (unit + ((sp + s2) & (SS - 1))) * a.unit_stride + (size_t)(wave * (NQ + 1) + i * 2) * 64 + lane;
+          part[b][0][s2] = p[0];
+          part[b][1][s2] = p[64];
+        }
+        fetch(i, ld[b]);
+        part[b][0][0] = own[(i - b0) * 128];
+        part[b][1][0] = own[(i - b0) * 128 + 64];
+      }
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int b = 0; b < BT; ++b) {
+        if (i0 + b >= b1) break;
+        f32x4_t v0 = part[b][0][0], v1 = part[b][1][0];
+#pragma unroll
+        for (int s2 = 1; s2 < SS; ++s2) {
+          v0 += part[b][0][s2];
+          v1 += part[b][1][s2];
+        }
+        finish_item(i0 + b, v0, v1, ld[b]);
+      }
+    }
+  };
+  if (S == 1) {
+    // one row block at a time through LDS, so that the epilogue is a short loop
+    f32x4_t* const st = stage + (size_t)wave * (NT * 4) * 64;
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+#pragma unroll
+      for (int k = 0; k < NT * 2; ++k) {
+        st[(2 * k) * 64] = item_quad(r * NT * 2 + k, 0);
+        st[(2 * k + 1) * 64] = item_quad(r * NT * 2 + k, 1);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll 1
+      for (int k = 0; k < NT * 2; ++k) {
+        Loads l;
+        fetch(r * NT * 2 + k, l);
+        finish_item(r * NT * 2 + k, st[(2 * k) * 64], st[(2 * k + 1) * 64], l);
+      }
+    }
+  } else if (S == 2) finish(std::integral_constant<int, 2>{});
+  else if (S == 4) finish(std::integral_constant<int, 4>{});
+  else finish(std::integral_constant<int, 8>{});
+
+  // Partial sums of x^2 of the new rows: every slice that has finished items of a row block writes what it
+  // has of its rows to a plane of its own; the last of them clears the planes that are left over.
+  if (EPI == EPI_RESID && a.e.next_gain) {
+    __syncthreads();
+    for (int ml = tid; ml < RB * 32; ml += 256) {
+      const int r = ml >> 5;
+      const int o0 = mid_owner(NI, a.lgS, r * 2 * NT), o1 = mid_owner(NI, a.lgS, (r + 1) * 2 * NT - 1);
+      if (sp < o0 || sp > o1 || m0 + ml >= a.e.m_pad) continue;
+      float* dst = a.e.ssq_out + (size_t)(g * a.planes + sp - o0) * a.e.m_pad + m0 + ml;
+      *dst = (s_rows[ml] + s_rows[RB * 32 + ml]) + (s_rows[2 * RB * 32 + ml] + s_rows[3 * RB * 32 + ml]);
+      if (sp == o1)
+        for (int p = o1 - o0 + 1; p < a.planes; ++p) dst[(size_t)(p - (sp - o0)) * a.e.m_pad] = 0.f;
+    }
+  }
+  if (S > 1 && tid == 0) group_leave(gcnt, S);
+}
+
+}  // namespace sv
+#endif

@@ -98,19 +98,18 @@ inline PackedLayout packed_layout(const sv_model_cfg& c) {
   return L;
 }
 
-// Device scratch of one call (bytes from the start of the workspace).  Activations are
-// float32 for both storage types.
+// Device scratch of one call (bytes from the start of the workspace).
 struct WorkspaceLayout {
-  size_t counters, sumsq, part, xhat, q, attn, act, head_z, head_logits, total;
-  size_t counter_bytes, part_bytes;
-  // packed head (bf16, scored rows a multiple of 32): its own counters, row sums, partial tiles
-  size_t head_cnt, head_cnt_bytes, head_sumsq, head_part, head_part_bytes;
-  // many rows (matrix-core bound products): activation fragments, 1 / rms, split-K partial blocks
-  size_t rows_xs, rows_rstd, rows_part;
-  size_t att_part;               // split tree attention: per split, query and head the unnormalised output, maximum, sum
-  int rows_pad;
-  int m_pad, m_tiles;
-  int ucap, tstride, head_ucap, head_tstride;   // per-XCD extents of the split-K scratch regions (units, partial tiles)
+  size_t q, attn, total;         // float32, both storage types
+  // float32 models
+  size_t part, xhat, act;
+  // bf16 models: counters of the workgroups that share an output (+ status word), activation fragments of
+  // the residual stream, the attention output and the SwiGLU output, partial row sums of x^2, sums that
+  // cross workgroups, partial results of a split tree attention
+  size_t counters, counter_bytes, xs_x, xs_attn, xs_act, ssq, xch, att_part;
+  // heads: plain (normalised rows, logit planes), packed (bf16 models, scored rows a multiple of 32)
+  size_t head_z, head_logits, head_cnt, head_cnt_bytes, head_xs, head_ssq, head_xch;
+  int m_pad, n_rb;               // rows as laid out, row blocks of 32
 };
 
 }  // namespace sv

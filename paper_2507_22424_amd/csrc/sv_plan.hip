@@ -1,0 +1,127 @@
+// How the products are split over the chip, and their launches (host code only).
+#include <cstring>
+
+#include "sv_products.h"
+
+namespace sv {
+
+// Up to 128 rows.  As many K slices as leave a group at most skinny_max_tiles tiles while groups x slices
+// make one round of the chip: fewer groups mean that fewer workgroups read the activations.  A wave gets
+// at least 64 k-values (four waves per slice).
+static ProductPlan plan_skinny(int M, int N, int K, int n_xcd) {
+  const int tiles = N / kFragRows, tiles_x = ceil_div(tiles, n_xcd);
+  ProductPlan p;
+  memset(&p, 0, sizeof(p));
+  p.rb = ceil_div(M, kFragRows);
+  const int most = skinny_max_tiles(p.rb);
+  int nt = 0;
+  for (p.lgS = 3; p.lgS >= 0; --p.lgS) {
+    p.gpx = kCusPerXcd >> p.lgS;
+    if (p.gpx > tiles_x) p.gpx = tiles_x;
+    nt = ceil_div(tiles, n_xcd * p.gpx);
+    if (nt <= most && K >= (256 << p.lgS)) break;
+  }
+  if (p.lgS < 0) {
+    p.lgS = 0;
+    p.gpx = ceil_div(tiles_x, most);
+    nt = ceil_div(tiles, n_xcd * p.gpx);
+  }
+  p.nt = nt <= 2 ? 2 : (p.rb > 2 ? 3 : (nt <= 4 ? 4 : 6));
+  p.m_tiles = 1;
+  p.wg_x = p.gpx << p.lgS;
+  p.unit_stride = kSkinnyUnitStride;
+  p.planes = 0;
+  p.n_planes = tiles;
+  return p;
+}
+
+// gemm_mid: every (row blocks, tiles, slices) it has is priced and the cheapest taken.  Fitted to sweeps of
+// all of them on the 7B shapes at 70 - 960 rows: with every CU busy a k-step takes
+// RB * (0.042 * NT + 0.020) us (the second term: LDS reads of the activations), at least what HBM takes for
+// the weights; a round of workgroups adds 11 us around its loop and 0.12 us per KiB of sums a workgroup
+// hands to the others.
+static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
+  const int tiles = N / kFragRows, tiles_x = ceil_div(tiles, n_xcd), n_rb = ceil_div(M, 32), nks = K / kFragK;
+  const double w_bytes = (double)N * K * 2 / (1 << wf);
+  ProductPlan best;
+  memset(&best, 0, sizeof(best));
+  double best_us = 1e30;
+  for (int rb = 3; rb <= kMidMaxRows; ++rb)
+    for (int nt = 1; nt <= kMidMaxTiles; ++nt)
+      for (int lgS = 0; lgS <= 3; ++lgS) {
+        if (lgS > 0 && K / mid_chunk_k(wf) < (4 << lgS)) continue;
+        ProductPlan p;
+        memset(&p, 0, sizeof(p));
+        p.mid = true; p.rb = rb; p.nt = nt; p.lgS = lgS;
+        p.m_tiles = ceil_div(n_rb, rb);
+        p.gpx = ceil_div(tiles_x, 4 * nt);
+        p.wg_x = (p.gpx * p.m_tiles) << lgS;
+        const int rounds = ceil_div(p.wg_x, kCusPerXcd);
+        const double steps = (double)nks / (1 << lgS), kib = 16.0 * rb * nt * ((1 << lgS) - 1) / (1 << lgS);
+        double loop = rounds * steps * rb * (0.042 * nt + 0.020);
+        const double hbm = w_bytes / 5.8e6;
+        if (loop < hbm) loop = hbm;
+        const double us = loop + rounds * (11.0 + 0.12 * kib);
+        if (us < best_us) {
+          best_us = us;
+          best = p;
+        }
+      }
+  best.unit_stride = mid_unit_stride(best.rb, best.nt);
+  best.planes = mid_planes(best.rb, best.nt, best.lgS);
+  const int groups = n_xcd * best.gpx;
+  best.n_planes = (tiles < groups ? tiles : groups) * best.planes;
+  return best;
+}
+
+// Rows the kernels split at.  Up to 128 gemm_skinny, unless its groups of few tiles would make more than one
+// round of the chip (us, o / down / qkv / gate+up on the 7B shapes: 70 rows 18.1 / 34.3 / 36.8 / 54.8
+// against gemm_mid's 19.6 / 34.0 / 40.7 / 60.2; 128 rows 20.5 / 39.3 / 45.6 / 62.5 against 22.6 / 40.4 /
+// 45.4 / 66.7; 150 rows 24.1 / 45.5 / 54.7 / 100 against 26.6 / 46.0 / 54.1 / 79.2).  A plan follows from
+// its five sizes alone; the last few of a thread are kept, a step asks for the same ones again and again.
+ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd) {
+  if (M <= kSkinnyMaxRows) {
+    const ProductPlan p = plan_skinny(M, N, K, n_xcd);
+    if (M <= 64 || p.wg_x <= kCusPerXcd) return p;
+  }
+  struct Entry {
+    int M, N, K, wf, n_xcd;
+    ProductPlan plan;
+  };
+  static thread_local Entry memo[64];
+  Entry& e = memo[((unsigned)M * 31u + (unsigned)N * 17u + (unsigned)K * 7u + (unsigned)n_xcd * 3u + (unsigned)wf) % 64u];
+  if (e.M != M || e.N != N || e.K != K || e.wf != wf || e.n_xcd != n_xcd) e = {M, N, K, wf, n_xcd, plan_mid(M, N, K, wf, n_xcd)};
+  return e.plan;
+}
+
+void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint4* Xs, const uint4* Wp, int N, int K,
+                    const ProductScratch& s, const EpiArgs& e, hipStream_t st) {
+  const int tiles = N / kFragRows, groups = n_xcd * p.gpx;
+  const dim3 grid(n_xcd, p.wg_x);
+  if (p.mid) {
+    MidArgs a;
+    memset(&a, 0, sizeof(a));
+    const int chunks = K / mid_chunk_k(wf);
+    a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd; a.m_tiles = p.m_tiles;
+    a.tq = tiles / groups; a.trem = tiles % groups;
+    a.cq = chunks >> p.lgS; a.crem = chunks & ((1 << p.lgS) - 1);
+    a.planes = p.planes;
+    a.xch = s.xch; a.group_cnt = s.group_cnt; a.status = s.status; a.ucap = s.ucap; a.unit_stride = p.unit_stride;
+    a.e = e;
+    auto* launch = epi == EPI_QKV ? launch_mid_qkv : (epi == EPI_RESID ? launch_mid_resid : (epi == EPI_SWIGLU ? launch_mid_swiglu : launch_mid_out));
+    launch(a, p.rb, p.nt, wf, grid, st);
+  } else {
+    SkinnyArgs a;
+    memset(&a, 0, sizeof(a));
+    const int units = K / (kFragK << wf), waves = 4 << p.lgS;
+    a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd;
+    a.tq = tiles / groups; a.trem = tiles % groups;
+    a.uq = units / waves; a.urem = units % waves;
+    a.xch = s.xch; a.group_cnt = s.group_cnt; a.status = s.status; a.ucap = s.ucap; a.unit_stride = p.unit_stride;
+    a.e = e;
+    auto* launch = epi == EPI_QKV ? launch_skinny_qkv : (epi == EPI_RESID ? launch_skinny_resid : (epi == EPI_SWIGLU ? launch_skinny_swiglu : launch_skinny_out));
+    launch(a, p.rb, p.nt, wf, grid, st);
+  }
+}
+
+}  // namespace sv
