@@ -531,8 +531,8 @@ static int pack_layer_codes(const sv_model_cfg* cfg, const sv_layer_weights* raw
       pack_rows<uint32_t, 2><<<grid, 256, 0, st>>>((const uint32_t*)p.src, (uint32_t*)(packed + p.dst), p.k, p.tiles, p.mode, p.off);
     else
       pack_rows<uint2, 1><<<grid, 256, 0, st>>>((const uint2*)p.src, (uint2*)(packed + p.dst), p.k, p.tiles, p.mode, p.off);
-    pack_row_scales<<<ceil_div(p.rows, 256), 256, 0, st>>>(p.scale, (float*)(packed + p.sdst), p.rows,
-                                                           p.mode, p.off);
+    pack_row_scales<<<ceil_div(p.rows, 256), 256, 0, st>>>(p.scale, (float*)(packed + p.sdst), p.rows, p.mode, p.off,
+                                                           dtype == SV_BF16_W4 ? kInt4Unit : 1.0f);
   }
   return launch_status();
 }

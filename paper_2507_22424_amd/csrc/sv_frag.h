@@ -58,30 +58,30 @@ __device__ inline float silu_fast(float x) {
 
 // The bf16 operand of k-step kk out of one 16-byte weight load of a lane.
 //   WF = 0: the load is the operand (one k-step).
-//   WF = 1: E4M3 codes of two k-steps.  Hardware conversion to float32 pairs, then the pack-convert;
-//           exact, every E4M3 value is a bf16 value.
-//   WF = 2: int4 codes of four k-steps, one 32-bit word per k-step, code i of a word in bits
-//           4i .. 4i+3.  A code c stands for the integer c - 8: with its top bit flipped it is that
-//           integer in 4-bit two's complement, which a signed bit-field extract widens; integer ->
-//           float32 -> bf16 is exact for these values.
-typedef float f32x2v_t __attribute__((ext_vector_type(2)));
+//   WF = 1: E4M3 codes of two k-steps, one hardware conversion per pair (gfx950; scale 1).  Exact, every E4M3
+//           value is a bf16 value.
+//   WF = 2: integers -8 .. 7 of four k-steps in 4-bit two's complement, one 32-bit word per k-step, value i of a
+//           word in bits 4i .. 4i+3.  v_cvt_off_f32_i4 takes the low four bits of a byte and gives a
+//           sixteenth of the integer; the sixteen is in the packed row scales.  Exact.  (Bit-field
+//           extract, integer conversion and a flip of the top bits, as before, are 21 instead of 13
+//           instructions for eight weights, next to four matrix instructions at up to 64 rows.)
+constexpr float kInt4Unit = 16.0f;
 template <int WF>
 __device__ inline bf16x8_t weight_operand(const u32x4_t raw, int kk) {
   u32x4_t o = raw;
   if (WF == 1) {
 #pragma unroll
-    for (int d = 0; d < 2; ++d) {
-      const f32x2v_t lo = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[2 * kk + d], false);
-      const f32x2v_t hi = __builtin_amdgcn_cvt_pk_f32_fp8((int)raw[2 * kk + d], true);
-      o[2 * d] = pack_bf16x2(lo[0], lo[1]);
-      o[2 * d + 1] = pack_bf16x2(hi[0], hi[1]);
-    }
+    for (int j = 0; j < 4; ++j)   // (the half of the word is an immediate)
+      o[j] = __builtin_bit_cast(uint32_t, j & 1 ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[2 * kk + j / 2], 1.0f, true)
+                                                : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[2 * kk + j / 2], 1.0f, false));
   }
   if (WF == 2) {
-    const int w = (int)(raw[kk] ^ 0x88888888u);
+    const unsigned even = raw[kk];
+    unsigned odd = even >> 4;
+    asm("" : "+v"(odd));          // (else each odd nibble is extracted on its own)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)   // (the builtin's result type is unsigned: the cast to int comes first)
-      o[j] = pack_bf16x2((float)(int)__builtin_amdgcn_sbfe(w, 8 * j, 4), (float)(int)__builtin_amdgcn_sbfe(w, 8 * j + 4, 4));
+    for (int j = 0; j < 4; ++j)
+      o[j] = pack_bf16x2(__builtin_amdgcn_cvt_off_f32_i4((int)(even >> (8 * j)) & 0xff), __builtin_amdgcn_cvt_off_f32_i4((int)(odd >> (8 * j)) & 0xff));
   }
   return __builtin_bit_cast(bf16x8_t, o);
 }

@@ -47,14 +47,17 @@ __global__ __launch_bounds__(256) void pack_rows(const V* __restrict__ src, V* _
     const int n = packed_row(r0 + r, mode, off);
     const size_t load = (size_t)(kc >> (1 + WF)) * n_tiles + n / kFragRows;
     const int lane = n % kFragRows + 32 * (kc & 1), step = (kc >> 1) & ((1 << WF) - 1);
-    dst[((load * 64 + lane) << WF) + step] = box[r][c >> 5];
+    V v = box[r][c >> 5];
+    if constexpr (WF == 2) v ^= 0x88888888u;                 // code c (c - 8) -> 4-bit two's complement
+    dst[((load * 64 + lane) << WF) + step] = v;
   }
 }
 
+// unit: what a code of 1 is multiplied as, inverted (a power of two)
 __global__ void pack_row_scales(const float* __restrict__ src, float* __restrict__ dst, int rows,
-                                int mode, int off) {
+                                int mode, int off, float unit) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < rows) dst[packed_row(i, mode, off)] = src[i];
+  if (i < rows) dst[packed_row(i, mode, off)] = src[i] * unit;
 }
 
 }  // namespace sv
