@@ -84,29 +84,45 @@ __global__ __launch_bounds__(128) void relaxed_accept_kernel(
 // Commit of the accepted path (the step of Alg. 1 between two verification passes): the K/V
 // rows of the accepted nodes, appended at cache rows P + node, move to rows P + depth, so that
 // the cache again holds one contiguous prefix; the root (depth 0) already sits at row P.
-// Moves run in increasing depth with a barrier in between: node index >= depth, so a row is
-// read before a later move overwrites it.  grid = (B, n_heads), block = 128.
-template <typename TKV>
-__global__ __launch_bounds__(128) void commit_path_kernel(
-    TKV* __restrict__ kc, TKV* __restrict__ vc, const int32_t* __restrict__ prefix_len, int p_max,
-    int cap, int T, int nh, int d, const int32_t* __restrict__ path,
+// Bound by memory latency: the rows of all depths are requested together and written after all
+// have arrived.  That equals moving them one after the other in increasing depth: only nodes with
+// index > depth move, so no move reads a row that a move of smaller depth has written.
+// U: unit of the copy, `units` per row (16 bytes where rows and caches are aligned to that, else one
+// element).  grid = (B, n_heads), block = 256.
+constexpr int kCommitBatch = 4;              // units in flight per thread: 8 rows of K and of V per pass
+template <typename U>
+__global__ __launch_bounds__(256) void commit_path_kernel(
+    U* __restrict__ kc, U* __restrict__ vc, const int32_t* __restrict__ prefix_len, int p_max,
+    int cap, int T, int nh, int units, const int32_t* __restrict__ path,
     const int32_t* __restrict__ accepted_len, int d_cap) {
+  __shared__ int s_node[SV_MAX_DEPTH + 1];
   const int b = blockIdx.x, h = blockIdx.y;
   int P = prefix_len[b];
-  P = P < 0 ? 0 : (P > p_max ? p_max : P);
   int len = accepted_len[b];
+  if ((int)threadIdx.x <= d_cap) s_node[threadIdx.x] = path[(size_t)b * (d_cap + 1) + threadIdx.x];
+  P = P < 0 ? 0 : (P > p_max ? p_max : P);
   len = len < 0 ? 0 : (len > d_cap ? d_cap : len);
-  TKV* kb = kc + ((size_t)b * nh + h) * cap * d;
-  TKV* vb = vc + ((size_t)b * nh + h) * cap * d;
-  for (int i = 1; i <= len; ++i) {
-    const int node = path[(size_t)b * (d_cap + 1) + i];
-    if (node > i && node < T) {              // node == i: already in place
-      for (int e = threadIdx.x; e < d; e += 128) {
-        kb[(size_t)(P + i) * d + e] = kb[(size_t)(P + node) * d + e];
-        vb[(size_t)(P + i) * d + e] = vb[(size_t)(P + node) * d + e];
-      }
+  const size_t base = ((size_t)b * nh + h) * cap + P;
+  const int n = len * 2 * units;             // depth after depth: K row, V row
+  __syncthreads();
+  for (int i0 = 0; i0 < n; i0 += 256 * kCommitBatch) {
+    U v[kCommitBatch];
+    U* dst[kCommitBatch];
+#pragma unroll
+    for (int k = 0; k < kCommitBatch; ++k) {
+      const int it = i0 + k * 256 + (int)threadIdx.x;
+      dst[k] = nullptr;
+      if (it >= n) continue;
+      const int row = it / units, e = it - row * units, depth = (row >> 1) + 1, node = s_node[depth];
+      if (node <= depth || node >= T) continue;              // node == depth: already in place
+      U* c = (row & 1 ? vc : kc) + base * units + e;
+      v[k] = c[(size_t)node * units];
+      dst[k] = c + (size_t)depth * units;
     }
-    __syncthreads();
+    __syncthreads();                         // every row of the pass has been read ...
+#pragma unroll
+    for (int k = 0; k < kCommitBatch; ++k)
+      if (dst[k]) *dst[k] = v[k];            // ... (later passes read rows beyond those written here)
   }
 }
 

@@ -809,7 +809,7 @@ int sv_tree_build_device(const int32_t* cand_parent, const float* cand_logp,
   if (B < 1 || B > (1 << 15) || T < 1 || T > SV_MAX_TREE_NODES || n_cand < T - 1 ||
       n_cand > kMaxCandidates || d_cap < 0 || d_cap > SV_MAX_DEPTH)
     return SV_ERR_SHAPE;
-  tree_build_kernel<<<B, 256, 0, (hipStream_t)stream>>>(cand_parent, cand_logp, cand_token, n_cand,
+  tree_build_kernel<<<B, 1024, 0, (hipStream_t)stream>>>(cand_parent, cand_logp, cand_token, n_cand,
                                                         root_token, T, (T + 63) / 64, d_cap, parent,
                                                         depth, anc_mask, draft_token, status);
   return launch_status();
@@ -825,14 +825,16 @@ int sv_commit_path(const sv_model_cfg* cfg, const sv_kv_view* kv, int T, const i
   if (kv->prefix_len_max < 0 || (long long)kv->capacity < (long long)kv->prefix_len_max + T)
     return SV_ERR_SHAPE;
   const dim3 grid(B, cfg->n_heads);
-  if (cfg->dtype == SV_F32)
-    commit_path_kernel<float><<<grid, 128, 0, (hipStream_t)stream>>>(
-        (float*)kv->k, (float*)kv->v, kv->prefix_len, kv->prefix_len_max, kv->capacity, T,
-        cfg->n_heads, cfg->head_dim, path, accepted_len, d_cap);
-  else
-    commit_path_kernel<bf16_t><<<grid, 128, 0, (hipStream_t)stream>>>(
-        (bf16_t*)kv->k, (bf16_t*)kv->v, kv->prefix_len, kv->prefix_len_max, kv->capacity, T,
-        cfg->n_heads, cfg->head_dim, path, accepted_len, d_cap);
+  hipStream_t st = (hipStream_t)stream;
+  auto commit = [&](auto* k, auto* v, int units) {
+    commit_path_kernel<<<grid, 256, 0, st>>>(k, v, kv->prefix_len, kv->prefix_len_max, kv->capacity, T, cfg->n_heads, units,
+                                             path, accepted_len, d_cap);
+  };
+  const int row_bytes = cfg->head_dim * (cfg->dtype == SV_F32 ? 4 : 2);
+  if (row_bytes % 16 == 0 && (uintptr_t)kv->k % 16 == 0 && (uintptr_t)kv->v % 16 == 0)
+    commit((u32x4_t*)kv->k, (u32x4_t*)kv->v, row_bytes / 16);
+  else if (cfg->dtype == SV_F32) commit((float*)kv->k, (float*)kv->v, cfg->head_dim);
+  else commit((uint16_t*)kv->k, (uint16_t*)kv->v, cfg->head_dim);
   return launch_status();
 }
 

@@ -9,8 +9,9 @@
 // behind the root.  Output = exactly the arrays the verification calls take (parent, depth,
 // ancestor-or-self bitmask, draft tokens), so a step needs no host round trip for its tree.
 //
-// One workgroup per episode; candidates <= 1024, kept in LDS; ranks by counting (n^2 / 256
-// comparisons per thread: 264 candidates of the paper's setting = 272 per thread).
+// One workgroup of 1024 threads per episode, a thread per candidate (at most 1024, kept in LDS).  Latency
+// bound: the paper's setting (264 candidates, 50 nodes, 16 episodes) took 37 us with 256 threads that walk
+// and sum every path on their own and count over all candidates twice.
 #ifndef SV_TREE_BUILD_H
 #define SV_TREE_BUILD_H
 
@@ -24,64 +25,86 @@ constexpr int kMaxCandidates = 1024;
 // bit 1 = a kept candidate is deeper than d_cap; bit 2 = a kept candidate's parent was not kept
 // (log-probabilities above zero).  A flagged episode gets a root-only chain
 // (every node a child of the root) so that later calls stay in bounds.
-__global__ __launch_bounds__(256) void tree_build_kernel(
+__global__ __launch_bounds__(1024) void tree_build_kernel(
     const int32_t* __restrict__ cand_parent, const float* __restrict__ cand_logp,
     const int32_t* __restrict__ cand_token, int n_cand, const int32_t* __restrict__ root_token,
     int T, int n_words, int d_cap, int32_t* __restrict__ parent, int32_t* __restrict__ depth,
     uint64_t* __restrict__ anc_mask, int32_t* __restrict__ draft_token, int32_t* __restrict__ status) {
   __shared__ float s_score[kMaxCandidates];
   __shared__ int s_par[kMaxCandidates];
-  __shared__ short s_depth[kMaxCandidates];
+  __shared__ int s_rank[kMaxCandidates];
+  __shared__ int s_key[SV_MAX_TREE_NODES];     // kept candidates in order of rank: depth * 1024 + index
   __shared__ short s_node[kMaxCandidates];     // node index of a kept candidate, -1 otherwise
-  __shared__ int s_bad;
+  __shared__ int s_bad, s_levels;
   const int b = blockIdx.x, tid = threadIdx.x;
-  const int32_t* cp = cand_parent + (size_t)b * n_cand;
-  const float* lp = cand_logp + (size_t)b * n_cand;
   const int n_keep = T - 1;
-  if (tid == 0) s_bad = 0;
-  for (int c = tid; c < n_cand; c += 256) {
-    const int p = cp[c];
-    s_par[c] = p;
-    if (p < -1 || p >= c) atomicOr(&s_bad, 1);
+  const bool own = tid < n_cand;               // this thread's candidate is tid
+  int par = -1, dep = 0, tok = 0;
+  float lp = 0.f;
+  if (tid == 0) s_bad = s_levels = 0;
+  __syncthreads();
+  if (own) {
+    par = cand_parent[(size_t)b * n_cand + tid];
+    lp = cand_logp[(size_t)b * n_cand + tid];
+    tok = cand_token[(size_t)b * n_cand + tid];
+    s_par[tid] = par;
+    s_rank[tid] = 0;
+    s_node[tid] = -1;
+    if (par < -1 || par >= tid) atomicOr(&s_bad, 1);
   }
   __syncthreads();
+  bool kept = false;
   if (s_bad == 0) {
-    // score and depth of candidate c: walk up to the root, then add the log-probabilities
-    // from the root down (the order of the sequential definition)
-    for (int c = tid; c < n_cand; c += 256) {
-      int path[SV_MAX_DEPTH + 1];
-      int len = 0, node = c;
-      while (node >= 0 && len <= SV_MAX_DEPTH) {
-        path[len++] = node;
+    bool deep = false;                         // deeper than any tree this library takes
+    if (own) {
+      int node = tid;
+      while (node >= 0 && dep <= SV_MAX_DEPTH) {
+        ++dep;
         node = s_par[node];
       }
-      if (node >= 0) {                 // deeper than any tree this library takes
-        s_depth[c] = (short)(SV_MAX_DEPTH + 1);
-        s_score[c] = -__builtin_inff();
-      } else {
-        float sc = 0.f;
-        for (int i = len - 1; i >= 0; --i) sc = sc + lp[path[i]];
-        s_depth[c] = (short)len;
-        s_score[c] = sc == sc ? sc : -__builtin_inff();   // NaN sorts last: the order stays total
-
-      }
+      deep = node >= 0;
+      atomicMax(&s_levels, dep);
     }
     __syncthreads();
-    // rank among all candidates: higher score first, lower index first on ties
-    for (int c = tid; c < n_cand; c += 256) {
+    // scores from the root down, level after level: one addition per edge, in the order of the sequential
+    // definition
+    const int levels = s_levels;
+    for (int l = 1; l <= levels; ++l) {
+      if (own && !deep && dep == l) s_score[tid] = (par < 0 ? 0.f : s_score[par]) + lp;
+      __syncthreads();
+    }
+    if (own) {
+      const float sc = deep ? -__builtin_inff() : s_score[tid];
+      s_score[tid] = sc == sc ? sc : -__builtin_inff();     // NaN sorts last: the order stays total
+    }
+    __syncthreads();
+    // rank among all candidates: higher score first, lower index first on ties.  `parts` threads count for a
+    // candidate, each over its share of the others.
+    const int parts = n_cand > 0 ? 1024 / n_cand : 0, part = parts ? tid / n_cand : 0, c = tid - part * n_cand;
+    if (part < parts) {
+      const int j0 = n_cand * part / parts, j1 = n_cand * (part + 1) / parts;
       const float sc = s_score[c];
       int rank = 0;
-      for (int j = 0; j < n_cand; ++j) {
+#pragma unroll 8
+      for (int j = j0; j < j1; ++j) {
         const float sj = s_score[j];
         rank += (sj > sc || (sj == sc && j < c)) ? 1 : 0;
       }
-      s_node[c] = rank < n_keep ? (short)0 : (short)-1;
-      if (rank < n_keep && s_depth[c] > d_cap) atomicOr(&s_bad, 2);
+      atomicAdd(&s_rank[c], rank);
+    }
+    __syncthreads();
+    if (own) {
+      const int rank = s_rank[tid];
+      kept = rank < n_keep;
+      if (kept) {
+        s_key[rank] = dep * kMaxCandidates + tid;
+        s_node[tid] = 0;
+        if (dep > d_cap) atomicOr(&s_bad, 2);
+      }
     }
     __syncthreads();
     // log-probabilities above zero can rank a child before its parent: not a tree
-    for (int c = tid; c < n_cand; c += 256)
-      if (s_node[c] >= 0 && s_par[c] >= 0 && s_node[s_par[c]] < 0) atomicOr(&s_bad, 4);
+    if (kept && par >= 0 && s_node[par] < 0) atomicOr(&s_bad, 4);
     __syncthreads();
   }
   int32_t* par_o = parent + (size_t)b * T;
@@ -89,7 +112,7 @@ __global__ __launch_bounds__(256) void tree_build_kernel(
   int32_t* tok_o = draft_token + (size_t)b * T;
   uint64_t* anc_o = anc_mask + (size_t)b * T * n_words;
   if (s_bad != 0) {
-    for (int i = tid; i < T; i += 256) {
+    for (int i = tid; i < T; i += 1024) {
       par_o[i] = i == 0 ? -1 : 0;
       dep_o[i] = i == 0 ? 0 : 1;
       tok_o[i] = root_token[b];
@@ -101,17 +124,13 @@ __global__ __launch_bounds__(256) void tree_build_kernel(
     return;
   }
   // breadth-first number of a kept candidate: 1 + kept candidates before it in (depth, index)
-  for (int c = tid; c < n_cand; c += 256) {
-    if (s_node[c] < 0) continue;
-    const int dc = s_depth[c];
-    int before = 0;
-    for (int j = 0; j < n_cand; ++j) {
-      const int dj = s_depth[j];
-      before += (s_node[j] >= 0 && (dj < dc || (dj == dc && j < c))) ? 1 : 0;
-    }
-    // s_node of kept candidates is only tested for >= 0 by the other threads, so writing the
-    // final (>= 1) number here does not disturb their counts
-    s_node[c] = (short)(1 + before);
+  int node_index = 0;
+  if (kept) {
+    const int key = dep * kMaxCandidates + tid;
+    node_index = 1;
+#pragma unroll 8
+    for (int j = 0; j < n_keep; ++j) node_index += s_key[j] < key ? 1 : 0;
+    s_node[tid] = (short)node_index;
   }
   __syncthreads();
   if (tid == 0) {
@@ -122,20 +141,18 @@ __global__ __launch_bounds__(256) void tree_build_kernel(
     anc_o[0] = 1ull;
     status[b] = 0;
   }
-  const int32_t* tk = cand_token + (size_t)b * n_cand;
-  for (int c = tid; c < n_cand; c += 256) {
-    const int i = s_node[c];
-    if (i < 1) continue;
-    const int p = s_par[c];
-    par_o[i] = p < 0 ? 0 : s_node[p];
-    dep_o[i] = s_depth[c];
-    tok_o[i] = tk[c];
+  if (kept) {
+    par_o[node_index] = par < 0 ? 0 : s_node[par];
+    dep_o[node_index] = dep;
+    tok_o[node_index] = tok;
     uint64_t m[2] = {1ull, 0ull};                      // the root
-    for (int node = c; node >= 0; node = s_par[node]) {
+    for (int node = tid; node >= 0; node = s_par[node]) {
       const int ni = s_node[node];
-      m[ni >> 6] |= 1ull << (ni & 63);
+      if (ni < 64) m[0] |= 1ull << ni;
+      else m[1] |= 1ull << (ni - 64);
     }
-    for (int w = 0; w < n_words; ++w) anc_o[(size_t)i * n_words + w] = m[w];
+    anc_o[(size_t)node_index * n_words] = m[0];
+    if (n_words > 1) anc_o[(size_t)node_index * n_words + 1] = m[1];
   }
 }
 

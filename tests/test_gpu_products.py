@@ -1,8 +1,11 @@
 """The layer's products where their split over the chip changes: row counts around the 32-row blocks and
 the kernels' limits (1, 64, 128 rows), ragged numbers of weight tiles per workgroup and of K steps per
 wave, every weight format.  One small layer stack against the float64 oracle."""
+import numpy as np
 import pytest
+import torch
 
+from paper_2507_22424_amd import binding as sv
 from paper_2507_22424_amd import workload as wl
 
 from parity_utils import SideBySide
@@ -28,3 +31,35 @@ def test_products_at_the_edges_of_their_split(dtype, T, B, H, F):
                        n_heads=H // 128, head_dim=128, mlp_dim=F, vocab=1024, n_bins=256, tree_nodes=T,
                        n_episodes=B, prefix_lo=20, prefix_hi=30, max_children=6, spine_lo=min(3, T - 1), r_values=(0, 4))
     check_forward(SideBySide(cfg), TOL)
+
+
+@pytest.mark.parametrize("dtype,d,shift", [("f32", 64, 0), ("f32", 6, 0), ("f32", 64, 1), ("bf16", 128, 0), ("bf16", 128, 1)])
+def test_commit_of_deep_paths_and_unaligned_caches(dtype, d, shift):
+    """Paths of up to 31 nodes (several passes of the copy), a moved row that is itself the target of a deeper
+    node, caches whose rows are not aligned to 16 bytes (shift: elements): rows move as one after the other."""
+    B, T, d_cap, nh, cap = 3, 128, 31, 2, 192
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    cfg = sv.ModelCfg(sv.SV_F32 if dtype == "f32" else sv.SV_BF16, 256, nh, d, 256, 512, 1e-5, 1e4)
+    prefix, n = [7, 0, 33], B * nh * cap * d
+    gen = torch.Generator().manual_seed(5)
+    k0, v0 = (torch.randn(n, generator=gen).to(tdt) for _ in "kv")
+    buf = [torch.zeros(n + 8, dtype=tdt, device="cuda") for _ in "kv"]
+    for t, src in zip(buf, (k0, v0)):
+        t[shift:shift + n] = src.cuda()
+    path = np.full((B, d_cap + 1), -1, dtype=np.int32)
+    path[0] = np.arange(32) * 4                             # 0, 4, 8, ...: node 4 moves to row 1, node 16 to row 4, ...
+    path[1, :9] = [0, 2, 3, 4, 5, 6, 7, 8, 100]             # every source row but one is a target as well
+    path[2, :4] = [0, 1, 2, 127]
+    alen = np.array([31, 8, 3], dtype=np.int32)
+    plen = torch.tensor(prefix, dtype=torch.int32, device="cuda")
+    size = k0.element_size()
+    view = sv.KvView(buf[0].data_ptr() + shift * size, buf[1].data_ptr() + shift * size, plen.data_ptr(), max(prefix), cap)
+    sv.sv_commit_path(cfg, view, T, torch.from_numpy(path).cuda(), torch.from_numpy(alen).cuda(), B, d_cap)
+    torch.cuda.synchronize()
+    for t, src in zip(buf, (k0, v0)):
+        want = src.clone().reshape(B, nh, cap, d)
+        for b in range(B):
+            for i in range(1, alen[b] + 1):
+                want[b, :, prefix[b] + i] = want[b, :, prefix[b] + path[b, i]].clone()
+        assert torch.equal(t[shift:shift + n].cpu().reshape(B, nh, cap, d), want)
+        assert not t[:shift].any() and not t[shift + n:].any()
