@@ -140,7 +140,8 @@ def _dev(t: Optional[torch.Tensor], dtype=None, name="tensor") -> int:
 
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # (the raw handle: building a Stream object costs as much as the rest of a call)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
