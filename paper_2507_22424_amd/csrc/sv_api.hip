@@ -11,6 +11,7 @@
 #include "specvla_verify_aux.h"
 #include "sv_accept.h"
 #include "sv_attention.h"
+#include "sv_f32.h"
 #include "sv_internal.h"
 #include "sv_kernels.h"
 #include "sv_pack.h"
@@ -109,17 +110,11 @@ static WorkspaceLayout workspace_layout(const sv_model_cfg& c, int m_rows, int n
     // partial results of the tree attention when the keys of a task are split
     L.att_part = o; o = align_up(o + 8 * mr * c.n_heads * kAttPartStride * 4, kAlign);
   } else {
-    size_t n_max = 3 * D;
-    if (2 * F > n_max) n_max = 2 * F;
-    if (H > n_max) n_max = H;
-    L.part = o;     o = align_up(o + mp * n_max * 4, kAlign);
-    L.xhat = o;     o = align_up(o + mp * H * 4, kAlign);
     L.q = o;        o = align_up(o + mp * D * 4, kAlign);
     L.attn = o;     o = align_up(o + mp * D * 4, kAlign);
     L.act = o;      o = align_up(o + mp * F * 4, kAlign);
   }
-  L.head_z = o;      o = align_up(o + mp * H * 4, kAlign);
-  L.head_logits = o; o = align_up(o + mp * (size_t)(n_scored > 0 ? n_scored : 0) * 4 * 16, kAlign);   // up to 16 K-slice planes
+  L.head_logits = o; o = align_up(o + mp * (size_t)(n_scored > 0 ? n_scored : 0) * 4, kAlign);
   // (the regions above do not move with n_scored: a layer call finds them without knowing it)
   if (c.dtype != SV_F32 && n_scored > 0 && n_scored % kFragRows == 0) {
     size_t wgs = 1, xch = 0;
@@ -160,12 +155,6 @@ static int check_packed_head(const sv_model_cfg* cfg, int vocab_lo, int vocab_hi
   return SV_OK;
 }
 
-// K slices of the LM-head GEMM (it has few output tiles, so the reduction is spread out).
-static int head_planes(int hidden) {
-  int p = hidden / 256;
-  return p < 1 ? 1 : (p > 16 ? 16 : p);
-}
-
 static inline int launch_status() { return hipGetLastError() == hipSuccess ? SV_OK : SV_ERR_LAUNCH; }
 
 __global__ void zero_ints(int* p, size_t n) {
@@ -173,7 +162,7 @@ __global__ void zero_ints(int* p, size_t n) {
   if (i < n) p[i] = 0;
 }
 
-// ---- float32 models: plain kernels, one launch per step of the layer ----------------------
+// ---- float32 models: five launches per layer ------------------------------------------------
 
 static int verify_layer_f32(const sv_model_cfg& c, const WorkspaceLayout& wl, const char* packed, float* x,
                             const sv_kv_view& kv, const sv_tree& tree, int B, char* ws,
@@ -182,44 +171,35 @@ static int verify_layer_f32(const sv_model_cfg& c, const WorkspaceLayout& wl, co
   auto mark = [&](int i) {
     if (ev) (void)hipEventRecord(ev[i], st);
   };
-  const int H = c.hidden, D = c.n_heads * c.head_dim, F = c.mlp_dim;
+  const int H = c.hidden, d = c.head_dim, D = c.n_heads * d, F = c.mlp_dim;
   const PackedLayout pl = packed_layout(c);
-  const float* g1 = (const float*)(packed + pl.g1);
-  const float* g2 = (const float*)(packed + pl.g2);
-  float* xhat = (float*)(ws + wl.xhat);
   float* q = (float*)(ws + wl.q);
   float* attn = (float*)(ws + wl.attn);
   float* act = (float*)(ws + wl.act);
-  float* part = (float*)(ws + wl.part);
-  auto gemm = [&](const float* X, size_t w_off, int N, int K) {
-    dim3 grid(ceil_div(N, 64), ceil_div(M, 64), 1);
-    gemm_nt_fma<float, float><<<grid, 256, 0, st>>>(X, K, (const float*)(packed + w_off), K, part,
-                                                    N, 0, M, N, K);
+  auto product = [&](auto epi, const float* X, size_t w_off, const float* gain, int N, int K, float* out) {
+    F32Args<float, float> a;
+    memset(&a, 0, sizeof(a));
+    a.X = X; a.gain = gain; a.W = (const float*)(packed + w_off); a.M = M; a.N = N; a.K = K; a.eps = c.rms_eps; a.out = out;
+    a.kc = (float*)kv.k; a.vc = (float*)kv.v; a.depth = tree.depth; a.prefix_len = kv.prefix_len; a.p_max = kv.prefix_len_max;
+    a.cap = kv.capacity; a.T = T_; a.nh = c.n_heads; a.d = d; a.theta = c.rope_theta;
+    f32_launch<decltype(epi)::value>(a, st);
   };
-  rmsnorm_rows<float><<<M, 256, 0, st>>>(x, g1, xhat, H, c.rms_eps);
   mark(0);
-  gemm(xhat, pl.wqkv, 3 * D, H);
+  product(std::integral_constant<int, EPI_QKV>{}, x, pl.wqkv, (const float*)(packed + pl.g1), 3 * D / 2, H, q);
   mark(1);
-  qkv_rope_append<float><<<M, 256, 0, st>>>(part, 1, 0, T_, c.n_heads, c.head_dim, tree.depth,
-                                            kv.prefix_len, kv.prefix_len_max, kv.capacity,
-                                            c.rope_theta, q, (float*)kv.k, (float*)kv.v);
   mark(2);
-  tree_attention_rowwise<float, float><<<dim3(ceil_div(M, 4), c.n_heads), 256, 0, st>>>(
-      q, (const float*)kv.k, (const float*)kv.v, kv.prefix_len, kv.prefix_len_max, tree.anc_mask,
-      tree.n_words, T_, c.n_heads, c.head_dim, kv.capacity, attn, M);
+  auto attention = d % 4 == 0 && (uintptr_t)kv.k % 16 == 0 && (uintptr_t)kv.v % 16 == 0 ? tree_attention_f32<4> : tree_attention_f32<1>;
+  attention<<<dim3(M, c.n_heads), 256, 0, st>>>(q, (const float*)kv.k, (const float*)kv.v, kv.prefix_len, kv.prefix_len_max,
+                                                tree.anc_mask, tree.n_words, T_, c.n_heads, d, kv.capacity, attn);
   mark(3);
-  gemm(attn, pl.wo, H, D);
+  product(std::integral_constant<int, EPI_RESID>{}, attn, pl.wo, nullptr, H, D, x);
   mark(4);
-  residual_rmsnorm<float><<<M, 256, 0, st>>>(part, 1, 0, x, g2, xhat, H, c.rms_eps);
   mark(5);
-  gemm(xhat, pl.wgu, 2 * F, H);
+  product(std::integral_constant<int, EPI_SWIGLU>{}, x, pl.wgu, (const float*)(packed + pl.g2), F, H, act);
   mark(6);
-  swiglu_rows<float><<<dim3(ceil_div(F, 256), M), 256, 0, st>>>(part, 1, 0, act, F);
   mark(7);
-  gemm(act, pl.wd, H, F);
+  product(std::integral_constant<int, EPI_RESID>{}, act, pl.wd, nullptr, H, F, x);
   mark(8);
-  residual_rmsnorm<float><<<M, 256, 0, st>>>(part, 1, 0, x, nullptr, (float*)nullptr, H,
-                                             c.rms_eps);
   return launch_status();
 }
 
@@ -358,29 +338,31 @@ static int pack_layer_t(const sv_model_cfg& c, const sv_layer_weights& w, char* 
   return launch_status();
 }
 
-// z: [n_rows, H] float32 normalised rows; parts: [planes][m_pad * n] float32 logit planes.
+// (a row of up to 2048 is one round trip for 256 threads)
+static void launch_argmax(const float* logits, int n_rows, int n, int lo, int32_t* out_token, float* copy, hipStream_t st) {
+  if (n > 2048) argmax_rows_wide<1024><<<n_rows, 1024, 0, st>>>(logits, n, lo, out_token, copy);
+  else argmax_rows_wide<256><<<n_rows, 256, 0, st>>>(logits, n, lo, out_token, copy);
+}
+
+// The head on raw rows: logits (to `logits_ws`, [n_rows, hi - lo], if the caller wants none), then the row argmax.
 template <typename T>
 static int head_t(const sv_model_cfg& c, const T* g_final, const T* w_lm, const float* x,
-                  int n_rows, int lo, int hi, int32_t* out_token, float* out_logits, float* z,
-                  float* parts, hipStream_t st) {
-  const int H = c.hidden, n = hi - lo;
-  const int planes = head_planes(H);
-  const size_t plane = (size_t)ceil_div(n_rows, kMTile) * kMTile * n;
-  rmsnorm_rows_tg<T, float><<<n_rows, 256, 0, st>>>(x, g_final, z, H, c.rms_eps);
-  dim3 grid(ceil_div(n, 64), ceil_div(n_rows, 64), planes);   // K cut into `planes` slices
-  gemm_nt_fma<float, T><<<grid, 256, 0, st>>>(z, H, w_lm + (size_t)lo * H, H, parts, n, plane,
-                                              n_rows, n, H);
-  argmax_rows<<<n_rows, 64, 0, st>>>(parts, planes, plane, out_logits, n, lo, out_token);
+                  int n_rows, int lo, int hi, int32_t* out_token, float* out_logits, float* logits_ws, hipStream_t st) {
+  F32Args<T, T> a;
+  memset(&a, 0, sizeof(a));
+  a.X = x; a.gain = g_final; a.W = w_lm + (size_t)lo * c.hidden; a.M = n_rows; a.N = hi - lo; a.K = c.hidden; a.eps = c.rms_eps;
+  a.out = out_logits ? out_logits : logits_ws;
+  a.T = 1; a.nh = 1; a.d = 2;
+  f32_launch<EPI_OUT>(a, st);
+  launch_argmax(a.out, n_rows, a.N, lo, out_token, nullptr, st);
   return launch_status();
 }
 
-// Scratch of sv_action_head_argmax_noalloc: the normalised rows and the logit planes of one call,
-// in device memory that belongs to the library image (one copy per GPU, for the life of the
+// Scratch of sv_action_head_argmax_noalloc: the logits of one call, in device memory that belongs to the library image (one copy per GPU, for the life of the
 // process).  Host code never uses the array's name as an address: scratch_address() asks the
 // runtime where the current device's copy lives, once per device.
 constexpr int kNoallocMaxRows = 64, kNoallocMaxScored = 256, kNoallocMaxHidden = 8192;
-constexpr size_t kNoallocZBytes = (size_t)kNoallocMaxRows * kNoallocMaxHidden * 4;
-constexpr size_t kNoallocScratchBytes = kNoallocZBytes + (size_t)16 * kMTile * kNoallocMaxScored * 4;
+constexpr size_t kNoallocScratchBytes = (size_t)kNoallocMaxRows * kNoallocMaxScored * 4;
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];
 
 static int scratch_address(unsigned char** out) {
@@ -407,7 +389,8 @@ static int head_packed(const sv_model_cfg& c, const char* packed, const float* x
   const WorkspaceLayout wl = workspace_layout(c, n_rows, n);
   const HeadLayout hl = head_layout(c, n);
   const int n_xcd = device_xcds();
-  float* logits = (float*)(ws + wl.head_logits);
+  // (the product stores 16 bytes at a time)
+  float* logits = out_logits && (uintptr_t)out_logits % 16 == 0 ? out_logits : (float*)(ws + wl.head_logits);
   uint4* xs = (uint4*)(ws + wl.head_xs);
   float* ssq = (float*)(ws + wl.head_ssq);
   split_gain_kernel<<<dim3(wl.n_rb, H / 256), 256, 0, st>>>(x, (const float*)(packed + hl.gain), n_rows, H, wl.m_pad, wl.n_rb, xs, ssq);
@@ -422,7 +405,7 @@ static int head_packed(const sv_model_cfg& c, const char* packed, const float* x
   e.M = n_rows; e.n_rb = wl.n_rb; e.m_pad = wl.m_pad; e.K = H; e.eps = c.rms_eps;
   e.ssq = ssq; e.n_ssq = H / 256; e.out = logits;
   launch_product(p, EPI_OUT, 0, n_xcd, xs, (const uint4*)(packed + hl.w), n, H, scratch, e, st);
-  argmax_rows_wide<<<n_rows, 256, 0, st>>>(logits, out_logits, n, lo, out_token);
+  launch_argmax(logits, n_rows, n, lo, out_token, out_logits == logits ? nullptr : out_logits, st);
   return launch_status();
 }
 
@@ -701,13 +684,12 @@ int sv_action_head_argmax(const sv_model_cfg* cfg, const void* g_final, const vo
       ws_bytes < workspace_layout(*cfg, n_rows, vocab_hi - vocab_lo).total)
     return SV_ERR_WORKSPACE;
   const WorkspaceLayout wl = workspace_layout(*cfg, n_rows, vocab_hi - vocab_lo);
-  float* z = (float*)((char*)workspace + wl.head_z);
-  float* parts = (float*)((char*)workspace + wl.head_logits);
+  float* logits = (float*)((char*)workspace + wl.head_logits);
   if (cfg->dtype == SV_F32)
     return head_t<float>(*cfg, (const float*)g_final, (const float*)w_lm, x, n_rows, vocab_lo,
-                         vocab_hi, out_token, out_logits, z, parts, (hipStream_t)stream);
+                         vocab_hi, out_token, out_logits, logits, (hipStream_t)stream);
   return head_t<bf16_t>(*cfg, (const bf16_t*)g_final, (const bf16_t*)w_lm, x, n_rows, vocab_lo,
-                        vocab_hi, out_token, out_logits, z, parts, (hipStream_t)stream);
+                        vocab_hi, out_token, out_logits, logits, (hipStream_t)stream);
 }
 
 int sv_action_head_argmax_noalloc(const sv_model_cfg* cfg, const void* g_final, const void* w_lm,
@@ -722,13 +704,12 @@ int sv_action_head_argmax_noalloc(const sv_model_cfg* cfg, const void* g_final, 
   unsigned char* base = nullptr;
   const int rs = scratch_address(&base);
   if (rs != SV_OK) return rs;
-  float* z = (float*)base;
-  float* parts = (float*)(base + kNoallocZBytes);
+  float* logits = (float*)base;
   if (cfg->dtype == SV_F32)
     return head_t<float>(*cfg, (const float*)g_final, (const float*)w_lm, x, n_rows, vocab_lo,
-                         vocab_hi, out_token, out_logits, z, parts, (hipStream_t)stream);
+                         vocab_hi, out_token, out_logits, logits, (hipStream_t)stream);
   return head_t<bf16_t>(*cfg, (const bf16_t*)g_final, (const bf16_t*)w_lm, x, n_rows, vocab_lo,
-                        vocab_hi, out_token, out_logits, z, parts, (hipStream_t)stream);
+                        vocab_hi, out_token, out_logits, logits, (hipStream_t)stream);
 }
 
 int sv_packed_head_bytes(const sv_model_cfg* cfg, int vocab_lo, int vocab_hi, size_t* bytes) {

@@ -59,16 +59,6 @@ __device__ inline float wave_sum(float v) {
   return v;
 }
 
-// Sum over a workgroup of 256 threads (4 waves); every thread gets the total.
-// `scratch` must hold 4 floats of LDS and may be reused after the call returns.
-__device__ inline float block_sum_256(float v, float* scratch) {
-  v = wave_sum(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return scratch[0] + scratch[1] + scratch[2] + scratch[3];
-}
-
 // Where the pieces of a packed layer live (bytes from the start of the blob).
 struct PackedLayout {
   size_t g1, g2, wqkv, wo, wgu, wd, total;
@@ -102,13 +92,13 @@ inline PackedLayout packed_layout(const sv_model_cfg& c) {
 struct WorkspaceLayout {
   size_t q, attn, total;         // float32, both storage types
   // float32 models
-  size_t part, xhat, act;
+  size_t act;
   // bf16 models: counters of the workgroups that share an output (+ status word), activation fragments of
   // the residual stream, the attention output and the SwiGLU output, partial row sums of x^2, sums that
   // cross workgroups, partial results of a split tree attention
   size_t counters, counter_bytes, xs_x, xs_attn, xs_act, ssq, xch, att_part;
-  // heads: plain (normalised rows, logit planes), packed (bf16 models, scored rows a multiple of 32)
-  size_t head_z, head_logits, head_cnt, head_cnt_bytes, head_xs, head_ssq, head_xch;
+  // heads: logits; packed (bf16 models, scored rows a multiple of 32)
+  size_t head_logits, head_cnt, head_cnt_bytes, head_xs, head_ssq, head_xch;
   int m_pad, n_rb;               // rows as laid out, row blocks of 32
 };
 

@@ -33,6 +33,26 @@ def test_products_at_the_edges_of_their_split(dtype, T, B, H, F):
     check_forward(SideBySide(cfg), TOL)
 
 
+# float32: sums of at most 8192 products in another order than the oracle's float64, 2^-24 each and random in
+# sign: below 1e-6 of a row; the parity tests' bound for float32 models leaves room for the softmax.
+TOL_F32 = 1e-5
+
+
+@pytest.mark.parametrize("T,B,P,H,nh,d,F,V", [
+    (1, 1, 5, 256, 4, 64, 688, 512),          # one row in a tile of 16
+    (17, 2, 40, 254, 3, 10, 77, 300),         # K no multiple of 4, odd half heads, ragged tiles everywhere
+    (33, 1, 250, 132, 2, 36, 90, 512),        # ragged K of 16-byte rows; keys beyond one pass of 256
+    (128, 1, 600, 64, 2, 128, 64, 512),       # two mask words, three passes, columns dealt in two key groups a wave
+    (128, 2, 20, 64, 32, 128, 8192, 8192),    # 64 x 64 blocks: q/k/v, gate/up, head
+    (100, 3, 20, 8192, 1, 64, 64, 512),       # 64 x 64 blocks: output, down; rows ragged
+])
+def test_float32_products_and_attention_at_their_edges(T, B, P, H, nh, d, F, V):
+    cfg = wl.C1.scaled(name=f"f32-{B}x{T}-{H}-{nh}x{d}-{F}", index=60 + B, n_layers=1, hidden=H, n_heads=nh, head_dim=d, mlp_dim=F,
+                       vocab=V, n_bins=256, tree_nodes=T, n_episodes=B, prefix_lo=max(1, P - 9), prefix_hi=P, max_children=6,
+                       spine_lo=min(3, T - 1), r_values=(0, 4))
+    check_forward(SideBySide(cfg, full_vocab=V > 4096), TOL_F32)
+
+
 @pytest.mark.parametrize("dtype,d,shift", [("f32", 64, 0), ("f32", 6, 0), ("f32", 64, 1), ("bf16", 128, 0), ("bf16", 128, 1)])
 def test_commit_of_deep_paths_and_unaligned_caches(dtype, d, shift):
     """Paths of up to 31 nodes (several passes of the copy), a moved row that is itself the target of a deeper
