@@ -256,7 +256,7 @@ static int verify_layer_bf16(const sv_model_cfg& c, const LayerCall& lc, const c
     launch_product(p, epi, wf, lc.n_xcd, xs, (const uint4*)(packed + w_off), N, K, scratch, e, st);
   };
   if (first)
-    split_gain_kernel<<<dim3(wl.n_rb, H / 256), 256, 0, st>>>(x, (const float*)(packed + pl.g1), M, H, wl.m_pad, wl.n_rb, xs_x, ssq);
+    split_gain_kernel<<<dim3(wl.n_rb * 4, H / 256), 256, 0, st>>>(x, (const float*)(packed + pl.g1), M, H, wl.m_pad, wl.n_rb, xs_x, ssq);
   mark(0);
   {
     EpiArgs e = epilogue(H, pl.sqkv);
@@ -393,7 +393,7 @@ static int head_packed(const sv_model_cfg& c, const char* packed, const float* x
   float* logits = out_logits && (uintptr_t)out_logits % 16 == 0 ? out_logits : (float*)(ws + wl.head_logits);
   uint4* xs = (uint4*)(ws + wl.head_xs);
   float* ssq = (float*)(ws + wl.head_ssq);
-  split_gain_kernel<<<dim3(wl.n_rb, H / 256), 256, 0, st>>>(x, (const float*)(packed + hl.gain), n_rows, H, wl.m_pad, wl.n_rb, xs, ssq);
+  split_gain_kernel<<<dim3(wl.n_rb * 4, H / 256), 256, 0, st>>>(x, (const float*)(packed + hl.gain), n_rows, H, wl.m_pad, wl.n_rb, xs, ssq);
   const ProductPlan p = plan_product(n_rows, n, H, 0, n_xcd);
   ProductScratch scratch;
   scratch.xch = (f32x4_t*)(ws + wl.head_xch);
