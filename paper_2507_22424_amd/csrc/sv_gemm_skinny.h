@@ -41,7 +41,9 @@ struct SkinnyArgs {
   int N;                     // output columns
   int lgS;                   // S = 1 << lgS workgroups along K
   int gpx, n_xcd;            // tile groups per XCD, XCDs
-  int tq, trem;              // tiles per group, groups with one more
+  // tiles per group, groups with one more, both in half tiles (lgH = 0) or tiles (1).  Half h of a tile:
+  // its rows 8h .. 8h+7 and 16+8h .. 16+8h+7, the quads q with q % 2 == h
+  int tq, trem, lgH;
   int uq, urem;              // weight loads (units of 16, 32 or 64 k-values) per wave, waves with one more
   // scratch of the sums that cross workgroups: one region per workgroup, addressed by XCD, so that no
   // address is ever written through one L2 and read through another
@@ -51,6 +53,16 @@ struct SkinnyArgs {
   int ucap, unit_stride;
   EpiArgs e;
 };
+
+// The tiles of group g: the first, how many, and which halves at the ends belong to its neighbours.
+struct SkinnyTiles {
+  int begin, count;
+  bool skip_first, skip_last;
+};
+__device__ inline SkinnyTiles skinny_tiles(const SkinnyArgs& a, int g) {
+  const int h0 = (g * a.tq + min(g, a.trem)) << a.lgH, h1 = h0 + ((a.tq + (g < a.trem ? 1 : 0)) << a.lgH);
+  return {h0 >> 1, h1 > h0 ? ((h1 + 1) >> 1) - (h0 >> 1) : 0, (h0 & 1) != 0, (h1 & 1) != 0};
+}
 
 // LDS: the sums in exchange between the waves, [dest wave][source][quads][64] x 16 bytes
 template <int RB, int NT, int EPI>
@@ -86,8 +98,8 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = 1 << a.lgS;
   const int g = xcd * a.gpx + ug;
-  const int t_begin = g * a.tq + min(g, a.trem);
-  const int t_count = a.tq + (g < a.trem ? 1 : 0);
+  const SkinnyTiles tl = skinny_tiles(a, g);
+  const int t_begin = tl.begin, t_count = tl.count;
 
   // this wave's run of weight loads
   const int ws = sp * 4 + wave;
@@ -117,7 +129,11 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   gptr_t xp = (gptr_t)a.Xs + (size_t)u0 * UK * x_step;
   unsigned w_off[NT], x_off[RB];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) w_off[t] = (unsigned)min(t, t_count - 1) * 64u + lane;   // (fewer tiles than NT: the last one again, dropped below)
+  for (int t = 0; t < NT; ++t) {
+    // (fewer tiles than NT: the last one again, dropped below; a half that is not this group's: the other half again)
+    const unsigned l = t == 0 && tl.skip_first ? lane | 8 : (t >= t_count - 1 && tl.skip_last ? lane & ~8 : lane);
+    w_off[t] = (unsigned)min(t, t_count - 1) * 64u + l;
+  }
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) x_off[rb] = rb * 128u + lane;
   u32x4_t xr[DX][2 * RB], wr[DW][NT];
@@ -288,6 +304,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
         const int u = PAIR ? 2 * j + (wave >> 1) : j, q = PAIR ? (wave & 1) : wave;
         const int t = u / RB, rb = u % RB;
         if (t >= t_count) break;
+        if ((t == 0 && tl.skip_first && !(q & 1)) || (t == t_count - 1 && tl.skip_last && (q & 1))) continue;
         f32x4_t v[2] = {part[b][0][0], part[b][QI - 1][0]};
 #pragma unroll
         for (int s2 = 1; s2 < SS; ++s2) {
@@ -335,8 +352,7 @@ __global__ __launch_bounds__(256, 1) void gemm_skinny(const SkinnyArgs a) {
   __shared__ int s_crow[EPI == EPI_QKV ? 32 * RB : 1];
   __shared__ __attribute__((aligned(16))) float s_freq[64];
   const int ug = (int)blockIdx.y >> a.lgS, sp = (int)blockIdx.y & ((1 << a.lgS) - 1);
-  const int g = (int)blockIdx.x * a.gpx + ug;
-  const int t_count = a.tq + (g < a.trem ? 1 : 0);
+  const int t_count = skinny_tiles(a, (int)blockIdx.x * a.gpx + ug).count;
   if (t_count == 0) return;
   if (t_count == NTM) skinny_body<RB, NTM, EPI, WF>(a, lds, s_rows, s_pos, s_crow, s_freq, blockIdx.x, ug, sp);
   else skinny_body<RB, NTM - 1, EPI, WF>(a, lds, s_rows, s_pos, s_crow, s_freq, blockIdx.x, ug, sp);

@@ -115,7 +115,14 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
     memset(&a, 0, sizeof(a));
     const int units = K / (kFragK << wf), waves = 4 << p.lgS;
     a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd;
-    a.tq = tiles / groups; a.trem = tiles % groups;
+    // Groups end at half tiles where that makes the largest group smaller, the weight bytes set the time (up to
+    // 32 rows of bf16 weights) and nothing is written per tile (the residual's row sums are).  7B, gate/up, 5.375 tiles
+    // a group: single row 3247 -> 3185 us per step, one layer of 26 nodes 104.3 -> 102.7; 60 rows 3851 -> 3864, and 3 %
+    // slower with 8-bit and 4-bit weights: more groups then multiply (and convert) six tiles.
+    const bool halves = p.rb == 1 && wf == 0 && epi != EPI_RESID && ceil_div(2 * tiles, groups) % 2;
+    a.lgH = halves ? 0 : 1;
+    const int pieces = halves ? 2 * tiles : tiles;
+    a.tq = pieces / groups; a.trem = pieces % groups;
     a.uq = units / waves; a.urem = units % waves;
     a.xch = s.xch; a.group_cnt = s.group_cnt; a.status = s.status; a.ucap = s.ucap; a.unit_stride = p.unit_stride;
     a.e = e;
