@@ -242,7 +242,7 @@ int sv_action_head_argmax(const sv_model_cfg *cfg, const void *g_final, const vo
 
 /* sv_action_head_argmax for callers that cannot allocate device memory and have no workspace to
  * hand over: code recorded into a HIP graph, tight serving loops, harnesses that forbid
- * hipMalloc.  Same kernels, same results; the scratch (normalised rows, logit planes: 3 MiB) is
+ * hipMalloc.  Same kernels, same results; the scratch (the logits: 64 KiB) is
  * a fixed array inside the library image, one copy per GPU for the life of the process.  The
  * call allocates nothing and frees nothing.  Limits: n_rows <= 64, vocab_hi - vocab_lo <= 256,
  * hidden <= 8192; beyond them SV_ERR_WORKSPACE and nothing is launched.  All calls on one GPU
