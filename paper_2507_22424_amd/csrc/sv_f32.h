@@ -221,8 +221,9 @@ __global__ __launch_bounds__(64 * NW) void f32_product(const F32Args<TW, TG> a) 
 }
 
 // Few outputs: one tile (pair) per workgroup, 8 waves along K, so that many CUs ask for the weights and each
-// wave has one or two round trips.  From 512 workgroups of 64 x 64 outputs on, those: every operand is then
-// used four times as often and the matrix cores, not the L2, set the time.
+// wave has one or two round trips.  From 96 workgroups of 64 x 64 outputs on, those: every operand is then
+// used four times as often.  us, 16 x 16 / 64 x 64 outputs at so many of the latter: float32, K = 256: 16: 10.3 /
+// 14.3, 128: 25.0 / 15.6, 512: 75.7 / 26.9; bf16 weights, K = 4096: 60: 69 / 106, 128: 136 / 109, 500: 506 / 189.
 template <int EPI, typename TW, typename TG>
 void f32_launch(const F32Args<TW, TG>& a, hipStream_t st) {
   const bool vec = a.K % 4 == 0 && (uintptr_t)a.X % 16 == 0 && (uintptr_t)a.W % (4 * sizeof(TW)) == 0 &&
@@ -230,7 +231,7 @@ void f32_launch(const F32Args<TW, TG>& a, hipStream_t st) {
   constexpr int P = epi_pairs(EPI) ? 2 : 1;
   const long long big = (long long)ceil_div(a.M, 64) * ceil_div(a.N, 64 / P);
   const dim3 wide(ceil_div(a.N, 64 / P), ceil_div(a.M, 64)), small(ceil_div(a.N, 16), ceil_div(a.M, 16));
-  if (big >= 512) {
+  if (big >= 96) {
     if (vec) f32_product<EPI, 4, 4, 4, true, TW, TG><<<wide, 256, 0, st>>>(a);
     else f32_product<EPI, 4, 4, 4, false, TW, TG><<<wide, 256, 0, st>>>(a);
   } else {
