@@ -165,7 +165,9 @@ int sv_workspace_bytes(const sv_model_cfg *cfg, int B, int T, int n_scored, size
 /* Prepares a freshly allocated (or otherwise dirty) workspace: zeroes the inter-workgroup
  * arrival counters at its start with a small kernel on `stream`.  Call once after allocating
  * the workspace and before its first use; every later call of the library leaves the counters
- * zero again.  workspace: [device], 256-byte aligned, ws_bytes >= sv_workspace_bytes(...). */
+ * zero again.  Their place does not depend on B, T or n_scored: one workspace, prepared once, serves
+ * calls of other sizes too - layers and heads - as long as it holds sv_workspace_bytes of each.
+ * workspace: [device], 256-byte aligned, ws_bytes >= sv_workspace_bytes(...). */
 int sv_workspace_init(const sv_model_cfg *cfg, int B, int T, int n_scored, void *workspace,
                       size_t ws_bytes, void *stream);
 
@@ -199,7 +201,8 @@ int sv_tree_build_device(const int32_t *cand_parent, const float *cand_logp,
  *   x:         [device] float32 [B*T, H], residual stream, updated in place
  *   kv, tree:  [host] structs of [device] pointers, see above; tree->n_nodes = T
  *   workspace: [device], 256-byte aligned, ws_bytes >= sv_workspace_bytes(cfg, B, T, *),
- *              prepared once with sv_workspace_init; calls sharing a workspace must not overlap
+ *              prepared once with sv_workspace_init (for these sizes or others); calls sharing
+ *              a workspace must not overlap
  * bf16 models (also with 8-bit or 4-bit weights): the float32 activations enter the projections
  * as the sum of two bf16 numbers (2^-16 of each value); the partial sums of workgroups that
  * share a product along K are float32 and added in a fixed order.  A NaN or infinity reaches exactly the
@@ -261,8 +264,8 @@ int sv_action_head_argmax_noalloc(const sv_model_cfg *cfg, const void *g_final, 
  *   sv_pack_head: g_final [device] [H] bf16, w_lm [device] [V, H] bf16 row-major;
  *                 packed [device], 256-byte aligned, packed_bytes >= sv_packed_head_bytes
  *   sv_action_head_argmax_packed: packed_head from sv_pack_head with the same cfg and range;
- *                 x, out_token, out_logits as in sv_action_head_argmax; workspace sized and
- *                 initialised with n_scored = vocab_hi - vocab_lo
+ *                 x, out_token, out_logits as in sv_action_head_argmax; workspace sized with
+ *                 n_scored = vocab_hi - vocab_lo and prepared with sv_workspace_init
  * SV_ERR_DTYPE for SV_F32, SV_ERR_SHAPE for ranges or sizes outside the rules above. */
 int sv_packed_head_bytes(const sv_model_cfg *cfg, int vocab_lo, int vocab_hi, size_t *bytes);
 int sv_pack_head(const sv_model_cfg *cfg, const void *g_final, const void *w_lm, int vocab_lo,

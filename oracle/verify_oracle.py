@@ -94,12 +94,14 @@ def silu(z: np.ndarray) -> np.ndarray:
 
 def verify_layer(x: np.ndarray, w: Dict[str, np.ndarray], k_prefix: np.ndarray,
                  v_prefix: np.ndarray, parent: Sequence[int], n_heads: int,
-                 eps: float, theta: float) -> Dict[str, np.ndarray]:
+                 eps: float, theta: float, store=None) -> Dict[str, np.ndarray]:
     """One Llama decoder layer over the T rows of a draft tree.
 
     x [T, H] residual stream; w: g1, wq, wk, wv, wo, g2, wg, wu, wd with the
     matrices stored [out, in]; k_prefix / v_prefix [n_heads, P, d] are used as
-    given (prefix keys are already rotated).  Returns the new residual stream
+    given (prefix keys are already rotated).  store: what the cache keeps of the tree's
+    own keys and values (a bf16 cache rounds them), float64 -> float64; None keeps them
+    as they are.  Returns the new residual stream
     "x", the attention output before the output projection "attn" [T, H] and
     the tree's own rotated keys / values "k_tree", "v_tree" [T, n_heads, d]."""
     T, H = x.shape
@@ -114,6 +116,8 @@ def verify_layer(x: np.ndarray, w: Dict[str, np.ndarray], k_prefix: np.ndarray,
     pos = P + depth
     q = rope(q, pos, theta)
     k = rope(k, pos, theta)
+    if store is not None:
+        k, v = store(k), store(v)
 
     attn = np.zeros((T, n_heads, d), dtype=np.float64)
     for h in range(n_heads):

@@ -62,7 +62,6 @@ static int weight_format(const sv_model_cfg& c) { return c.dtype == SV_BF16_W8 ?
 // The four products of a layer (bf16 models) and the head's, for one XCD count.
 struct LayerPlan {
   ProductPlan qkv, o, gu, down;
-  int ucap;                    // workgroups per XCD, the largest of the four
 };
 static LayerPlan plan_layer(const sv_model_cfg& c, int m_rows, int n_xcd) {
   const int H = c.hidden, D = c.n_heads * c.head_dim, F = c.mlp_dim, wf = weight_format(c);
@@ -71,8 +70,6 @@ static LayerPlan plan_layer(const sv_model_cfg& c, int m_rows, int n_xcd) {
   p.o = plan_product(m_rows, H, D, wf, n_xcd);
   p.gu = plan_product(m_rows, 2 * F, H, wf, n_xcd);
   p.down = plan_product(m_rows, H, F, wf, n_xcd);
-  p.ucap = 1;
-  for (const ProductPlan* q : {&p.qkv, &p.o, &p.gu, &p.down}) p.ucap = q->wg_x > p.ucap ? q->wg_x : p.ucap;
   return p;
 }
 
@@ -87,18 +84,16 @@ static WorkspaceLayout workspace_layout(const sv_model_cfg& c, int m_rows, int n
   if (c.dtype != SV_F32) {
     // sized for the largest split over the XCD counts a device can have
     const size_t mr = L.m_pad;
-    size_t wgs = 1, xch = 0, planes = H / 256;
+    size_t xch = 0, planes = H / 256;
     for (int n_xcd = 1; n_xcd <= kXcds; n_xcd *= 2) {
       const LayerPlan p = plan_layer(c, m_rows, n_xcd);
-      const size_t n = (size_t)n_xcd * p.ucap;
-      wgs = n > wgs ? n : wgs;
       for (const ProductPlan* q : {&p.qkv, &p.o, &p.gu, &p.down}) {
-        const size_t x = n * q->unit_stride * 16;
+        const size_t x = (size_t)n_xcd * q->wg_x * q->unit_stride * 16;
         xch = x > xch ? x : xch;
       }
       for (const ProductPlan* q : {&p.o, &p.down}) planes = (size_t)q->n_planes > planes ? q->n_planes : planes;
     }
-    L.counter_bytes = align_up((wgs * kCntStride + 64) * sizeof(int), kAlign);   // group counters + status word
+    L.counter_bytes = align_up((kMaxGroups * kCntStride + 64) * sizeof(int), kAlign);   // group counters + status word
     L.counters = o; o += L.counter_bytes;
     L.xs_x = o;     o = align_up(o + mr * H * 4, kAlign);
     L.xs_attn = o;  o = align_up(o + mr * D * 4, kAlign);
@@ -117,15 +112,12 @@ static WorkspaceLayout workspace_layout(const sv_model_cfg& c, int m_rows, int n
   L.head_logits = o; o = align_up(o + mp * (size_t)(n_scored > 0 ? n_scored : 0) * 4, kAlign);
   // (the regions above do not move with n_scored: a layer call finds them without knowing it)
   if (c.dtype != SV_F32 && n_scored > 0 && n_scored % kFragRows == 0) {
-    size_t wgs = 1, xch = 0;
+    size_t xch = 0;
     for (int n_xcd = 1; n_xcd <= kXcds; n_xcd *= 2) {
       const ProductPlan p = plan_product(m_rows, n_scored, (int)H, 0, n_xcd);
-      const size_t n = (size_t)n_xcd * p.wg_x, x = n * p.unit_stride * 16;
-      wgs = n > wgs ? n : wgs;
+      const size_t x = (size_t)n_xcd * p.wg_x * p.unit_stride * 16;
       xch = x > xch ? x : xch;
     }
-    L.head_cnt_bytes = align_up(wgs * kCntStride * sizeof(int), kAlign);
-    L.head_cnt = o; o += L.head_cnt_bytes;
     L.head_xs = o;  o = align_up(o + (size_t)L.m_pad * H * 4, kAlign);
     L.head_ssq = o; o = align_up(o + (size_t)L.m_pad * (H / 256) * 4, kAlign);
     L.head_xch = o; o = align_up(o + xch, kAlign);
@@ -244,7 +236,6 @@ static int verify_layer_bf16(const sv_model_cfg& c, const LayerCall& lc, const c
   scratch.xch = (f32x4_t*)(ws + wl.xch);
   scratch.group_cnt = (unsigned*)(ws + wl.counters);
   scratch.status = (int*)(ws + wl.counters + wl.counter_bytes) - 1;   // last word of the counter region
-  scratch.ucap = lc.plan.ucap;
   auto epilogue = [&](int K, size_t scale_off) {
     EpiArgs e;
     memset(&e, 0, sizeof(e));
@@ -397,9 +388,8 @@ static int head_packed(const sv_model_cfg& c, const char* packed, const float* x
   const ProductPlan p = plan_product(n_rows, n, H, 0, n_xcd);
   ProductScratch scratch;
   scratch.xch = (f32x4_t*)(ws + wl.head_xch);
-  scratch.group_cnt = (unsigned*)(ws + wl.head_cnt);
-  scratch.status = (int*)(ws + wl.counters + wl.counter_bytes) - 1;   // the layers' status word
-  scratch.ucap = p.wg_x;
+  scratch.group_cnt = (unsigned*)(ws + wl.counters);                  // the layers' counters and status word
+  scratch.status = (int*)(ws + wl.counters + wl.counter_bytes) - 1;
   EpiArgs e;
   memset(&e, 0, sizeof(e));
   e.M = n_rows; e.n_rb = wl.n_rb; e.m_pad = wl.m_pad; e.K = H; e.eps = c.rms_eps;
@@ -555,10 +545,6 @@ int sv_workspace_init(const sv_model_cfg* cfg, int B, int T, int n_scored, void*
   if (n > 0)
     zero_ints<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
         (int*)((char*)workspace + wl.counters), n);
-  const size_t nh = wl.head_cnt_bytes / sizeof(int);
-  if (nh > 0)
-    zero_ints<<<(unsigned)((nh + 255) / 256), 256, 0, (hipStream_t)stream>>>(
-        (int*)((char*)workspace + wl.head_cnt), nh);
   return launch_status();
 }
 

@@ -18,6 +18,9 @@ constexpr int kFragRows = 32;    // weight rows per fragment and per tile (MFMA 
 constexpr int kFragK = 16;       // k-values per fragment (MFMA K)
 constexpr int kXcds = 8, kCusPerXcd = 32;
 constexpr int kCntStride = 32;     // 32-bit words per group's counters: a 128-byte line of its own
+// Groups of workgroups that share an output in one launch, at most, over all XCDs of a device: a product with
+// more is not split along K.  (8192 x 28672 at 18464 rows asks for 3712; up to 1024 rows the largest of many shapes asks for 608.)
+constexpr int kMaxGroups = 4096;
 
 enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_OUT = 3 };
 enum { PACK_PLAIN = 0, PACK_PAIR16_HEAD = 1, PACK_PAIR16_GU = 2 };

@@ -35,9 +35,9 @@ struct MidArgs {
   // scratch of the sums that cross workgroups, addressed by XCD: no address is ever written through one
   // L2 and read through another
   f32x4_t* xch;              // [n_xcd][ucap][unit_stride]
-  unsigned* group_cnt;       // [n_xcd][ucap][kCntStride], zero between launches
+  unsigned* group_cnt;       // [n_xcd][gcap][kCntStride], zero between launches
   int* status;
-  int ucap, unit_stride;
+  int ucap, unit_stride, gcap;
   EpiArgs e;
 };
 
@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   // ---- output ----
   const int h = lane >> 5;
   const size_t unit = (size_t)xcd * a.ucap + (size_t)gm * S;       // first workgroup of the group
-  const auto gcnt = a.group_cnt + ((size_t)xcd * a.ucap + gm) * kCntStride;
+  const auto gcnt = a.group_cnt + ((size_t)xcd * a.gcap + gm) * kCntStride;
   f32x4_t* const stage = reinterpret_cast<f32x4_t*>(&lds[0][0]) + lane;
   auto item_quad = [&](int i, int qi) -> f32x4_t {
     const int q = PAIR ? (i & 1) + 2 * qi : 2 * (i & 1) + qi;

@@ -48,9 +48,9 @@ struct SkinnyArgs {
   // scratch of the sums that cross workgroups: one region per workgroup, addressed by XCD, so that no
   // address is ever written through one L2 and read through another
   f32x4_t* xch;              // [n_xcd][ucap][unit_stride]
-  unsigned* group_cnt;       // [n_xcd][ucap][kCntStride], zero between launches
+  unsigned* group_cnt;       // [n_xcd][gcap][kCntStride], zero between launches
   int* status;
-  int ucap, unit_stride;
+  int ucap, unit_stride, gcap;
   EpiArgs e;
 };
 
@@ -251,7 +251,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
       for (int qi = 0; qi < QI; ++qi) dst[qi * 64] = mine[j * QI + qi];
     }
   }
-  const auto gcnt = a.group_cnt + ((size_t)xcd * a.ucap + ug) * kCntStride;
+  const auto gcnt = a.group_cnt + ((size_t)xcd * a.gcap + ug) * kCntStride;
   if (S > 1) {
     __builtin_amdgcn_s_waitcnt(0);         // this wave's sums are in the L2
     __syncthreads();

@@ -93,12 +93,15 @@ struct WorkspaceLayout {
   size_t q, attn, total;         // float32, both storage types
   // float32 models
   size_t act;
-  // bf16 models: counters of the workgroups that share an output (+ status word), activation fragments of
-  // the residual stream, the attention output and the SwiGLU output, partial row sums of x^2, sums that
-  // cross workgroups, partial results of a split tree attention
-  size_t counters, counter_bytes, xs_x, xs_attn, xs_act, ssq, xch, att_part;
+  // bf16 models: counters of the workgroups that share an output (+ status word).  They alone outlive a call
+  // and have to be zero when one begins, so their place and extent are the same for every row count, number of
+  // scored rows and model: one workspace serves calls of any sizes that fit it, layers and heads.
+  size_t counters, counter_bytes;
+  // activation fragments of the residual stream, the attention output and the SwiGLU output, partial row sums
+  // of x^2, sums that cross workgroups, partial results of a split tree attention
+  size_t xs_x, xs_attn, xs_act, ssq, xch, att_part;
   // heads: logits; packed (bf16 models, scored rows a multiple of 32)
-  size_t head_logits, head_cnt, head_cnt_bytes, head_xs, head_ssq, head_xch;
+  size_t head_logits, head_xs, head_ssq, head_xch;
   int m_pad, n_rb;               // rows as laid out, row blocks of 32
 };
 

@@ -56,6 +56,7 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
         p.m_tiles = ceil_div(n_rb, rb);
         p.gpx = ceil_div(tiles_x, 4 * nt);
         p.wg_x = (p.gpx * p.m_tiles) << lgS;
+        if (lgS > 0 && p.gpx * p.m_tiles > kMaxGroups / n_xcd) continue;
         const int rounds = ceil_div(p.wg_x, kCusPerXcd);
         const double steps = (double)nks / (1 << lgS), kib = 16.0 * rb * nt * ((1 << lgS) - 1) / (1 << lgS);
         double loop = rounds * steps * rb * (0.042 * nt + 0.020);
@@ -106,7 +107,8 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
     a.tq = tiles / groups; a.trem = tiles % groups;
     a.cq = chunks >> p.lgS; a.crem = chunks & ((1 << p.lgS) - 1);
     a.planes = p.planes;
-    a.xch = s.xch; a.group_cnt = s.group_cnt; a.status = s.status; a.ucap = s.ucap; a.unit_stride = p.unit_stride;
+    a.xch = s.xch; a.group_cnt = s.group_cnt; a.status = s.status; a.ucap = p.wg_x; a.unit_stride = p.unit_stride;
+    a.gcap = kMaxGroups / n_xcd;
     a.e = e;
     auto* launch = epi == EPI_QKV ? launch_mid_qkv : (epi == EPI_RESID ? launch_mid_resid : (epi == EPI_SWIGLU ? launch_mid_swiglu : launch_mid_out));
     launch(a, p.rb, p.nt, wf, grid, st);
@@ -124,7 +126,8 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
     const int pieces = halves ? 2 * tiles : tiles;
     a.tq = pieces / groups; a.trem = pieces % groups;
     a.uq = units / waves; a.urem = units % waves;
-    a.xch = s.xch; a.group_cnt = s.group_cnt; a.status = s.status; a.ucap = s.ucap; a.unit_stride = p.unit_stride;
+    a.xch = s.xch; a.group_cnt = s.group_cnt; a.status = s.status; a.ucap = p.wg_x; a.unit_stride = p.unit_stride;
+    a.gcap = kMaxGroups / n_xcd;
     a.e = e;
     auto* launch = epi == EPI_QKV ? launch_skinny_qkv : (epi == EPI_RESID ? launch_skinny_resid : (epi == EPI_SWIGLU ? launch_skinny_swiglu : launch_skinny_out));
     launch(a, p.rb, p.nt, wf, grid, st);

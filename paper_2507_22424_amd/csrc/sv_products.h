@@ -24,7 +24,6 @@ struct ProductScratch {
   f32x4_t* xch;
   unsigned* group_cnt;
   int* status;
-  int ucap;                  // workgroups per XCD the scratch is laid out for
 };
 
 // epi: EPI_*; wf: weight format (0 bf16, 1 E4M3, 2 int4; EPI_OUT: 0 only)

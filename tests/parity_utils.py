@@ -40,6 +40,11 @@ def f64(t):
     return t.to(torch.float64).numpy()
 
 
+def bf16_store(a):
+    """What a bf16 cache keeps of float64 values."""
+    return f64(torch.from_numpy(a).to(torch.float32).to(torch.bfloat16))
+
+
 def row_rel_err(gpu, ref):
     """Per row: max |gpu - ref| / max |ref|.  A NaN or infinity must sit in the same element on
     both sides (asserted); such elements are then left out of the row's maximum."""

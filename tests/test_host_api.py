@@ -86,6 +86,26 @@ def test_sizes_and_cfg_checks():
     assert e.value.status == -2
 
 
+MODELS = [(4096, 32, 128, 11008, 32000), (512, 4, 128, 1536, 1024), (5120, 40, 128, 13824, 32000), (256, 2, 128, 256, 512)]
+ROW_COUNTS = [(1, 1), (1, 26), (1, 32), (1, 33), (1, 60), (1, 64), (1, 65), (1, 128), (3, 50), (2, 96), (4, 60), (8, 65),
+              (9, 64), (10, 64), (12, 64), (16, 50), (16, 60), (256, 128)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_w8", "bf16_w4"])
+@pytest.mark.parametrize("model", MODELS)
+def test_arrival_counters_have_one_place_for_every_size(model, dtype):
+    """The counters are the only part of a workspace that outlives a call: a workspace prepared once serves
+    calls of other row counts, and heads, only if counters and status word never move.  They fill the start of
+    the workspace up to the status word; everything a call overwrites lies behind."""
+    cfg = sv.model_cfg(dtype, *model)
+    ends = {sv.sv_workspace_region(cfg, B, T, n, sv.SV_WS_STATUS) for B, T in ROW_COUNTS for n in (0, 32, 256, model[4])}
+    assert len(ends) == 1
+    end = sum(ends.pop())
+    for B, T in ROW_COUNTS:
+        for n in (0, 256):
+            assert min(sv.sv_workspace_region(cfg, B, T, n, w)[0] for w in (sv.SV_WS_ATTN_OUT, sv.SV_WS_Q)) >= end
+
+
 def test_null_and_range_arguments_fail_before_any_launch():
     lib = sv.lib()
     c1 = sv.model_cfg("f32", 256, 4, 64, 688, 512)
