@@ -159,7 +159,8 @@ int sv_pack_layer_w4(const sv_model_cfg *cfg, const sv_layer_weights *raw,
                      void *stream);
 
 /* Host-only.  Bytes of device scratch that sv_verify_layer / sv_action_head_argmax need for
- * B episodes of T nodes and up to n_scored scored vocabulary rows -> *bytes. */
+ * B episodes of T nodes and up to n_scored scored vocabulary rows -> *bytes.  Never less than for
+ * fewer nodes: a workspace of that size serves calls of every row count up to B * T. */
 int sv_workspace_bytes(const sv_model_cfg *cfg, int B, int T, int n_scored, size_t *bytes);
 
 /* Prepares a freshly allocated (or otherwise dirty) workspace: zeroes the inter-workgroup

@@ -522,25 +522,38 @@ int sv_pack_layer_w4(const sv_model_cfg* cfg, const sv_layer_weights* raw,
   return pack_layer_codes(cfg, raw, sc, packed_v, packed_bytes, stream, SV_BF16_W4);
 }
 
-int sv_workspace_bytes(const sv_model_cfg* cfg, int B, int T, int n_scored, size_t* bytes) {
-  if (!bytes) return SV_ERR_NULL;
+static int check_workspace_sizes(const sv_model_cfg* cfg, int B, int T, int n_scored) {
   const int rc = check_cfg(cfg);
   if (rc != SV_OK) return rc;
   if (B < 1 || T < 1 || T > SV_MAX_TREE_NODES || n_scored < 0 || n_scored > cfg->vocab ||
       (long long)B * T > (1 << 15))
     return SV_ERR_SHAPE;
-  *bytes = workspace_layout(*cfg, B * T, n_scored).total;
+  return SV_OK;
+}
+
+// What a call needs depends on how its products are split, and some row counts need more than larger ones
+// (7B: 320 rows 144 MB, 384 rows 135).  The bytes handed out are therefore the most that any row count up to
+// B * T needs; a call itself asks for its own only.
+int sv_workspace_bytes(const sv_model_cfg* cfg, int B, int T, int n_scored, size_t* bytes) {
+  if (!bytes) return SV_ERR_NULL;
+  const int rc = check_workspace_sizes(cfg, B, T, n_scored);
+  if (rc != SV_OK) return rc;
+  size_t most = workspace_layout(*cfg, B * T, n_scored).total;
+  for (int rows = 32; cfg->dtype != SV_F32 && rows < B * T; rows += 32) {      // (plans follow from the 32-row blocks)
+    const size_t n = workspace_layout(*cfg, rows, n_scored).total;
+    most = n > most ? n : most;
+  }
+  *bytes = most;
   return SV_OK;
 }
 
 int sv_workspace_init(const sv_model_cfg* cfg, int B, int T, int n_scored, void* workspace,
                       size_t ws_bytes, void* stream) {
-  size_t total;
-  const int rc = sv_workspace_bytes(cfg, B, T, n_scored, &total);
+  const int rc = check_workspace_sizes(cfg, B, T, n_scored);
   if (rc != SV_OK) return rc;
   if (!workspace) return SV_ERR_NULL;
-  if (((uintptr_t)workspace % kAlign) || ws_bytes < total) return SV_ERR_WORKSPACE;
   const WorkspaceLayout wl = workspace_layout(*cfg, B * T, n_scored);
+  if (((uintptr_t)workspace % kAlign) || ws_bytes < wl.total) return SV_ERR_WORKSPACE;
   const size_t n = wl.counter_bytes / sizeof(int);
   if (n > 0)
     zero_ints<<<(unsigned)((n + 255) / 256), 256, 0, (hipStream_t)stream>>>(
@@ -551,8 +564,7 @@ int sv_workspace_init(const sv_model_cfg* cfg, int B, int T, int n_scored, void*
 int sv_workspace_region(const sv_model_cfg* cfg, int B, int T, int n_scored, int which,
                         size_t* offset, size_t* bytes) {
   if (!offset || !bytes) return SV_ERR_NULL;
-  size_t total;
-  const int rc = sv_workspace_bytes(cfg, B, T, n_scored, &total);
+  const int rc = check_workspace_sizes(cfg, B, T, n_scored);
   if (rc != SV_OK) return rc;
   const WorkspaceLayout wl = workspace_layout(*cfg, B * T, n_scored);
   const size_t D = (size_t)cfg->n_heads * cfg->head_dim, M = (size_t)B * T;

@@ -106,6 +106,18 @@ def test_arrival_counters_have_one_place_for_every_size(model, dtype):
             assert min(sv.sv_workspace_region(cfg, B, T, n, w)[0] for w in (sv.SV_WS_ATTN_OUT, sv.SV_WS_Q)) >= end
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_w8", "bf16_w4", "f32"])
+@pytest.mark.parametrize("model", MODELS)
+def test_a_workspace_for_many_rows_holds_that_of_fewer(model, dtype):
+    """Bytes never fall as the rows grow, layers alone or with a head: a workspace sized for the largest call is
+    large enough for every other."""
+    cfg = sv.model_cfg(dtype, *model)
+    for n in (0, 256, 320, model[4]):
+        sizes = [sv.sv_workspace_bytes(cfg, 1, T, n) for T in range(1, 129)]
+        sizes += [sv.sv_workspace_bytes(cfg, B, 16, n) for B in range(9, 140, 1)]
+        assert sizes == sorted(sizes), n
+
+
 def test_null_and_range_arguments_fail_before_any_launch():
     lib = sv.lib()
     c1 = sv.model_cfg("f32", 256, 4, 64, 688, 512)
