@@ -138,10 +138,16 @@ def _dev(t: Optional[torch.Tensor], dtype=None, name="tensor") -> int:
     return t.data_ptr()
 
 
+# The handle of a device's current stream.  Building a Stream object costs as much as the rest of a call, so
+# torch's own short cut is taken where this torch has it (it is not part of its public interface).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        # (the raw handle: building a Stream object costs as much as the rest of a call)
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

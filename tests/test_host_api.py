@@ -271,6 +271,19 @@ def test_stream_read_checks_its_arguments_before_any_launch():
     assert lib.sv_stream_read(a, 4096, C.c_void_p(4104), None) == -2
 
 
+def test_calls_without_a_stream_take_the_current_one_with_or_without_the_short_cut(monkeypatch):
+    """torch's short cut to the raw handle is private: a torch without it gets the public way."""
+    import types
+
+    monkeypatch.setattr(sv.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(sv.torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(sv, "_raw_stream", lambda device: 40 + device)
+    assert sv._stream(None) == 43
+    monkeypatch.setattr(sv, "_raw_stream", None)
+    assert sv._stream(None) == 77
+    assert sv._stream(types.SimpleNamespace(cuda_stream=5)) == 5 and sv._stream(9) == 9
+
+
 def test_bench_refuses_more_than_one_gpu_with_a_message():
     """Nothing here uses a second GPU: `bench.py --gpus N` with N > 1 exits with a message (before
     anything touches a GPU)."""
