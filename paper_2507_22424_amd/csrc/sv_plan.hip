@@ -78,21 +78,13 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
 // Rows the kernels split at.  Up to 128 gemm_skinny, unless its groups of few tiles would make more than one
 // round of the chip (us, o / down / qkv / gate+up on the 7B shapes: 70 rows 18.1 / 34.3 / 36.8 / 54.8
 // against gemm_mid's 19.6 / 34.0 / 40.7 / 60.2; 128 rows 20.5 / 39.3 / 45.6 / 62.5 against 22.6 / 40.4 /
-// 45.4 / 66.7; 150 rows 24.1 / 45.5 / 54.7 / 100 against 26.6 / 46.0 / 54.1 / 79.2).  A plan follows from
-// its five sizes alone; the last few of a thread are kept, a step asks for the same ones again and again.
+// 45.4 / 66.7; 150 rows 24.1 / 45.5 / 54.7 / 100 against 26.6 / 46.0 / 54.1 / 79.2).
 ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd) {
   if (M <= kSkinnyMaxRows) {
     const ProductPlan p = plan_skinny(M, N, K, n_xcd);
     if (M <= 64 || p.wg_x <= kCusPerXcd) return p;
   }
-  struct Entry {
-    int M, N, K, wf, n_xcd;
-    ProductPlan plan;
-  };
-  static thread_local Entry memo[64];
-  Entry& e = memo[((unsigned)M * 31u + (unsigned)N * 17u + (unsigned)K * 7u + (unsigned)n_xcd * 3u + (unsigned)wf) % 64u];
-  if (e.M != M || e.N != N || e.K != K || e.wf != wf || e.n_xcd != n_xcd) e = {M, N, K, wf, n_xcd, plan_mid(M, N, K, wf, n_xcd)};
-  return e.plan;
+  return plan_mid(M, N, K, wf, n_xcd);
 }
 
 void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint4* Xs, const uint4* Wp, int N, int K,
