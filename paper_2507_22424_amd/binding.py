@@ -25,11 +25,12 @@ SV_WS_ATTN_OUT, SV_WS_Q, SV_WS_STATUS = 0, 1, 2
 EXPORTS = ("sv_version", "sv_strerror", "sv_tree_build_masks", "sv_packed_layer_bytes",
            "sv_pack_layer", "sv_pack_layer_w8", "sv_pack_layer_w4", "sv_workspace_bytes", "sv_workspace_init", "sv_workspace_region",
            "sv_verify_layer",
-           "sv_verify_layer_timed", "sv_verify_stack",
+           "sv_verify_layer_timed", "sv_verify_stack", "sv_product_plan",
            "sv_action_head_argmax", "sv_action_head_argmax_noalloc", "sv_packed_head_bytes", "sv_pack_head",
            "sv_action_head_argmax_packed", "sv_stream_read", "sv_relaxed_accept",
            "sv_commit_path", "sv_advance_prefix", "sv_tree_build_device")
 SV_N_TIMING_EVENTS = 9
+SV_PLAN_QKV, SV_PLAN_OUT, SV_PLAN_GATE_UP, SV_PLAN_DOWN, SV_PLAN_HEAD = range(5)
 
 
 class SvError(RuntimeError):
@@ -89,6 +90,7 @@ def lib() -> C.CDLL:
                                         C.c_size_t, C.c_void_p]
         l.sv_workspace_region.argtypes = [C.POINTER(ModelCfg), C.c_int, C.c_int, C.c_int, C.c_int,
                                           C.POINTER(C.c_size_t), C.POINTER(C.c_size_t)]
+        l.sv_product_plan.argtypes = [C.POINTER(ModelCfg), C.c_int, C.c_int, C.c_int, C.c_int, C.c_void_p]
         l.sv_verify_layer.argtypes = [C.POINTER(ModelCfg), C.c_void_p, C.c_void_p,
                                       C.POINTER(KvView), C.POINTER(Tree), C.c_int, C.c_void_p,
                                       C.c_size_t, C.c_void_p]
@@ -243,6 +245,13 @@ def sv_workspace_region(cfg: ModelCfg, B: int, T: int, n_scored: int, which: int
     _check(lib().sv_workspace_region(C.byref(cfg), B, T, n_scored, which, C.byref(off),
                                      C.byref(nb)), "sv_workspace_region")
     return off.value, nb.value
+
+
+def sv_product_plan(cfg: ModelCfg, n_rows: int, which: int, n_scored: int = 0, n_xcd: int = 8) -> Tuple[int, ...]:
+    """(kernel, row blocks, weight tiles, K slices, column groups per XCD, blocks of rows): see the header."""
+    plan = (C.c_int32 * 6)()
+    _check(lib().sv_product_plan(C.byref(cfg), n_rows, which, n_scored, n_xcd, plan), "sv_product_plan")
+    return tuple(plan)
 
 
 def sv_verify_layer(cfg: ModelCfg, packed: torch.Tensor, x: torch.Tensor, kv: KvView,

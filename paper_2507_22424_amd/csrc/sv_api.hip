@@ -710,6 +710,26 @@ int sv_action_head_argmax_noalloc(const sv_model_cfg* cfg, const void* g_final, 
                         vocab_hi, out_token, out_logits, logits, (hipStream_t)stream);
 }
 
+int sv_product_plan(const sv_model_cfg* cfg, int n_rows, int which, int n_scored, int n_xcd, int32_t* plan) {
+  if (!plan) return SV_ERR_NULL;
+  const int rc = check_cfg(cfg);
+  if (rc != SV_OK) return rc;
+  if (cfg->dtype == SV_F32) return SV_ERR_DTYPE;
+  if (n_rows < 1 || n_rows > (1 << 15) || which < SV_PLAN_QKV || which > SV_PLAN_HEAD || n_xcd < 1 || n_xcd > kXcds)
+    return SV_ERR_SHAPE;
+  if (which == SV_PLAN_HEAD && (n_scored < 1 || n_scored > cfg->vocab || n_scored % kFragRows)) return SV_ERR_SHAPE;
+  ProductPlan p;
+  if (which == SV_PLAN_HEAD) {
+    p = plan_product(n_rows, n_scored, cfg->hidden, 0, n_xcd);
+  } else {
+    const LayerPlan l = plan_layer(*cfg, n_rows, n_xcd);
+    p = which == SV_PLAN_QKV ? l.qkv : (which == SV_PLAN_OUT ? l.o : (which == SV_PLAN_GATE_UP ? l.gu : l.down));
+  }
+  const int32_t v[6] = {p.mid ? 1 : 0, p.rb, p.nt, 1 << p.lgS, p.gpx, p.m_tiles};
+  memcpy(plan, v, sizeof(v));
+  return SV_OK;
+}
+
 int sv_packed_head_bytes(const sv_model_cfg* cfg, int vocab_lo, int vocab_hi, size_t* bytes) {
   if (!bytes) return SV_ERR_NULL;
   const int rc = check_packed_head(cfg, vocab_lo, vocab_hi);

@@ -78,12 +78,13 @@ class SideBySide:
     """Outputs of one configuration from both sides."""
 
     def __init__(self, cfg, n_layers=None, full_vocab=False, per_layer=True, tag="",
-                 hidden_transform=None, finite_rows=None, stack_tol=2e-3):
+                 hidden_transform=None, finite_rows=None, stack_tol=2e-3, store=None):
         """hidden_transform(b, rows float32 [T, H]) -> rows: applied to the seeded input rows of
         episode b before either side sees them.  finite_rows: only the first `finite_rows` node
         rows enter the error figures (a test that plants a NaN in a later episode checks those
         rows itself); by default every row does, and a NaN or infinity anywhere must then sit in
-        the same element on both sides."""
+        the same element on both sides.  store: what the oracle's cache keeps of the tree's keys
+        and values (see verify_oracle.verify_layer; bf16_store for bf16 models)."""
         self.finite_rows = finite_rows
         L = cfg.n_layers if n_layers is None else n_layers
         self.cfg = cfg = cfg.scaled(n_layers=L)
@@ -124,7 +125,7 @@ class SideBySide:
                 kp, vp = wl.prefix_kv(cfg, b, l, P)
                 self.gpu.load_prefix(l, b, kp, vp)
                 out = vo.verify_layer(x_ref[b], w64, f64(kp), f64(vp), self.parents[b],
-                                      cfg.n_heads, cfg.rms_eps, cfg.rope_theta)
+                                      cfg.n_heads, cfg.rms_eps, cfg.rope_theta, store)
                 x_ref[b] = out["x"]
                 ref_attn.append(out["attn"])
             if per_layer:

@@ -1,0 +1,50 @@
+"""Every form in which the planner splits a product of the 7B shape - kernel, row blocks, weight tiles, K slices,
+weight format - is held to the oracle by a GPU test: the listed sizes reach all forms of the declared range."""
+import pytest
+
+from paper_2507_22424_amd import binding as sv
+from perf import cases
+from test_gpu_products import WIDE_ELSEWHERE, WIDE_HEAD, WIDE_LAYERS
+
+LAYER = (sv.SV_PLAN_QKV, sv.SV_PLAN_OUT, sv.SV_PLAN_GATE_UP, sv.SV_PLAN_DOWN)
+
+
+def _cfg(dtype):
+    return sv.model_cfg(dtype, *cases.MODELS["7b"])
+
+
+def _forms(dtype, rows):
+    return {(which,) + sv.sv_product_plan(_cfg(dtype), rows, which)[:4] for which in LAYER}
+
+
+def _head_form(rows, n):
+    return sv.sv_product_plan(_cfg("bf16"), rows, sv.SV_PLAN_HEAD, n)[:4]
+
+
+@pytest.mark.parametrize("dtype,most", [("bf16", 960), ("bf16_w8", 240), ("bf16_w4", 240)])
+def test_every_form_of_a_layers_products_has_a_test(dtype, most):
+    tested = set().union(*(_forms(dtype, M) for M in [B * T for B, T in WIDE_LAYERS[dtype]] + WIDE_ELSEWHERE[dtype]))
+    missing = {M: _forms(dtype, M) - tested for M in range(1, most + 1)}
+    assert not {M: f for M, f in missing.items() if f}
+
+
+def test_every_form_of_the_heads_product_has_a_test():
+    layers = [B * T for B, T in WIDE_LAYERS["bf16"]] + WIDE_ELSEWHERE["bf16"]      # (their logits: 256 action rows)
+    assert {_head_form(M, 256) for M in range(1, 961)} <= {_head_form(M, 256) for M in layers}
+    assert {_head_form(M, 32000) for M in range(1, 961)} <= {_head_form(M, 32000) for M in WIDE_HEAD}
+
+
+def test_the_timed_cases_lie_in_the_range_that_is_tested():
+    for case in cases.listed():
+        rows = case["episodes"] * case["nodes"]
+        assert case["model"] != "7b" or rows <= (960 if case["dtype"] == "bf16" else 240), case["name"]
+
+
+def test_plan_queries_check_their_arguments():
+    bf, f32 = _cfg("bf16"), sv.model_cfg("f32", 256, 4, 64, 688, 512)
+    assert sv.lib().sv_product_plan(bf, 60, 0, 0, 8, None) == sv.SV_ERR_NULL
+    for args, status in (((f32, 60, 0), sv.SV_ERR_DTYPE), ((bf, 0, 0), sv.SV_ERR_SHAPE), ((bf, 1 << 16, 0), sv.SV_ERR_SHAPE),
+                         ((bf, 60, 5), sv.SV_ERR_SHAPE), ((bf, 60, 4, 100), sv.SV_ERR_SHAPE), ((bf, 60, 0, 0, 9), sv.SV_ERR_SHAPE)):
+        with pytest.raises(sv.SvError) as e:
+            sv.sv_product_plan(*args)
+        assert e.value.status == status, args
