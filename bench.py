@@ -297,16 +297,19 @@ def main():
     gemm_ms_raw = sum(raw_ms[k] for k in gemm_bytes)
     gemm_gbs = sum(gemm_bytes.values()) * L / (gemm_ms_raw * 1e-3) / 1e9
     # matrix-core work as issued: every product is done on the hi and on the lo half of the
-    # float32 activations (2 x the algorithmic flops), on rows padded to blocks of 32
-    m_issue = -(-M // 32) * 32
-    issued_flops = 2.0 * sum(gemm_flops.values()) * L * m_issue / M
+    # float32 activations (2 x the algorithmic flops), on the rows that its plan multiplies
+    n_xcd = max(1, min(8, torch.cuda.get_device_properties(0).multi_processor_count // 32))
+    plans = {k: sv.sv_product_plan(vp.cfg, M, which, n_xcd=n_xcd)
+             for k, which in (("qkv", sv.SV_PLAN_QKV), ("o", sv.SV_PLAN_OUT), ("gate_up", sv.SV_PLAN_GATE_UP), ("down", sv.SV_PLAN_DOWN))}
+    rows_issued = {k: 32 * p[1] * p[5] for k, p in plans.items()}
+    issued_flops = 2.0 * L * sum(gemm_flops[k] * rows_issued[k] / M for k in plans)
     mfma_tflops = issued_flops / (gemm_ms_raw * 1e-3) / 1e12
     kv_bytes = sum(2 * cfg.n_heads * (int(p) + T) * cfg.head_dim * 2 for p in prefix_len)   # all episodes, one layer
     weights_total = sum(gemm_bytes.values()) * L
     step_bytes = weights_total + kv_bytes * L + cfg.n_bins * H * 2 + 2 * cfg.n_heads * M * cfg.head_dim * 2 * L
     step_flops = sum(gemm_flops.values()) * L
 
-    mfma_bound = M > 128                 # many rows: the products are bound by the matrix cores
+    mfma_bound = plans["gate_up"][0] == 1    # gemm_mid: the products are bound by the matrix cores
     key = (args.config, args.weights)
     if mfma_bound:
         roofline = {"bound": "mfma", "kernel": "gemm_mid (4 launches per layer: q/k/v, o, gate/up, down)",
@@ -314,7 +317,8 @@ def main():
                     "frac": mfma_tflops / MFMA_PEAK_TFLOPS,
                     "traffic": TRAFFIC_BYTES_PER_LAUNCH.get(key),
                     "traffic_source": TRAFFIC_SOURCE.get(key),
-                    "flops_counted": "matrix-core flops as issued: hi and lo halves of the activations, rows padded to blocks of 32",
+                    "flops_counted": "matrix-core flops as issued: hi and lo halves of the activations, rows as the plans pad them",
+                    "rows_issued": rows_issued,
                     "algorithmic_frac": step_flops / (gemm_ms_raw * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS,
                     "flops_per_launch_avg": issued_flops / (4 * L),
                     "avg_launch_us": gemm_ms_raw * 1e3 / (4 * L)}
@@ -346,7 +350,7 @@ def main():
                    "launch": "HIP graph replay" if graph is not None else "host launches"},
         "step_hbm_frac": step_bytes / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS,
         "step_algorithmic_bytes": step_bytes,
-        "step_mfma_frac": 2.0 * step_flops * m_issue / M / (ms_per_step * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS,
+        "step_mfma_frac": issued_flops / (ms_per_step * 1e-3) / 1e12 / MFMA_PEAK_TFLOPS,
         "mfma_frac": mfma_tflops / MFMA_PEAK_TFLOPS,
         "accepted_len": accepted, "accepted_len_by_r": accepted_by_r,
         "layers_ms_per_step": layers_ms,
