@@ -77,7 +77,7 @@ static WorkspaceLayout workspace_layout(const sv_model_cfg& c, int m_rows, int n
   const size_t H = c.hidden, D = (size_t)c.n_heads * c.head_dim, F = c.mlp_dim;
   WorkspaceLayout L;
   memset(&L, 0, sizeof(L));
-  const size_t mp = (size_t)ceil_div(m_rows, kMTile) * kMTile;
+  const size_t mp = (size_t)ceil_div(m_rows, kRowPad) * kRowPad;
   L.n_rb = ceil_div(m_rows, 32);
   L.m_pad = c.dtype == SV_F32 ? (int)mp : L.n_rb * 32;
   size_t o = 0;
@@ -335,7 +335,8 @@ static void launch_argmax(const float* logits, int n_rows, int n, int lo, int32_
   else argmax_rows_wide<256><<<n_rows, 256, 0, st>>>(logits, n, lo, out_token, copy);
 }
 
-// The head on raw rows: logits (to `logits_ws`, [n_rows, hi - lo], if the caller wants none), then the row argmax.
+// The head on raw rows: logits (to `logits_ws`, [n_rows, hi - lo], if the caller wants none), then the row
+// argmax.
 template <typename T>
 static int head_t(const sv_model_cfg& c, const T* g_final, const T* w_lm, const float* x,
                   int n_rows, int lo, int hi, int32_t* out_token, float* out_logits, float* logits_ws, hipStream_t st) {
@@ -349,9 +350,10 @@ static int head_t(const sv_model_cfg& c, const T* g_final, const T* w_lm, const 
   return launch_status();
 }
 
-// Scratch of sv_action_head_argmax_noalloc: the logits of one call, in device memory that belongs to the library image (one copy per GPU, for the life of the
-// process).  Host code never uses the array's name as an address: scratch_address() asks the
-// runtime where the current device's copy lives, once per device.
+// Scratch of sv_action_head_argmax_noalloc: the logits of one call, in device memory that belongs to the
+// library image (one copy per GPU, for the life of the process).  Host code never uses the array's name as an
+// address: scratch_address() asks the runtime where the current device's copy lives, once per device.
+// The logits do not grow with `hidden`; its limit is part of the documented call (what was refused stays so).
 constexpr int kNoallocMaxRows = 64, kNoallocMaxScored = 256, kNoallocMaxHidden = 8192;
 constexpr size_t kNoallocScratchBytes = (size_t)kNoallocMaxRows * kNoallocMaxScored * 4;
 static __device__ __align__(256) unsigned char scratch[kNoallocScratchBytes];

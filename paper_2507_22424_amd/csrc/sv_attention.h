@@ -45,11 +45,6 @@ __device__ inline uint4 ld_global_u4(const void* p) {
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-__device__ inline bf16x8_t pack8_hi(const float* v) {
-  const uint4 u = make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
-                             pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
-  return __builtin_bit_cast(bf16x8_t, u);
-}
 __device__ inline void split8(const float* v, bf16x8_t& hi, bf16x8_t& lo) {
   uint4 h, l;
   h.x = pack_bf16x2(v[0], v[1]); h.y = pack_bf16x2(v[2], v[3]);

@@ -5,9 +5,10 @@
 // large bf16 product of the vendor's library sustains on the same card (1.16).  What is left to lose is
 // around the loop and in work on rows that do not exist (7B layer of 150 rows: 305 us for the four products
 // and their helper launches before, 207 now; 960 rows: 775 and 775), hence:
-//   * blocks of RB = 3, 4 or 5 row blocks of 32 rows x 4 waves x NT weight tiles; the host picks RB so that
-//     few padded rows are multiplied (150 rows: 160, not 256) and RB, NT, S so that the workgroups fill the
-//     chip in whole rounds;
+//   * blocks of RB = 3, 4 or 5 row blocks of 32 rows x 4 waves x NT weight tiles; the host weighs rows that
+//     are only padding against whole rounds of the chip (150 rows: 160 are multiplied in the down projection,
+//     192 in the other three: two blocks of 3 fill the chip with half the K slices, and so less exchange, than
+//     one of 5 would need);
 //   * a weight tile belongs to one wave: its fragments go from memory straight into operand registers,
 //     through a ring of D chunks.  The activations of a chunk (two k-steps; four with 4-bit weights) are
 //     fetched once per workgroup, each wave loading a quarter of the fragments into registers and writing
@@ -32,8 +33,7 @@ struct MidArgs {
   int tq, trem;              // tiles per column group, groups with one more
   int cq, crem;              // chunks per K slice, slices with one more
   int planes;                // EPI_RESID: row-sum planes per column group
-  // scratch of the sums that cross workgroups, addressed by XCD: no address is ever written through one
-  // L2 and read through another
+  // scratch of the sums that cross workgroups, by XCD: see gemm_skinny
   f32x4_t* xch;              // [n_xcd][ucap][unit_stride]
   unsigned* group_cnt;       // [n_xcd][gcap][kCntStride], zero between launches
   int* status;

@@ -45,8 +45,9 @@ struct SkinnyArgs {
   // its rows 8h .. 8h+7 and 16+8h .. 16+8h+7, the quads q with q % 2 == h
   int tq, trem, lgH;
   int uq, urem;              // weight loads (units of 16, 32 or 64 k-values) per wave, waves with one more
-  // scratch of the sums that cross workgroups: one region per workgroup, addressed by XCD, so that no
-  // address is ever written through one L2 and read through another
+  // scratch of the sums that cross workgroups: one region per workgroup, and within a launch every region (and
+  // for good every counter) belongs to one XCD, so that what one workgroup writes another reads through the same
+  // L2.  From launch to launch a region may pass to another XCD: a launch reads only what it has written itself.
   f32x4_t* xch;              // [n_xcd][ucap][unit_stride]
   unsigned* group_cnt;       // [n_xcd][gcap][kCntStride], zero between launches
   int* status;

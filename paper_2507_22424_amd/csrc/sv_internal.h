@@ -11,11 +11,10 @@
 namespace sv {
 
 constexpr int kWave = 64;           // CDNA wavefront
-constexpr int kMTile = 64;          // rows of activations one GEMM workgroup covers
+constexpr int kRowPad = 64;         // float32 buffers and logits are laid out for a multiple of this many rows
 constexpr size_t kAlign = 256;      // alignment of every region inside packed blobs / workspace
 
-// bfloat16 stored as its 16 bits; converted by hand so that rounding is explicit
-// (round to nearest, ties to even; NaN stays NaN).
+// bfloat16 stored as its 16 bits.
 struct bf16_t {
   uint16_t bits;
 };
@@ -26,28 +25,6 @@ __host__ __device__ inline float to_f32(bf16_t v) {
   return c.f;
 }
 __host__ __device__ inline float to_f32(float v) { return v; }
-
-__host__ __device__ inline bf16_t f32_to_bf16(float f) {
-  union { uint32_t u; float f; } c;
-  c.f = f;
-  uint32_t u = c.u;
-  bf16_t r;
-  if ((u & 0x7fffffffu) > 0x7f800000u) {
-    r.bits = (uint16_t)((u >> 16) | 0x0040u);
-  } else {
-    u += 0x7fffu + ((u >> 16) & 1u);
-    r.bits = (uint16_t)(u >> 16);
-  }
-  return r;
-}
-
-template <typename T> struct Cvt;
-template <> struct Cvt<float> {
-  __device__ static inline float from(float f) { return f; }
-};
-template <> struct Cvt<bf16_t> {
-  __device__ static inline bf16_t from(float f) { return f32_to_bf16(f); }
-};
 
 __host__ __device__ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 __host__ __device__ inline int ceil_div(int a, int b) { return (a + b - 1) / b; }

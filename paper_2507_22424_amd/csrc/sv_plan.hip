@@ -78,7 +78,8 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
 // Rows the kernels split at.  Up to 128 gemm_skinny, unless its groups of few tiles would make more than one
 // round of the chip (us, o / down / qkv / gate+up on the 7B shapes: 70 rows 18.1 / 34.3 / 36.8 / 54.8
 // against gemm_mid's 19.6 / 34.0 / 40.7 / 60.2; 128 rows 20.5 / 39.3 / 45.6 / 62.5 against 22.6 / 40.4 /
-// 45.4 / 66.7; 150 rows 24.1 / 45.5 / 54.7 / 100 against 26.6 / 46.0 / 54.1 / 79.2).
+// 45.4 / 66.7; a gemm_skinny of five row blocks, not kept, took 24.1 / 45.5 / 54.7 / 100 at 150 rows against
+// 26.6 / 46.0 / 54.1 / 79.2).
 ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd) {
   if (M <= kSkinnyMaxRows) {
     const ProductPlan p = plan_skinny(M, N, K, n_xcd);
