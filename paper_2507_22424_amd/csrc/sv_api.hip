@@ -114,7 +114,7 @@ static WorkspaceLayout workspace_layout(const sv_model_cfg& c, int m_rows, int n
   if (c.dtype != SV_F32 && n_scored > 0 && n_scored % kFragRows == 0) {
     size_t xch = 0;
     for (int n_xcd = 1; n_xcd <= kXcds; n_xcd *= 2) {
-      const ProductPlan p = plan_product(m_rows, n_scored, (int)H, 0, n_xcd);
+      const ProductPlan p = plan_head(m_rows, n_scored, (int)H, n_xcd);
       const size_t x = (size_t)n_xcd * p.wg_x * p.unit_stride * 16;
       xch = x > xch ? x : xch;
     }
@@ -387,7 +387,7 @@ static int head_packed(const sv_model_cfg& c, const char* packed, const float* x
   uint4* xs = (uint4*)(ws + wl.head_xs);
   float* ssq = (float*)(ws + wl.head_ssq);
   split_gain_kernel<<<dim3(wl.n_rb * 4, H / 256), 256, 0, st>>>(x, (const float*)(packed + hl.gain), n_rows, H, wl.m_pad, wl.n_rb, xs, ssq);
-  const ProductPlan p = plan_product(n_rows, n, H, 0, n_xcd);
+  const ProductPlan p = plan_head(n_rows, n, H, n_xcd);
   ProductScratch scratch;
   scratch.xch = (f32x4_t*)(ws + wl.head_xch);
   scratch.group_cnt = (unsigned*)(ws + wl.counters);                  // the layers' counters and status word
@@ -722,7 +722,7 @@ int sv_product_plan(const sv_model_cfg* cfg, int n_rows, int which, int n_scored
   if (which == SV_PLAN_HEAD && (n_scored < 1 || n_scored > cfg->vocab || n_scored % kFragRows)) return SV_ERR_SHAPE;
   ProductPlan p;
   if (which == SV_PLAN_HEAD) {
-    p = plan_product(n_rows, n_scored, cfg->hidden, 0, n_xcd);
+    p = plan_head(n_rows, n_scored, cfg->hidden, n_xcd);
   } else {
     const LayerPlan l = plan_layer(*cfg, n_rows, n_xcd);
     p = which == SV_PLAN_QKV ? l.qkv : (which == SV_PLAN_OUT ? l.o : (which == SV_PLAN_GATE_UP ? l.gu : l.down));

@@ -40,7 +40,7 @@ struct SkinnyArgs {
   const uint4* Wp;           // packed weights [K / (16 << WF)][N / 32][64]
   int N;                     // output columns
   int lgS;                   // S = 1 << lgS workgroups along K
-  int gpx, n_xcd;            // tile groups per XCD, XCDs
+  int gpx, n_xcd, m_tiles;   // tile groups per XCD, XCDs, blocks of RB row blocks (EPI_OUT; else one)
   // tiles per group, groups with one more, both in half tiles (lgH = 0) or tiles (1).  Half h of a tile:
   // its rows 8h .. 8h+7 and 16+8h .. 16+8h+7, the quads q with q % 2 == h
   int tq, trem, lgH;
@@ -88,7 +88,7 @@ struct SkinnyRing {
 
 template <int RB, int NT, int EPI, int WF>
 __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, float* s_rows, float* s_pos, int* s_crow,
-                                            float* s_freq, const int xcd, const int ug, const int sp) {
+                                            float* s_freq, const int xcd, const int ug, const int mt, const int sp) {
   typedef SkinnyRing<RB, NT, WF> Ring;
   constexpr int U = RB * NT, UK = Ring::UK, DW = Ring::DW, DX = Ring::DX;
   constexpr bool PAIR = epi_pairs(EPI);
@@ -99,6 +99,8 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int S = 1 << a.lgS;
   const int g = xcd * a.gpx + ug;
+  const int m0 = EPI == EPI_OUT ? mt * RB * 32 : 0;      // first row of this block
+  const int gm = EPI == EPI_OUT ? ug * a.m_tiles + mt : ug;   // group of workgroups that share sums, on this XCD
   const SkinnyTiles tl = skinny_tiles(a, g);
   const int t_begin = tl.begin, t_count = tl.count;
 
@@ -112,7 +114,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   constexpr int kRows = RB * 32, kParts = 256 / kRows, kSsqBatch = 32;
   const int row = tid % kRows, part0 = tid / kRows;
   float ssv[kSsqBatch];
-  const float* const ssq = a.e.ssq + row;
+  const float* const ssq = a.e.ssq + (EPI == EPI_OUT ? min(m0 + row, a.e.m_pad - 1) : row);
   if (EPI != EPI_RESID) {
 #pragma unroll
     for (int i = 0; i < kSsqBatch; ++i) ssv[i] = ssq[(size_t)(min(part0 + kParts * i, a.e.n_ssq - 1) * a.e.m_pad)];
@@ -136,7 +138,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
     w_off[t] = (unsigned)min(t, t_count - 1) * 64u + l;
   }
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) x_off[rb] = rb * 128u + lane;
+  for (int rb = 0; rb < RB; ++rb) x_off[rb] = (EPI == EPI_OUT ? (unsigned)min(mt * RB + rb, a.e.n_rb - 1) : rb) * 128u + lane;
   u32x4_t xr[DX][2 * RB], wr[DW][NT];
   int w_left = n_units, x_left = n_units * UK;
   if (n_units == 0) wp = xp = (gptr_t)a.Xs;
@@ -239,7 +241,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
 
   // ---- the S workgroups' sums meet in the XCD's L2 ----
   // item j of a wave is finished by slice j % S
-  const size_t unit = (size_t)xcd * a.ucap + ug * S;               // first workgroup of the group
+  const size_t unit = (size_t)xcd * a.ucap + gm * S;               // first workgroup of the group
 #pragma unroll
   for (int j = 0; j < NI; ++j) {
     if (j >= n_mine) continue;
@@ -252,7 +254,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
       for (int qi = 0; qi < QI; ++qi) dst[qi * 64] = mine[j * QI + qi];
     }
   }
-  const auto gcnt = a.group_cnt + ((size_t)xcd * a.gcap + ug) * kCntStride;
+  const auto gcnt = a.group_cnt + ((size_t)xcd * a.gcap + gm) * kCntStride;
   if (S > 1) {
     __builtin_amdgcn_s_waitcnt(0);         // this wave's sums are in the L2
     __syncthreads();
@@ -316,7 +318,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
         const float pos = EPI == EPI_QKV ? s_pos[ml] : 0.f;
         const int crow = EPI == EPI_QKV ? s_crow[ml] : 0;
         const float rs = EPI != EPI_RESID ? s_rstd[ml] : 1.f;
-        float sq = epi_quad<EPI, WF>(a.e, a.N, t_begin + t, q, ml, h, rs, pos, crow, s_freq, v[0], v[1], ld[b]);
+        float sq = epi_quad<EPI, WF>(a.e, a.N, t_begin + t, q, m0 + ml, h, rs, pos, crow, s_freq, v[0], v[1], ld[b]);
         if (EPI == EPI_RESID) {
           sq = lane_pair32_sum(sq);
           if (h == 0) s_rows[(wave * U + u) * 32 + lane] = sq;
@@ -341,9 +343,9 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   if (S > 1 && tid == 0) group_leave(gcnt, S);
 }
 
-// grid = (n_xcd, gpx * S), block = 256, one workgroup per CU.  The hardware deals workgroups to the XCDs in
-// turn, so x is the XCD; in y the S slices of a tile group follow each other.  A group has NTM or NTM - 1
-// tiles (fewer: the spare ones are multiplied and dropped).
+// grid = (n_xcd, gpx * m_tiles * S), block = 256, one workgroup per CU.  The hardware deals workgroups to the
+// XCDs in turn, so x is the XCD; in y the S slices of a tile group follow each other, then its blocks of rows.
+// A group has NTM or NTM - 1 tiles (fewer: the spare ones are multiplied and dropped).
 template <int RB, int NTM, int EPI, int WF>
 __global__ __launch_bounds__(256, 1) void gemm_skinny(const SkinnyArgs a) {
   constexpr int kRowWords = EPI == EPI_RESID ? 4 * RB * NTM * 32 : 256 + 4 * RB * 32;
@@ -352,11 +354,12 @@ __global__ __launch_bounds__(256, 1) void gemm_skinny(const SkinnyArgs a) {
   __shared__ float s_pos[EPI == EPI_QKV ? 32 * RB : 1];
   __shared__ int s_crow[EPI == EPI_QKV ? 32 * RB : 1];
   __shared__ __attribute__((aligned(16))) float s_freq[64];
-  const int ug = (int)blockIdx.y >> a.lgS, sp = (int)blockIdx.y & ((1 << a.lgS) - 1);
+  const int gm = (int)blockIdx.y >> a.lgS, sp = (int)blockIdx.y & ((1 << a.lgS) - 1);
+  const int ug = EPI == EPI_OUT ? gm / a.m_tiles : gm, mt = EPI == EPI_OUT ? gm - ug * a.m_tiles : 0;
   const int t_count = skinny_tiles(a, (int)blockIdx.x * a.gpx + ug).count;
   if (t_count == 0) return;
-  if (t_count == NTM) skinny_body<RB, NTM, EPI, WF>(a, lds, s_rows, s_pos, s_crow, s_freq, blockIdx.x, ug, sp);
-  else skinny_body<RB, NTM - 1, EPI, WF>(a, lds, s_rows, s_pos, s_crow, s_freq, blockIdx.x, ug, sp);
+  if (t_count == NTM) skinny_body<RB, NTM, EPI, WF>(a, lds, s_rows, s_pos, s_crow, s_freq, blockIdx.x, ug, mt, sp);
+  else skinny_body<RB, NTM - 1, EPI, WF>(a, lds, s_rows, s_pos, s_crow, s_freq, blockIdx.x, ug, mt, sp);
 }
 
 }  // namespace sv

@@ -88,6 +88,34 @@ ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd) {
   return plan_mid(M, N, K, wf, n_xcd);
 }
 
+// The head's product of more than 64 rows and at most two weight tiles per XCD (the 256 action rows): gemm_skinny
+// on blocks of rows, as many K slices and as few rows per workgroup as one round of the chip takes.  Elsewhere
+// plan_product: of gemm_mid's four waves, three would have no tile here.  us of the whole call, 256 columns of
+// H = 4096, without / with this at 65, 150, 240, 480, 960 rows: 16.1 / 14.7, 22.4 / 17.8, 24.6 / 21.0, 30.5 / 26.9,
+// 39.6 / 35.9; H = 1024: 13.8 / 12.8, 16.6 / 14.0, 17.2 / 13.8, 19.0 / 16.0, 23.3 / 21.7; 512 columns: the same or
+// up to 20 % less; from 1024 columns on: 10 % less to 11 % more.
+ProductPlan plan_head(int M, int N, int K, int n_xcd) {
+  const int tiles = N / kFragRows, tiles_x = ceil_div(tiles, n_xcd), n_rb = ceil_div(M, kFragRows);
+  for (int lgS = 3; M > 64 && tiles_x <= 2 && lgS >= 0; --lgS) {
+    if (K < (256 << lgS)) continue;
+    for (int rb = 1; rb <= 4; ++rb) {
+      const int m_tiles = ceil_div(n_rb, rb), fit = (kCusPerXcd >> lgS) / m_tiles, gpx = fit < tiles_x ? fit : tiles_x;
+      if (gpx < 1) continue;
+      const int nt = ceil_div(tiles, n_xcd * gpx);
+      if (nt > skinny_max_tiles(rb)) continue;
+      ProductPlan p;
+      memset(&p, 0, sizeof(p));
+      p.rb = rb; p.lgS = lgS; p.gpx = gpx; p.m_tiles = m_tiles;
+      p.nt = nt <= 2 ? 2 : (rb > 2 ? 3 : (nt <= 4 ? 4 : 6));
+      p.wg_x = (gpx * m_tiles) << lgS;
+      p.unit_stride = kSkinnyUnitStride;
+      p.n_planes = tiles;
+      return p;
+    }
+  }
+  return plan_product(M, N, K, 0, n_xcd);
+}
+
 void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint4* Xs, const uint4* Wp, int N, int K,
                     const ProductScratch& s, const EpiArgs& e, hipStream_t st) {
   const int tiles = N / kFragRows, groups = n_xcd * p.gpx;
@@ -109,7 +137,7 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
     SkinnyArgs a;
     memset(&a, 0, sizeof(a));
     const int units = K / (kFragK << wf), waves = 4 << p.lgS;
-    a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd;
+    a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd; a.m_tiles = p.m_tiles;
     // Groups end at half tiles where that makes the largest group smaller, the weight bytes set the time (up to
     // 32 rows of bf16 weights) and nothing is written per tile (the residual's row sums are).  7B, gate/up, 5.375 tiles
     // a group: single row 3247 -> 3185 us per step, one layer of 26 nodes 104.3 -> 102.7; 60 rows 3851 -> 3864, and 3 %

@@ -18,6 +18,7 @@ struct ProductPlan {
   int planes, n_planes;      // EPI_RESID: row-sum planes per column group, in all
 };
 ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd);
+ProductPlan plan_head(int M, int N, int K, int n_xcd);     // EPI_OUT on bf16 weights
 
 // Where a product finds its scratch.
 struct ProductScratch {

@@ -91,6 +91,35 @@ def test_full_vocabulary_head_in_every_form_of_its_product():
         assert np.array_equal(token.cpu().numpy(), np.argmax(got, axis=1))
 
 
+@pytest.mark.parametrize("H", [512, 4096])
+def test_head_of_few_columns_on_blocks_of_rows(H):
+    """Up to two weight tiles per XCD and more than 64 rows: one to four 32-row blocks per workgroup, the last block
+    of rows full, ragged or partly beyond the rows; one column tile, one and two per XCD."""
+    V, rows = 512, [65, 96, 128, 129, 225, 257, 289, 400, 481, 673, 960]
+    cfg = sv.model_cfg("bf16", H, H // 128, 128, 256, V)
+    gen = torch.Generator().manual_seed(29)
+    x = torch.randn(max(rows), H, generator=gen)
+    g = (1.0 + 0.1 * torch.randn(H, generator=gen)).to(torch.bfloat16)
+    w = (0.02 * torch.randn(V, H, generator=gen)).to(torch.bfloat16)
+    ref, _ = vo.action_head(f64(x), f64(g), f64(w), 0, 1e-5)
+    xd, gd, wd = x.cuda(), g.cuda(), w.cuda()
+    for n in (32, 256, 512):
+        packed = torch.empty(sv.sv_packed_head_bytes(cfg, V - n, V), dtype=torch.uint8, device="cuda")
+        sv.sv_pack_head(cfg, gd, wd, V - n, V, packed)
+        ws = torch.empty(sv.sv_workspace_bytes(cfg, 16, 60, n), dtype=torch.uint8, device="cuda").fill_(0xFF)
+        sv.sv_workspace_init(cfg, 16, 60, n, ws)
+        off, _ = sv.sv_workspace_region(cfg, 16, 60, n, sv.SV_WS_STATUS)
+        for M in rows:
+            token = torch.full((M + 1,), -7, dtype=torch.int32, device="cuda")
+            logits = torch.full((M + 1, n), -7.0, dtype=torch.float32, device="cuda")
+            sv.sv_action_head_argmax_packed(cfg, packed, xd, M, V - n, V, token, logits, ws)
+            assert int(ws[off:off + 4].view(torch.int32).item()) == 0
+            got = logits.cpu().numpy()
+            assert worst_row(row_rel_err(got[:M], ref[:M, V - n:])) <= TOL, (n, M)
+            assert np.array_equal(token[:M].cpu().numpy(), V - n + np.argmax(got[:M], axis=1))
+            assert (got[M] == -7.0).all() and int(token[M]) == -7
+
+
 # float32: sums of at most 8192 products in another order than the oracle's float64, 2^-24 each and random in
 # sign: below 1e-6 of a row; the parity tests' bound for float32 models leaves room for the softmax.
 TOL_F32 = 1e-5
