@@ -383,7 +383,7 @@ def main():
         out["roofline"]["frac_of_stream_read"] = gemm_gbs / ceiling
     if headline:
         # how often the greedy choice over the WHOLE vocabulary leaves the 256 action tokens
-        # (the acceptance rule then rejects): the full head on the packed streaming kernel, once
+        # (the acceptance rule then rejects): the full packed head, once
         full = wl.head_weights(cfg, full_vocab=True)
         nb = sv.sv_packed_head_bytes(vp.cfg, 0, cfg.vocab)
         ph = torch.empty(nb, dtype=torch.uint8, device="cuda")

@@ -45,7 +45,7 @@ class VerifyPass:
         dt = sv.storage_dtype(self.cfg)
         self.g_final = torch.ones(wc.hidden, dtype=dt, device=device)
         self.w_lm = torch.zeros(wc.vocab, wc.hidden, dtype=dt, device=device)
-        # bf16 models score the head on the streaming kernel, from a packed copy of its rows
+        # bf16 models score the head on the layers' product kernels, from a packed copy of its rows
         self.packed_head: Optional[torch.Tensor] = None
         self.head_packable = self.cfg.dtype != sv.SV_F32 and self.n_scored % 32 == 0
         self.x0 = torch.zeros(self.M, wc.hidden, dtype=torch.float32, device=device)

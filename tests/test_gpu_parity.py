@@ -130,7 +130,7 @@ def test_c1_tiny_f32_layer_head_accept():
 
 @pytest.mark.parametrize("T,B,P", [(1, 1, 64), (70, 2, 33), (128, 1, 200)])
 def test_f32_odd_shapes(T, B, P):
-    """Root-only tree, a 140-row batch (three 64-row tiles with a ragged tail), two mask words."""
+    """Root-only tree, a 140-row batch with a ragged tail, two mask words."""
     cfg = wl.C1.scaled(name=f"f32-T{T}-B{B}", index=10 + B, n_layers=2, tree_nodes=T,
                        n_episodes=B, prefix_lo=max(1, P - 9), prefix_hi=P, max_children=4,
                        spine_lo=min(3, max(T - 1, 0)))
@@ -144,9 +144,8 @@ def test_f32_odd_shapes(T, B, P):
 @pytest.mark.parametrize("T,B,P", [(26, 3, 90), (60, 1, 280), (128, 1, 300), (70, 2, 40), (26, 1, 1200),
                                    (100, 3, 150), (128, 2, 64)])
 def test_bf16_small_model(T, B, P):
-    """Several row tiles, ragged prefixes: 64 rows and fewer on the streaming kernel, more on the
-    many-row kernels with one, two or three 128-row blocks (with and without K split across
-    workgroups); the case (26, 1, 1200) has so few (episode, head, query block) tasks and so long
+    """One to ten 32-row blocks, ragged prefixes: up to 128 rows on gemm_skinny, more on gemm_mid;
+    the case (26, 1, 1200) has so few (episode, head, query block) tasks and so long
     a prefix that the tree attention splits its keys across workgroups."""
     cfg = wl.C2.scaled(name=f"bf16-small-T{T}-B{B}", index=20 + B, n_layers=3, hidden=512,
                        n_heads=4, head_dim=128, mlp_dim=1536, vocab=1024, n_bins=256,
@@ -276,8 +275,7 @@ def _small_bf16(T=26, B=2, P=70, layers=2, name="bf16-robust"):
 def test_results_are_bit_reproducible_and_independent_of_workspace_contents(T, B):
     """Split-K partial sums are added in a fixed order: two runs give identical bits, also after
     the scratch workspace was filled with NaN patterns (only sv_workspace_init's counters count).
-    52 rows run on the streaming kernel, 80 and 300 on the many-row kernels (K split across
-    workgroups, float32 partial blocks)."""
+    52 and 80 rows run on gemm_skinny (two and three row blocks), 300 on gemm_mid."""
     s = SideBySide(_small_bf16(T=T, B=B, name=f"bf16-robust-T{T}-B{B}"), per_layer=False)
     first = (s.gpu_logits.copy(), s.gpu_x.copy(), s.gpu_token.copy())
     s.gpu.workspace.fill_(0xFF)                      # NaN everywhere, counters included
@@ -300,23 +298,21 @@ def test_bf16_degenerate_trees_and_prefixes(T, B, P):
     check_accept_paths(s, (0, 2))
 
 
-@pytest.mark.parametrize("T", [30, 45])
+@pytest.mark.parametrize("T", [30, 45, 70])
 def test_bf16_rows_of_very_different_size_keep_their_relative_precision(T):
-    """Rows that share a 64-row tile and differ by up to 10^8 in size: every row still meets the
-    bar measured against its own size (the split-K partial sums travel as 16-bit fixed point, so
-    this holds only because each row is normalised before the tile's scale is chosen; with 90
-    rows the many-row kernels run, whose activations are normalised before they are split)."""
+    """Rows that share a row block and differ by up to 10^8 in size: every row still meets the bar
+    measured against its own size (its two bf16 parts and float32 sums are its own; 1 / rms is
+    applied to the finished sums).  60 and 90 rows: gemm_skinny; 140: gemm_mid."""
     cfg = _small_bf16(T=T, B=2, P=60, name=f"bf16-row-sizes-T{T}")
     s = SideBySide(cfg, hidden_transform=lambda b, h: h * wl.row_magnitudes(cfg, b, 4.0)[:, None])
     check_forward(s, TOL["bf16"])
 
 
-@pytest.mark.parametrize("T", [24, 40])
+@pytest.mark.parametrize("T", [24, 40, 72])
 def test_bf16_nan_in_one_episode_stays_in_that_episode(T):
-    """A NaN in an input row of episode 1: episode 0, which shares the row tile, the partial
-    tiles and the launches with it, is unaffected and still matches the oracle; the poisoned
-    row itself comes out as NaN on both sides.  (48 rows: streaming kernel; 80 rows: many-row
-    kernels.)"""
+    """A NaN in an input row of episode 1: episode 0, which shares row blocks, exchanged sums and
+    launches with it, is unaffected and still matches the oracle; the poisoned row itself comes
+    out as NaN on both sides.  (48 and 80 rows: gemm_skinny; 144: gemm_mid.)"""
     cfg = _small_bf16(T=T, B=2, P=50, name=f"bf16-nan-row-T{T}")
     T = cfg.tree_nodes
 
@@ -429,23 +425,22 @@ def _head_both_ways(H, V, M, ranges, seed, rows_scale=None):
 
 
 def test_packed_head_small_shapes_and_ranges():
-    """The head on the streaming kernel (Eq. 1; Sec. 4.3 for the action rows): one tile, fewer
-    tiles than tile groups, the action rows, the full vocabulary; one row, a ragged row tile,
-    several row tiles."""
+    """The head on the product kernels (Eq. 1; Sec. 4.3 for the action rows): one tile, fewer tiles
+    than XCDs, the action rows, the full vocabulary; one row, a ragged row block, six row blocks."""
     _head_both_ways(512, 1024, 1, [(992, 1024), (768, 1024)], seed=11)
     _head_both_ways(512, 1024, 60, [(512, 608), (768, 1024), (0, 1024)], seed=12)
     _head_both_ways(1024, 2048, 192, [(1792, 2048), (0, 2048)], seed=13)
 
 
 def test_packed_head_tiles_shared_between_waves_with_short_k_slices():
-    """Many tiles per group and K slices of 2 and of 4 pieces: the waves' runs of pieces cut
-    through tiles (5 or 6 tiles per group over four waves), so tiles are summed from two waves."""
+    """About 45000 columns: six weight tiles per group with the shortest run of K that a wave can get
+    (64 values), and the many-row kernel without K slices (70 rows)."""
     _head_both_ways(256, 44800, 20, [(0, 44800)], seed=15)
     _head_both_ways(512, 45056, 70, [(0, 45056)], seed=16)
 
 
 def test_packed_head_7b_shape_action_rows_and_full_vocabulary():
-    """H = 4096, V = 32000, 60 rows of very different size (the row scales of the partial tiles)."""
+    """H = 4096, V = 32000, 60 rows of very different size."""
     scale = torch.tensor([10.0 ** ((i % 7) - 3) for i in range(60)])
     _head_both_ways(4096, 32000, 60, [(32000 - 256, 32000), (0, 32000)], seed=14, rows_scale=scale)
 
@@ -462,12 +457,12 @@ def test_stream_read_aid_runs_on_ragged_sizes_and_leaves_memory_alone():
         assert torch.equal(buf, keep) and int(sink.sum()) == 0
 
 
-@pytest.mark.parametrize("T", [26, 48])
+@pytest.mark.parametrize("T", [26, 48, 80])
 def test_graph_replays_match_host_launched_steps(T):
     """One step recorded into a HIP graph and replayed: every replay - with new hidden rows and
     draft tokens written between replays, host-launched steps and synchronisations in between -
-    gives bit for bit what the host-launched step gives on the same inputs.  (52 rows: streaming
-    kernel; 96 rows: the many-row kernels with their split, row-norm and reduction launches.)"""
+    gives bit for bit what the host-launched step gives on the same inputs.  (52 and 96 rows:
+    gemm_skinny; 160 rows: gemm_mid.)"""
     cfg = _small_bf16(T=T, B=2, P=40, name=f"bf16-graph-T{T}")
     B, T = cfg.n_episodes, cfg.tree_nodes
     pl = wl.prefix_lengths(cfg)
