@@ -257,7 +257,7 @@ int sv_action_head_argmax_noalloc(const sv_model_cfg *cfg, const void *g_final, 
                                   const float *x, int n_rows, int vocab_lo, int vocab_hi,
                                   int32_t *out_token, float *out_logits, void *stream);
 
-/* The same head for bf16 models (SV_BF16, SV_BF16_W8) on the streaming matrix-core kernel of
+/* The same head for bf16 models (SV_BF16, SV_BF16_W8, SV_BF16_W4) on the streaming matrix-core kernel of
  * the layers: the head rows [vocab_lo, vocab_hi) are re-tiled once at load time, and every
  * call then reads them once at streaming speed (final RMSNorm, Eq. 1; Sec. 4.3 for the
  * action rows).  vocab_hi - vocab_lo must be a multiple of 32 and H a multiple of 256.

@@ -41,6 +41,27 @@ def test_products_at_the_edges_of_their_split(dtype, T, B, H, F):
     check_forward(SideBySide(cfg, store=bf16_store, stack_tol=TOL), TOL, TOL_ATTN)
 
 
+@pytest.mark.parametrize("T,B", [(20, 1), (65, 2)])
+def test_every_finite_e4m3_code(T, B, monkeypatch):
+    """Codes drawn evenly from all 254 finite ones, subnormals and 448 among them (drawn weights use the middle of
+    the range only), on both product kernels."""
+    drawn = wl.layer_weights_w8
+
+    def all_codes(cfg, layer):
+        w, rng = drawn(cfg, layer), np.random.default_rng(layer)
+        codes = np.array([c for c in range(256) if c & 0x7f != 0x7f], dtype=np.uint8)
+        for n in ("wq", "wk", "wv", "wo", "wg", "wu", "wd"):
+            w[n] = torch.from_numpy(rng.choice(codes, size=tuple(w[n].shape)))
+            w[n + "_scale"] = w[n + "_scale"] * 0 + 2e-4       # (the codes' root mean square is 100)
+        return w
+
+    monkeypatch.setattr(wl, "layer_weights_w8", all_codes)
+    cfg = wl.C2.scaled(name=f"codes-{B}x{T}", index=79, dtype="bf16_w8", n_layers=2, hidden=512, n_heads=4, head_dim=128, mlp_dim=768,
+                       vocab=1024, n_bins=256, tree_nodes=T, n_episodes=B, prefix_lo=20, prefix_hi=30, max_children=6, spine_lo=3,
+                       r_values=(0, 4))
+    check_forward(SideBySide(cfg, store=bf16_store, stack_tol=TOL), TOL, TOL_ATTN)
+
+
 # One layer of the 7B shape.  Episodes and nodes for which the planner gives each product, up to 960 rows of bf16
 # weights and 240 of the others, every form it has (tests/test_plan_coverage.py holds the lists to that).
 # Here the softmax often picks one key, and 4096 terms make large keys: appended values that round to the

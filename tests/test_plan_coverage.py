@@ -40,6 +40,18 @@ def test_the_timed_cases_lie_in_the_range_that_is_tested():
         assert case["model"] != "7b" or rows <= (960 if case["dtype"] == "bf16" else 240), case["name"]
 
 
+@pytest.mark.parametrize("H,F", [(256, 65536), (512, 65536), (4096, 11008), (8192, 28672)])
+def test_groups_that_share_sums_fit_the_counters(H, F):
+    """A workspace holds counters of 4096 groups, an equal share for every XCD, whatever the sizes: no plan that
+    splits along K has more."""
+    cfg = sv.model_cfg("bf16", H, H // 128, 128, F, 32000)
+    for n_xcd in range(1, 9):
+        for rows in list(range(1, 1025, 31)) + list(range(1025, 32769, 401)):
+            for which in LAYER + (sv.SV_PLAN_HEAD,):
+                _, _, _, slices, groups, blocks = sv.sv_product_plan(cfg, rows, which, 32000, n_xcd)
+                assert slices == 1 or groups * blocks <= 4096 // n_xcd, (n_xcd, rows, which)
+
+
 def test_plan_queries_check_their_arguments():
     bf, f32 = _cfg("bf16"), sv.model_cfg("f32", 256, 4, 64, 688, 512)
     assert sv.lib().sv_product_plan(bf, 60, 0, 0, 8, None) == sv.SV_ERR_NULL
