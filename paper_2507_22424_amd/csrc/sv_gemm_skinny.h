@@ -40,7 +40,7 @@ struct SkinnyArgs {
   const uint4* Wp;           // packed weights [K / (16 << WF)][N / 32][64]
   int N;                     // output columns
   int lgS;                   // S = 1 << lgS workgroups along K
-  int gpx, n_xcd, m_tiles;   // tile groups per XCD, XCDs, blocks of RB row blocks (EPI_OUT; else one)
+  int gpx, n_xcd;            // tile groups per XCD, XCDs
   // tiles per group, groups with one more, both in half tiles (lgH = 0) or tiles (1).  Half h of a tile:
   // its rows 8h .. 8h+7 and 16+8h .. 16+8h+7, the quads q with q % 2 == h
   int tq, trem, lgH;
@@ -100,7 +100,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   const int S = 1 << a.lgS;
   const int g = xcd * a.gpx + ug;
   const int m0 = EPI == EPI_OUT ? mt * RB * 32 : 0;      // first row of this block
-  const int gm = EPI == EPI_OUT ? ug * a.m_tiles + mt : ug;   // group of workgroups that share sums, on this XCD
+  const int gm = EPI == EPI_OUT ? mt * a.gpx + ug : ug;  // group of workgroups that share sums, on this XCD
   const SkinnyTiles tl = skinny_tiles(a, g);
   const int t_begin = tl.begin, t_count = tl.count;
 
@@ -343,9 +343,9 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   if (S > 1 && tid == 0) group_leave(gcnt, S);
 }
 
-// grid = (n_xcd, gpx * m_tiles * S), block = 256, one workgroup per CU.  The hardware deals workgroups to the
-// XCDs in turn, so x is the XCD; in y the S slices of a tile group follow each other, then its blocks of rows.
-// A group has NTM or NTM - 1 tiles (fewer: the spare ones are multiplied and dropped).
+// grid = (n_xcd, gpx * S, blocks of RB row blocks: EPI_OUT, else 1), block = 256, one workgroup per CU.  The
+// hardware deals workgroups to the XCDs in turn, so x is the XCD; in y the S slices of a tile group follow each
+// other.  A group has NTM or NTM - 1 tiles (fewer: the spare ones are multiplied and dropped).
 template <int RB, int NTM, int EPI, int WF>
 __global__ __launch_bounds__(256, 1) void gemm_skinny(const SkinnyArgs a) {
   constexpr int kRowWords = EPI == EPI_RESID ? 4 * RB * NTM * 32 : 256 + 4 * RB * 32;
@@ -354,8 +354,7 @@ __global__ __launch_bounds__(256, 1) void gemm_skinny(const SkinnyArgs a) {
   __shared__ float s_pos[EPI == EPI_QKV ? 32 * RB : 1];
   __shared__ int s_crow[EPI == EPI_QKV ? 32 * RB : 1];
   __shared__ __attribute__((aligned(16))) float s_freq[64];
-  const int gm = (int)blockIdx.y >> a.lgS, sp = (int)blockIdx.y & ((1 << a.lgS) - 1);
-  const int ug = EPI == EPI_OUT ? gm / a.m_tiles : gm, mt = EPI == EPI_OUT ? gm - ug * a.m_tiles : 0;
+  const int ug = (int)blockIdx.y >> a.lgS, sp = (int)blockIdx.y & ((1 << a.lgS) - 1), mt = EPI == EPI_OUT ? (int)blockIdx.z : 0;
   const int t_count = skinny_tiles(a, (int)blockIdx.x * a.gpx + ug).count;
   if (t_count == 0) return;
   if (t_count == NTM) skinny_body<RB, NTM, EPI, WF>(a, lds, s_rows, s_pos, s_crow, s_freq, blockIdx.x, ug, mt, sp);

@@ -119,7 +119,7 @@ ProductPlan plan_head(int M, int N, int K, int n_xcd) {
 void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint4* Xs, const uint4* Wp, int N, int K,
                     const ProductScratch& s, const EpiArgs& e, hipStream_t st) {
   const int tiles = N / kFragRows, groups = n_xcd * p.gpx;
-  const dim3 grid(n_xcd, p.wg_x);
+  const dim3 grid(n_xcd, p.mid ? p.wg_x : p.gpx << p.lgS, p.mid ? 1 : p.m_tiles);
   if (p.mid) {
     MidArgs a;
     memset(&a, 0, sizeof(a));
@@ -137,7 +137,7 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
     SkinnyArgs a;
     memset(&a, 0, sizeof(a));
     const int units = K / (kFragK << wf), waves = 4 << p.lgS;
-    a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd; a.m_tiles = p.m_tiles;
+    a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd;
     // Groups end at half tiles where that makes the largest group smaller, the weight bytes set the time (up to
     // 32 rows of bf16 weights) and nothing is written per tile (the residual's row sums are).  7B, gate/up, 5.375 tiles
     // a group: single row 3247 -> 3185 us per step, one layer of 26 nodes 104.3 -> 102.7; 60 rows 3851 -> 3864, and 3 %
