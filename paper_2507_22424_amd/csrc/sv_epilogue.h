@@ -150,6 +150,12 @@ __device__ inline float lane_pair32_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Sum of v over the lanes l, l ^ 16, l ^ 32, l ^ 48, in all of them.
+__device__ inline float lane_quad16_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return lane_pair32_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
 // ---- workgroups that share an output along K ---------------------------------------------------
 // They run on one XCD and exchange float32 sums through that XCD's L2: plain stores, wait for their
 // completion, arrival at a counter, bounded wait until all have arrived, L1 invalidate, loads.  The

@@ -13,6 +13,7 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kFragRows = 32;    // weight rows per fragment and per tile (MFMA N)
 constexpr int kFragK = 16;       // k-values per fragment (MFMA K)
@@ -88,6 +89,17 @@ __device__ inline bf16x8_t weight_operand(const u32x4_t raw, int kk) {
   }
   return __builtin_bit_cast(bf16x8_t, o);
 }
+
+// The same out of a lane's share of 32 weight rows x 64 k-values, two matrix instructions of 32 k-values: as above,
+// but an int4 lane has the words of its own two k-steps only.
+template <int WF, typename T>
+__device__ inline bf16x8_t weight_half(const T raw, int kk) {
+  if constexpr (WF == 2) return weight_operand<2>(u32x4_t{raw[0], raw[1], 0u, 0u}, kk);
+  else return weight_operand<WF>(raw, kk);
+}
+
+// Scheduling barrier that matrix instructions do not cross and everything else does.
+constexpr int kMfmaOrder = 0x2 | 0x4 | 0x10 | 0x20 | 0x40 | 0x80 | 0x100 | 0x200 | 0x400;
 
 // XCD (accelerator complex die) this wave runs on: bits 3:0 of the XCC_ID hardware register.
 __device__ inline int xcd_actual(int n_xcd) {

@@ -44,17 +44,16 @@ struct MidArgs {
 constexpr int kMidMaxTiles = 3;            // weight tiles per wave
 constexpr int kMidMaxRows = 5;             // row blocks per workgroup
 
-// An item = half a unit (32 x 32 sums): quads p and p + 2 where the epilogue works on pairs, else 2p and
-// 2p + 1.  A wave has 2 * RB * NT items, row block after row block; slice sp finishes the items from
-// mid_first(sp) on.
+// An item = 16 rows of a weight tile (32 x 16 sums: two accumulators, whose quads are p and p + 2 of a lane).
+// A wave has 2 * RB * NT items, 16 rows after 16 rows; slice sp finishes the items from mid_first(sp) on.
 constexpr int mid_items(int rb, int nt) { return 2 * rb * nt; }
 __host__ __device__ constexpr int mid_first(int items, int lgS, int sp) { return (sp * items + (1 << lgS) - 1) >> lgS; }
 __host__ __device__ constexpr int mid_owner(int items, int lgS, int i) { return (i << lgS) / items; }
-// slices that finish a part of one row block's items, at most: its planes of row sums
+// slices that finish a part of the items of 16 rows, at most: the planes of row sums
 constexpr int mid_planes(int rb, int nt, int lgS) {
   int most = 1;
-  for (int r = 0; r < rb; ++r) {
-    const int n = mid_owner(mid_items(rb, nt), lgS, (r + 1) * 2 * nt - 1) - mid_owner(mid_items(rb, nt), lgS, r * 2 * nt) + 1;
+  for (int r = 0; r < 2 * rb; ++r) {
+    const int n = mid_owner(mid_items(rb, nt), lgS, (r + 1) * nt - 1) - mid_owner(mid_items(rb, nt), lgS, r * nt) + 1;
     most = n > most ? n : most;
   }
   return most;
@@ -62,17 +61,18 @@ constexpr int mid_planes(int rb, int nt, int lgS) {
 // float4 a workgroup may send (4 waves, padded so that the regions do not share memory channels)
 constexpr int mid_unit_stride(int rb, int nt) { return (4 * (rb * nt * 4 + 1) + 5) * 64; }
 
+// A chunk is KK matrix instructions deep (32 k-values each): one with bf16 weights, two with codes.
 template <int RB, int NT, int WF>
 struct MidShape {
-  static constexpr int UK = 1 << WF, CK = UK < 2 ? 2 : UK;     // k-steps of a weight load, of a chunk
-  static constexpr int LW = CK / UK * NT, LX = CK * RB / 2;    // loads of a wave per chunk
+  static constexpr int KK = WF ? 2 : 1, CK = 2 * KK;           // matrix instructions, k-steps of a chunk
+  static constexpr int LW = 2 * NT, LX = CK * RB / 2;          // loads of a wave per chunk
   // chunks in flight: what the load counter (63) and the registers hold, 12 k-steps at most
-  static constexpr int kCnt = 60 / (LW + LX), kReg = (416 - 16 * RB * NT) / (4 * (LW + LX));
+  static constexpr int kCnt = 60 / (LW + LX), kReg = (416 - 16 * RB * NT) / (4 * LX + (WF == 2 ? 2 : 4) * LW);
   static constexpr int D0 = kCnt < kReg ? kCnt : kReg;
-  static constexpr int D = D0 > 6 ? 6 : D0;
+  static constexpr int D = D0 > 12 / CK ? 12 / CK : D0;
   static_assert(D >= 2, "ring too short");
 };
-constexpr int mid_chunk_k(int wf) { return wf == 2 ? 64 : 32; }
+constexpr int mid_chunk_k(int wf) { return wf ? 64 : 32; }
 
 // grid = (n_xcd, gpx * m_tiles * S), block = 256, one workgroup per CU: x is the XCD; in y the S slices of
 // an output block follow each other, then the blocks of rows of a column group, which read the same
@@ -80,11 +80,11 @@ constexpr int mid_chunk_k(int wf) { return wf == 2 ? 64 : 32; }
 template <int RB, int NT, int EPI, int WF>
 __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   typedef MidShape<RB, NT, WF> Sh;
-  constexpr int UK = Sh::UK, CK = Sh::CK, LX = Sh::LX, D = Sh::D, CW = CK / UK;
-  constexpr int E = CK * RB, PD = 2;                           // steps of a chunk; operands are read two steps ahead
+  constexpr int KK = Sh::KK, CK = Sh::CK, LX = Sh::LX, D = Sh::D, R = 2 * RB;
+  constexpr int E = KK * R, PD = NT == 1 ? 4 : 2;              // steps (16 rows) of a chunk; operands are read PD steps ahead
   constexpr int kChunk = CK * RB * 2;                          // activation fragments of a chunk
   constexpr bool PAIR = epi_pairs(EPI);
-  constexpr int U = RB * NT, NI = mid_items(RB, NT), NQ = U * 4;   // units, items, quads of a wave
+  constexpr int NI = mid_items(RB, NT), NQ = 2 * NI;           // items, quads of a wave
   constexpr int kLdsFr = 3 * kChunk > NQ * 2 ? 3 * kChunk : NQ * 2;   // ring; after the loop, half of the sums
   __shared__ u32x4_t lds[kLdsFr][64];
   __shared__ float s_rows[EPI == EPI_RESID ? 4 * RB * 32 : (RB * 32 > 256 ? RB * 32 : 256)];
@@ -106,14 +106,22 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   const int c0 = sp * a.cq + min(sp, a.crem);
   const int n = a.cq + (sp < a.crem ? 1 : 0);                  // chunks of this slice
 
+  // Lane (i, g) = (lane % 16, lane / 16) of v_mfma_f32_16x16x32_bf16 holds eight k-values of weight row (or
+  // activation row) i.  Out of the 32-row fragments: k-half g % 2 of k-step KK * (g / 2) + kk, whichever way round
+  // as long as both operands agree.  Coded weights: a 16-byte piece covers two k-steps (E4M3) or four (int4,
+  // of which a lane fetches its two).
   typedef const __attribute__((address_space(1))) u32x4_t* gptr_t;
-  gptr_t wp = (gptr_t)a.Wp + ((size_t)c0 * CW * n_tiles + t_begin) * 64;
+  typedef typename std::conditional<WF == 2, u32x2_t, u32x4_t>::type wload_t;
+  typedef const __attribute__((address_space(1))) wload_t* wptr_t;
+  constexpr int CW = WF == 2 ? 1 : 2, WU = WF == 2 ? 2 : 1;    // weight units of a chunk; loads in a 16-byte piece
+  const int g16 = lane >> 4, in_frag = (lane & 15) + 32 * (g16 & 1);
+  wptr_t wp = (wptr_t)((gptr_t)a.Wp + ((size_t)c0 * CW * n_tiles + t_begin) * 64);
   const unsigned w_row = n_tiles * 64u;
-  size_t w_step = (size_t)CW * w_row;
+  size_t w_step = (size_t)CW * w_row * WU;
   unsigned w_off[NT];
 #pragma unroll
   for (int t = 0; t < NT; ++t)       // (beyond the group's tiles: the last one again, dropped at the end)
-    w_off[t] = (unsigned)min(wave * NT + t, t_count - 1) * 64u + lane;
+    w_off[t] = ((unsigned)min(wave * NT + t, t_count - 1) * 64u + in_frag) * WU + (WF == 2 ? g16 >> 1 : (g16 >> 1) * w_row);
   gptr_t xp = (gptr_t)a.Xs + (size_t)c0 * CK * a.e.n_rb * 128;
   const unsigned x_step = CK * a.e.n_rb * 128u;
   unsigned x_off[LX];
@@ -122,7 +130,8 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
     const int f = wave * LX + i;
     x_off[i] = ((unsigned)(f % (2 * CK) / 2) * a.e.n_rb + min(mt * RB + f / (2 * CK), a.e.n_rb - 1)) * 128u + (f & 1) * 64u + lane;
   }
-  u32x4_t xin[D][LX], wr[D][CW][NT];
+  u32x4_t xin[D][LX];
+  wload_t wr[D][2 * NT];
   int wl = n, xl = n;                                          // chunks still to be requested
   // (once nothing is left the loads repeat the first activations, which the caches hold: the number of
   // loads in flight stays fixed)
@@ -134,13 +143,11 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   };
   auto issue_w = [&](int d) {
 #pragma unroll
-    for (int cw = 0; cw < CW; ++cw)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) wr[d][cw][t] = __builtin_nontemporal_load(wp + (w_off[t] + cw * w_row));
+    for (int t = 0; t < 2 * NT; ++t) wr[d][t] = __builtin_nontemporal_load(wp + (w_off[t / 2] + (t & 1) * 16 * WU));
     if (--wl > 0) {
       wp += w_step;
     } else {
-      wp = (gptr_t)a.Xs;
+      wp = (wptr_t)a.Xs;
       w_step = 0;
     }
   };
@@ -175,20 +182,21 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   }
   if (EPI == EPI_QKV) epi_tables(a.e, er, tid, RB * 32, s_pos, s_crow, s_freq);
 
-  f32x16_t acc[RB][NT];
+  f32x4_t acc[R][2 * NT];                                      // 16 activation rows x 16 weight rows each
 #pragma unroll
-  for (int i = 0; i < RB; ++i)
+  for (int i = 0; i < R; ++i)
 #pragma unroll
-    for (int j = 0; j < NT; ++j) acc[i][j] = f32x16_t{};
+    for (int j = 0; j < 2 * NT; ++j) acc[i][j] = f32x4_t{};
 
   put_x(0, 0);
   issue_x(0);
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   u32x4_t xo[PD + 1][2];
-  auto get = [&](int s, int buf, int e) {                      // step e = k-step * RB + row block
-    const int f = buf * kChunk + ((e % RB) * CK + e / RB) * 2;
-    xo[s][0] = lds[f][lane];
-    xo[s][1] = lds[f + 1][lane];
+  const u32x4_t* const x_lane = &lds[0][0] + (g16 >> 1) * KK * 128 + in_frag;
+  auto get = [&](int s, int buf, int e) {                      // step e = kk * R + 16-row block
+    const int r = e % R, f = buf * kChunk + ((r >> 1) * CK + e / R) * 2;
+    xo[s][0] = x_lane[f * 64 + (r & 1) * 16];
+    xo[s][1] = x_lane[(f + 1) * 64 + (r & 1) * 16];
   };
 #pragma unroll
   for (int e = 0; e < PD; ++e) get(e, 0, e);
@@ -203,23 +211,27 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
       put_x((d + 1) % D, nb);
       issue_x((d + 1) % D);
       if (left > d) {
-        bf16x8_t w[NT];
+        bf16x8_t w[2 * NT];
 #pragma unroll
         for (int e = 0; e < E; ++e) {
-          const int kk = e / RB, rb = e % RB;
+          const int kk = e / R, r = e % R;
           // (own LDS writes are older than the 2 * PD reads that may still be under way)
           if (e == E - PD) asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(2 * PD) : "memory");
           if (e + PD < E) get((e + PD) % (PD + 1), buf, e + PD);
           else get((e + PD) % (PD + 1), nb, e + PD - E);
-          if (rb == 0) {
+          if (r == 0) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t) w[t] = weight_operand<WF>(wr[d][kk / UK][t], kk % UK);
+            for (int t = 0; t < 2 * NT; ++t) w[t] = weight_half<WF>(wr[d][t], kk);
           }
+          // hi and lo of the same rows into the same sums, one after the other, then the next weights: the
+          // cheapest order for the power that sets the clock
 #pragma unroll
-          for (int hl = 0; hl < 2; ++hl)
+          for (int t = 0; t < 2 * NT; ++t) {
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
-              acc[rb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t], __builtin_bit_cast(bf16x8_t, xo[e % (PD + 1)][hl]), acc[rb][t], 0, 0, 0);
+            for (int hl = 0; hl < 2; ++hl)
+              acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[t], __builtin_bit_cast(bf16x8_t, xo[e % (PD + 1)][hl]), acc[r][t], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(kMfmaOrder);
+          }
           __builtin_amdgcn_sched_barrier(0);   // left alone the scheduler sinks the operand reads to their use
         }
         buf = nb;
@@ -242,15 +254,13 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // all waves have read the ring
 
   // ---- output ----
-  const int h = lane >> 5;
   const size_t unit = (size_t)xcd * a.ucap + (size_t)gm * S;       // first workgroup of the group
   const auto gcnt = a.group_cnt + ((size_t)xcd * a.gcap + gm) * kCntStride;
   f32x4_t* const stage = reinterpret_cast<f32x4_t*>(&lds[0][0]) + lane;
-  auto item_quad = [&](int i, int qi) -> f32x4_t {
-    const int q = PAIR ? (i & 1) + 2 * qi : 2 * (i & 1) + qi;
-    const f32x16_t& c = acc[(i >> 1) / NT][(i >> 1) % NT];
-    return f32x4_t{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
-  };
+  // item i = tile i % NT of this wave, rows 16 * (i / NT) ..: lane (i16, g) has activation row i16, quad g / 2 of the
+  // tile and its partner, quad g / 2 + 2
+  const int h = g16 & 1, p = g16 >> 1, i16 = lane & 15;
+  auto item_quad = [&](int i, int qi) -> f32x4_t { return acc[i / NT][2 * (i % NT) + qi]; };
   const int b0 = mid_first(NI, a.lgS, sp), b1 = mid_first(NI, a.lgS, sp + 1);   // this slice's items
   f32x4_t* const own = stage + (size_t)wave * (NQ / 2) * 64;
   if (S > 1) {
@@ -288,21 +298,21 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
     EpiLoads l[PAIR ? 1 : 2];
   };
   auto fetch = [&](int i, Loads& l) {
-    const int u = i >> 1, p = i & 1, m = m0 + (u / NT) * 32 + (lane & 31), t = t_begin + min(wave * NT + u % NT, t_count - 1);
-    epi_fetch<EPI, WF>(a.e, a.N, t, PAIR ? p : 2 * p, m, h, l.l[0]);
-    if (!PAIR) epi_fetch<EPI, WF>(a.e, a.N, t, 2 * p + 1, m, h, l.l[PAIR ? 0 : 1]);
+    const int m = m0 + (i / NT) * 16 + i16, t = t_begin + min(wave * NT + i % NT, t_count - 1);
+    epi_fetch<EPI, WF>(a.e, a.N, t, p, m, h, l.l[0]);
+    if (!PAIR) epi_fetch<EPI, WF>(a.e, a.N, t, p + 2, m, h, l.l[PAIR ? 0 : 1]);
   };
   auto finish_item = [&](int i, const f32x4_t v0, const f32x4_t v1, const Loads& l) {
-    const int u = i >> 1, p = i & 1, ml = (u / NT) * 32 + (lane & 31), t = wave * NT + u % NT;
+    const int ml = (i / NT) * 16 + i16, t = wave * NT + i % NT;
     if (t >= t_count) return;
     const float pos = EPI == EPI_QKV ? s_pos[ml] : 0.f;
     const int crow = EPI == EPI_QKV ? s_crow[ml] : 0;
     const float rs = s_rstd[ml];
-    float sq = epi_quad<EPI, WF>(a.e, a.N, t_begin + t, PAIR ? p : 2 * p, m0 + ml, h, rs, pos, crow, s_freq, v0, v1, l.l[0]);
-    if (!PAIR) sq += epi_quad<EPI, WF>(a.e, a.N, t_begin + t, 2 * p + 1, m0 + ml, h, rs, pos, crow, s_freq, v1, v1, l.l[PAIR ? 0 : 1]);
+    float sq = epi_quad<EPI, WF>(a.e, a.N, t_begin + t, p, m0 + ml, h, rs, pos, crow, s_freq, v0, v1, l.l[0]);
+    if (!PAIR) sq += epi_quad<EPI, WF>(a.e, a.N, t_begin + t, p + 2, m0 + ml, h, rs, pos, crow, s_freq, v1, v1, l.l[PAIR ? 0 : 1]);
     if (EPI == EPI_RESID) {
-      sq = lane_pair32_sum(sq);
-      if (h == 0) s_rows[wave * RB * 32 + ml] += sq;       // (this lane's own word)
+      sq = lane_quad16_sum(sq);
+      if (lane < 16) s_rows[wave * RB * 32 + ml] += sq;    // (this lane's own word)
     }
   };
   auto finish = [&](auto split) {
@@ -339,34 +349,34 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
     }
   };
   if (S == 1) {
-    // one row block at a time through LDS, so that the epilogue is a short loop
-    f32x4_t* const st = stage + (size_t)wave * (NT * 4) * 64;
+    // 16 rows at a time through LDS, so that the epilogue is a short loop
+    f32x4_t* const st = stage + (size_t)wave * (NT * 2) * 64;
 #pragma unroll
-    for (int r = 0; r < RB; ++r) {
+    for (int r = 0; r < R; ++r) {
 #pragma unroll
-      for (int k = 0; k < NT * 2; ++k) {
-        st[(2 * k) * 64] = item_quad(r * NT * 2 + k, 0);
-        st[(2 * k + 1) * 64] = item_quad(r * NT * 2 + k, 1);
+      for (int k = 0; k < NT; ++k) {
+        st[(2 * k) * 64] = item_quad(r * NT + k, 0);
+        st[(2 * k + 1) * 64] = item_quad(r * NT + k, 1);
       }
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll 1
-      for (int k = 0; k < NT * 2; ++k) {
+      for (int k = 0; k < NT; ++k) {
         Loads l;
-        fetch(r * NT * 2 + k, l);
-        finish_item(r * NT * 2 + k, st[(2 * k) * 64], st[(2 * k + 1) * 64], l);
+        fetch(r * NT + k, l);
+        finish_item(r * NT + k, st[(2 * k) * 64], st[(2 * k + 1) * 64], l);
       }
     }
   } else if (S == 2) finish(std::integral_constant<int, 2>{});
   else if (S == 4) finish(std::integral_constant<int, 4>{});
   else finish(std::integral_constant<int, 8>{});
 
-  // Partial sums of x^2 of the new rows: every slice that has finished items of a row block writes what it
+  // Partial sums of x^2 of the new rows: every slice that has finished items of a row writes what it
   // has of its rows to a plane of its own; the last of them clears the planes that are left over.
   if (EPI == EPI_RESID && a.e.next_gain) {
     __syncthreads();
     for (int ml = tid; ml < RB * 32; ml += 256) {
-      const int r = ml >> 5;
-      const int o0 = mid_owner(NI, a.lgS, r * 2 * NT), o1 = mid_owner(NI, a.lgS, (r + 1) * 2 * NT - 1);
+      const int r = ml >> 4;
+      const int o0 = mid_owner(NI, a.lgS, r * NT), o1 = mid_owner(NI, a.lgS, (r + 1) * NT - 1);
       if (sp < o0 || sp > o1 || m0 + ml >= a.e.m_pad) continue;
       float* dst = a.e.ssq_out + (size_t)(g * a.planes + sp - o0) * a.e.m_pad + m0 + ml;
       *dst = (s_rows[ml] + s_rows[RB * 32 + ml]) + (s_rows[2 * RB * 32 + ml] + s_rows[3 * RB * 32 + ml]);
