@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   constexpr int kLdsFr = 3 * kChunk > NQ * 2 ? 3 * kChunk : NQ * 2;   // ring; after the loop, half of the sums
   __shared__ u32x4_t lds[kLdsFr][64];
   __shared__ float s_rows[EPI == EPI_RESID ? 4 * RB * 32 : (RB * 32 > 256 ? RB * 32 : 256)];
-  __shared__ float s_rstd[RB * 32];
+  __shared__ float s_rstd[EPI != EPI_RESID ? RB * 32 : 1];
   __shared__ float s_pos[EPI == EPI_QKV ? 32 * RB : 1];
   __shared__ int s_crow[EPI == EPI_QKV ? 32 * RB : 1];
   __shared__ __attribute__((aligned(16))) float s_freq[64];
@@ -156,32 +156,11 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
     for (int i = 0; i < LX; ++i) lds[buf * kChunk + wave * LX + i][lane] = xin[d][i];
   };
 
-  // row sums of x^2: thread (row, part) adds its share of the planes; requested first, added once the ring
-  // is on its way
-  constexpr int kParts = RB * 32 <= 128 ? 2 : 1, kSsqBatch = 32;
-  const int row = tid % (RB * 32), part0 = tid / (RB * 32);
-  float ssv[kSsqBatch];
-  const float* const ssq = a.e.ssq + min(m0 + row, a.e.m_pad - 1);
-  if (EPI != EPI_RESID) {
-#pragma unroll
-    for (int i = 0; i < kSsqBatch; ++i) ssv[i] = ssq[(size_t)min(part0 + kParts * i, a.e.n_ssq - 1) * a.e.m_pad];
-  }
-  EpiRow er;
-  if (EPI == EPI_QKV) er = epi_row_fetch(a.e, min(m0 + row, a.e.M - 1));
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     issue_x(d);
     issue_w(d);
   }
-  if (EPI != EPI_RESID) {
-    float ss = 0.f;
-#pragma unroll
-    for (int i = 0; i < kSsqBatch; ++i) ss += part0 + kParts * i < a.e.n_ssq ? ssv[i] : 0.f;
-    for (int p = part0 + kParts * kSsqBatch; p < a.e.n_ssq; p += kParts) ss += ssq[(size_t)p * a.e.m_pad];
-    if (part0 < kParts) s_rows[part0 * RB * 32 + row] = ss;
-  }
-  if (EPI == EPI_QKV) epi_tables(a.e, er, tid, RB * 32, s_pos, s_crow, s_freq);
-
   f32x4_t acc[R][2 * NT];                                      // 16 activation rows x 16 weight rows each
 #pragma unroll
   for (int i = 0; i < R; ++i)
@@ -254,6 +233,12 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // all waves have read the ring
 
   // ---- output ----
+  // (row sums and rotary positions: see gemm_skinny)
+  constexpr int kRows = RB * 32;
+  SsqSums<kRows, 32> rows(a.e, m0, tid);
+  if (EPI != EPI_RESID) rows.request();
+  EpiRow er;
+  if (EPI == EPI_QKV) er = epi_row_fetch(a.e, min(m0 + tid % kRows, a.e.M - 1));
   const size_t unit = (size_t)xcd * a.ucap + (size_t)gm * S;       // first workgroup of the group
   const auto gcnt = a.group_cnt + ((size_t)xcd * a.gcap + gm) * kCntStride;
   f32x4_t* const stage = reinterpret_cast<f32x4_t*>(&lds[0][0]) + lane;
@@ -276,24 +261,22 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
       }
     }
   }
-  for (int r = tid; r < RB * 32; r += 256) {
-    float t = 1.f;
-    if (EPI != EPI_RESID) {
-      t = s_rows[r];
-      if (kParts > 1) t += s_rows[RB * 32 + r];
-      t = 1.0f / sqrtf(t / (float)a.e.K + a.e.eps);
-    }
-    s_rstd[r] = t;
+  if (EPI != EPI_RESID) {
+    const float ss = rows.sum();
+    if (tid < rows.kParts * kRows) s_rows[tid] = ss;
   }
+  if (EPI == EPI_QKV) epi_tables(a.e, er, tid, kRows, s_pos, s_crow, s_freq);
   if (EPI == EPI_RESID)
     for (int i = tid; i < 4 * RB * 32; i += 256) s_rows[i] = 0.f;
   if (S > 1) __builtin_amdgcn_s_waitcnt(0);         // this wave's sums are in the L2
   __syncthreads();
-  if (S > 1) {
-    if (tid == 0) group_arrive_and_wait(gcnt, S, a.n_xcd, a.status);
-    __syncthreads();
-    asm volatile("buffer_inv sc0" ::: "memory");                   // drop stale L1 lines (the L2 is shared)
+  if (EPI != EPI_RESID && tid < kRows) {            // 1 / rms of the rows, while the group meets
+    const float t = s_rows[tid] + (rows.kParts > 1 ? s_rows[kRows + tid] : 0.f);
+    s_rstd[tid] = 1.0f / sqrtf(t / (float)a.e.K + a.e.eps);
   }
+  if (S > 1 && tid == 0) group_arrive_and_wait(gcnt, S, a.n_xcd, a.status);
+  if (S > 1 || EPI != EPI_RESID) __syncthreads();
+  if (S > 1) asm volatile("buffer_inv sc0" ::: "memory");          // drop stale L1 lines (the L2 is shared)
   struct Loads {
     EpiLoads l[PAIR ? 1 : 2];
   };
@@ -307,7 +290,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
     if (t >= t_count) return;
     const float pos = EPI == EPI_QKV ? s_pos[ml] : 0.f;
     const int crow = EPI == EPI_QKV ? s_crow[ml] : 0;
-    const float rs = s_rstd[ml];
+    const float rs = EPI != EPI_RESID ? s_rstd[ml] : 1.f;
     float sq = epi_quad<EPI, WF>(a.e, a.N, t_begin + t, p, m0 + ml, h, rs, pos, crow, s_freq, v0, v1, l.l[0]);
     if (!PAIR) sq += epi_quad<EPI, WF>(a.e, a.N, t_begin + t, p + 2, m0 + ml, h, rs, pos, crow, s_freq, v1, v1, l.l[PAIR ? 0 : 1]);
     if (EPI == EPI_RESID) {

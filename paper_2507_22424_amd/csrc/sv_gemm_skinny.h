@@ -109,19 +109,6 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   const int u0 = ws * a.uq + min(ws, a.urem);
   const int n_units = a.uq + (ws < a.urem ? 1 : 0);
 
-  // What the epilogue needs to know of the rows, requested ahead of everything else: row sums of x^2 -
-  // thread (row, part) adds its share of the planes - and rotary positions.
-  constexpr int kRows = RB * 32, kParts = 256 / kRows, kSsqBatch = 32;
-  const int row = tid % kRows, part0 = tid / kRows;
-  float ssv[kSsqBatch];
-  const float* const ssq = a.e.ssq + (EPI == EPI_OUT ? min(m0 + row, a.e.m_pad - 1) : row);
-  if (EPI != EPI_RESID) {
-#pragma unroll
-    for (int i = 0; i < kSsqBatch; ++i) ssv[i] = ssq[(size_t)(min(part0 + kParts * i, a.e.n_ssq - 1) * a.e.m_pad)];
-  }
-  EpiRow er;
-  if (EPI == EPI_QKV) er = epi_row_fetch(a.e, min(row, a.e.M - 1));
-
   // Rings.  Every step issues exactly as many loads as it has used - from the activations' first fragments,
   // which the caches hold, once nothing is left - so that the number of younger loads behind any slot is
   // a compile-time constant and the waits are exact.
@@ -162,15 +149,6 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
     if (d < DX) issue_x(d);
     if (d < DW) issue_w(d);
   }
-  if (EPI != EPI_RESID) {
-    float ss = 0.f;
-#pragma unroll
-    for (int i = 0; i < kSsqBatch; ++i) ss += part0 + kParts * i < a.e.n_ssq ? ssv[i] : 0.f;
-    for (int p = part0 + kParts * kSsqBatch; p < a.e.n_ssq; p += kParts) ss += ssq[(size_t)p * a.e.m_pad];
-    s_rows[tid] = ss;
-  }
-  if (EPI == EPI_QKV) epi_tables(a.e, er, tid, kRows, s_pos, s_crow, s_freq);
-
   f32x16_t acc[NT][RB];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
@@ -201,6 +179,15 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
     }
     left -= DW;
   }
+
+  // What the epilogue needs to know of the rows: row sums of x^2 - thread (row, part) adds its share of the
+  // planes - and rotary positions.  Requested here, answered while the sums meet.  (Requested and waited for
+  // ahead of the loop they held it up by 2.5 us, by 9 us at 128 rows.)
+  constexpr int kRows = RB * 32;
+  SsqSums<kRows, (RB > 2 ? 64 : 32)> rows(a.e, EPI == EPI_OUT ? m0 : 0, tid);
+  if (EPI != EPI_RESID) rows.request();
+  EpiRow er;
+  if (EPI == EPI_QKV) er = epi_row_fetch(a.e, min(tid % kRows, a.e.M - 1));
 
   // ---- the four waves' sums meet in LDS ----
   // A wave finishes, of every unit, the quad of its own number (of every second unit the quads p and
@@ -254,10 +241,12 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
       for (int qi = 0; qi < QI; ++qi) dst[qi * 64] = mine[j * QI + qi];
     }
   }
+  if (EPI != EPI_RESID) s_rows[tid] = rows.sum();
+  if (EPI == EPI_QKV) epi_tables(a.e, er, tid, kRows, s_pos, s_crow, s_freq);
   const auto gcnt = a.group_cnt + ((size_t)xcd * a.gcap + gm) * kCntStride;
+  if (S > 1) __builtin_amdgcn_s_waitcnt(0);         // this wave's sums are in the L2
+  __syncthreads();
   if (S > 1) {
-    __builtin_amdgcn_s_waitcnt(0);         // this wave's sums are in the L2
-    __syncthreads();
     if (tid == 0) group_arrive_and_wait(gcnt, S, a.n_xcd, a.status);
     __syncthreads();
     asm volatile("buffer_inv sc0" ::: "memory");                   // drop stale L1 lines (the L2 is shared)
@@ -272,7 +261,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
       for (int rb = 0; rb < RB; ++rb) {
         float t = 0.f;
 #pragma unroll
-        for (int p = 0; p < kParts; ++p) t += s_rows[p * kRows + rb * 32 + lane];
+        for (int p = 0; p < 256 / kRows; ++p) t += s_rows[p * kRows + rb * 32 + lane];
         s_rstd[rb * 32 + lane] = 1.0f / sqrtf(t / (float)a.e.K + a.e.eps);
       }
     }
