@@ -177,10 +177,20 @@ __device__ inline float lane_pair32_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Sum of v over the lanes l, l ^ 16, l ^ 32, l ^ 48, in all of them.
-__device__ inline float lane_quad16_sum(float v) {
+// ... over the lane pair (l, l ^ 16), and over the lanes l, l ^ 16, l ^ 32, l ^ 48, in all of them.
+__device__ inline float lane_pair16_sum(float v) {
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return lane_pair32_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ inline float lane_quad16_sum(float v) { return lane_pair32_sum(lane_pair16_sum(v)); }
+// a's lanes 32 .. 63 change places with b's lanes 0 .. 31.
+__device__ inline void lane_pair32_swap(f32x4_t& a, f32x4_t& b) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a[i]), __float_as_uint(b[i]), false, false);
+    a[i] = __uint_as_float(r[0]);
+    b[i] = __uint_as_float(r[1]);
+  }
 }
 
 // ---- workgroups that share an output along K ---------------------------------------------------

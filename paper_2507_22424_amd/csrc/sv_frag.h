@@ -60,42 +60,37 @@ __device__ inline float silu_fast(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
 }
 
-// The bf16 operand of k-step kk out of one 16-byte weight load of a lane.
-//   WF = 0: the load is the operand (one k-step).
-//   WF = 1: E4M3 codes of two k-steps, one hardware conversion per pair (gfx950; scale 1).  Exact, every E4M3
+// The bf16 operand of k-step kk out of one weight load of a lane (of up to 16 bytes: 1, 2 or 4 k-steps).
+//   WF = 0: the load is the operand.
+//   WF = 1: 8 bytes of E4M3 codes per k-step, one hardware conversion per pair (gfx950; scale 1).  Exact, every E4M3
 //           value is a bf16 value.
-//   WF = 2: integers -8 .. 7 of four k-steps in 4-bit two's complement, one 32-bit word per k-step, value i of a
-//           word in bits 4i .. 4i+3.  v_cvt_off_f32_i4 takes the low four bits of a byte and gives a
-//           sixteenth of the integer; the sixteen is in the packed row scales.  Exact.  (Bit-field
+//   WF = 2: integers -8 .. 7 in 4-bit two's complement, one 32-bit word per k-step, value i of a word in bits
+//           4i .. 4i+3.  v_cvt_off_f32_i4 takes the low four bits of a byte and gives a sixteenth of the integer; the sixteen is in the packed row scales.  Exact.  (Bit-field
 //           extract, integer conversion and a flip of the top bits, as before, are 21 instead of 13
 //           instructions for eight weights, next to four matrix instructions at up to 64 rows.)
 constexpr float kInt4Unit = 16.0f;
-template <int WF>
-__device__ inline bf16x8_t weight_operand(const u32x4_t raw, int kk) {
-  u32x4_t o = raw;
-  if (WF == 1) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j)   // (the half of the word is an immediate)
-      o[j] = __builtin_bit_cast(uint32_t, j & 1 ? __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[2 * kk + j / 2], 1.0f, true)
-                                                : __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[2 * kk + j / 2], 1.0f, false));
-  }
-  if (WF == 2) {
-    const unsigned even = raw[kk];
-    unsigned odd = even >> 4;
-    asm("" : "+v"(odd));          // (else each odd nibble is extracted on its own)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      o[j] = pack_bf16x2(__builtin_amdgcn_cvt_off_f32_i4((int)(even >> (8 * j)) & 0xff), __builtin_amdgcn_cvt_off_f32_i4((int)(odd >> (8 * j)) & 0xff));
-  }
-  return __builtin_bit_cast(bf16x8_t, o);
-}
-
-// The same out of a lane's share of 32 weight rows x 64 k-values, two matrix instructions of 32 k-values: as above,
-// but an int4 lane has the words of its own two k-steps only.
+// Word j (two weights) of it; odd: scratch that the words 0 .. 3 of an operand share (int4: the odd nibbles).
 template <int WF, typename T>
-__device__ inline bf16x8_t weight_half(const T raw, int kk) {
-  if constexpr (WF == 2) return weight_operand<2>(u32x4_t{raw[0], raw[1], 0u, 0u}, kk);
-  else return weight_operand<WF>(raw, kk);
+__device__ inline uint32_t weight_word(const T raw, int kk, int j, unsigned& odd) {
+  if constexpr (WF == 1)        // (the half of the word is an immediate)
+    return j & 1 ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[2 * kk + j / 2], 1.0f, true))
+                 : __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[2 * kk + j / 2], 1.0f, false));
+  if constexpr (WF == 2) {
+    if (j == 0) {
+      odd = raw[kk] >> 4;
+      asm("" : "+v"(odd));      // (else each odd nibble is extracted on its own)
+    }
+    return pack_bf16x2(__builtin_amdgcn_cvt_off_f32_i4((int)(raw[kk] >> (8 * j)) & 0xff), __builtin_amdgcn_cvt_off_f32_i4((int)(odd >> (8 * j)) & 0xff));
+  }
+  return raw[j];
+}
+template <int WF, typename T>
+__device__ inline bf16x8_t weight_operand(const T raw, int kk) {
+  u32x4_t o;
+  unsigned odd = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) o[j] = weight_word<WF>(raw, kk, j, odd);
+  return __builtin_bit_cast(bf16x8_t, o);
 }
 
 // Scheduling barrier that matrix instructions do not cross and everything else does.

@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   typedef typename std::conditional<WF == 2, u32x2_t, u32x4_t>::type wload_t;
   typedef const __attribute__((address_space(1))) wload_t* wptr_t;
   constexpr int CW = WF == 2 ? 1 : 2, WU = WF == 2 ? 2 : 1;    // weight units of a chunk; loads in a 16-byte piece
-  const int g16 = lane >> 4, in_frag = (lane & 15) + 32 * (g16 & 1);
+  const int g16 = lane >> 4, i16 = lane & 15, in_frag = i16 + 32 * (g16 & 1);
   wptr_t wp = (wptr_t)((gptr_t)a.Wp + ((size_t)c0 * CW * n_tiles + t_begin) * 64);
   const unsigned w_row = n_tiles * 64u;
   size_t w_step = (size_t)CW * w_row * WU;
@@ -149,6 +149,8 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
     } else {
       wp = (wptr_t)a.Xs;
       w_step = 0;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) w_off[t] = i16;
     }
   };
   auto put_x = [&](int d, int buf) {
@@ -160,6 +162,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   for (int d = 0; d < D; ++d) {
     issue_x(d);
     issue_w(d);
+    __builtin_amdgcn_sched_barrier(0);                         // (in this order: see skinny_body)
   }
   f32x4_t acc[R][2 * NT];                                      // 16 activation rows x 16 weight rows each
 #pragma unroll
@@ -200,7 +203,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
           else get((e + PD) % (PD + 1), nb, e + PD - E);
           if (r == 0) {
 #pragma unroll
-            for (int t = 0; t < 2 * NT; ++t) w[t] = weight_half<WF>(wr[d][t], kk);
+            for (int t = 0; t < 2 * NT; ++t) w[t] = weight_operand<WF>(wr[d][t], kk);
           }
           // hi and lo of the same rows into the same sums, one after the other, then the next weights: the
           // cheapest order for the power that sets the clock
@@ -244,7 +247,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   f32x4_t* const stage = reinterpret_cast<f32x4_t*>(&lds[0][0]) + lane;
   // item i = tile i % NT of this wave, rows 16 * (i / NT) ..: lane (i16, g) has activation row i16, quad g / 2 of the
   // tile and its partner, quad g / 2 + 2
-  const int h = g16 & 1, p = g16 >> 1, i16 = lane & 15;
+  const int h = g16 & 1, p = g16 >> 1;
   auto item_quad = [&](int i, int qi) -> f32x4_t { return acc[i / NT][2 * (i % NT) + qi]; };
   const int b0 = mid_first(NI, a.lgS, sp), b1 = mid_first(NI, a.lgS, sp + 1);   // this slice's items
   f32x4_t* const own = stage + (size_t)wave * (NQ / 2) * 64;

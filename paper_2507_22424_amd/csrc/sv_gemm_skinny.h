@@ -148,6 +148,9 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   for (int d = 0; d < DX || d < DW; ++d) {
     if (d < DX) issue_x(d);
     if (d < DW) issue_w(d);
+    // (in this order: the waits in the loop hold for both ways into it, so a slot asked for last here would
+    // be waited for as the last one in every round)
+    __builtin_amdgcn_sched_barrier(0);
   }
   f32x16_t acc[NT][RB];
 #pragma unroll
@@ -173,9 +176,13 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
                 acc[t][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, __builtin_bit_cast(bf16x8_t, xr[xs][2 * rb + hl]), acc[t][rb], 0, 0, 0);
           }
         }
+        // (the loads stay where they are: left alone the scheduler moves them to their use, for some forms)
+        __builtin_amdgcn_sched_barrier(0);
         issue_x(xs);
+        __builtin_amdgcn_sched_barrier(0);
       }
       issue_w(d);
+      __builtin_amdgcn_sched_barrier(0);
     }
     left -= DW;
   }

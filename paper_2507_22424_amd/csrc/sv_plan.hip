@@ -136,7 +136,8 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
   } else {
     SkinnyArgs a;
     memset(&a, 0, sizeof(a));
-    const int units = K / (kFragK << wf), waves = 4 << p.lgS;
+    const bool thin = e.M <= kThinRows && p.m_tiles == 1;
+    const int units = K / (thin ? thin_step_k(wf) : kFragK << wf), waves = 4 << p.lgS;
     a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd;
     // Groups end at half tiles where that makes the largest group smaller, the weight bytes set the time (up to
     // 32 rows of bf16 weights) and nothing is written per tile (the residual's row sums are).  7B, gate/up, 5.375 tiles
@@ -151,7 +152,7 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
     a.gcap = kMaxGroups / n_xcd;
     a.e = e;
     auto* launch = epi == EPI_QKV ? launch_skinny_qkv : (epi == EPI_RESID ? launch_skinny_resid : (epi == EPI_SWIGLU ? launch_skinny_swiglu : launch_skinny_out));
-    launch(a, p.rb, p.nt, wf, grid, st);
+    launch(a, thin ? 0 : p.rb, p.nt, wf, grid, st);
   }
 }
 

@@ -5,6 +5,7 @@
 
 #include "sv_gemm_mid.h"
 #include "sv_gemm_skinny.h"
+#include "sv_gemm_thin.h"
 
 namespace sv {
 
@@ -31,7 +32,7 @@ struct ProductScratch {
 void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint4* Xs, const uint4* Wp, int N, int K,
                     const ProductScratch& s, const EpiArgs& e, hipStream_t st);
 
-// one function per kernel family and epilogue, each in its own source file
+// one function per kernel family and epilogue, each in its own source file (skinny: rb = 0 is gemm_thin)
 void launch_skinny_qkv(const SkinnyArgs& a, int rb, int nt, int wf, dim3 grid, hipStream_t st);
 void launch_skinny_resid(const SkinnyArgs& a, int rb, int nt, int wf, dim3 grid, hipStream_t st);
 void launch_skinny_swiglu(const SkinnyArgs& a, int rb, int nt, int wf, dim3 grid, hipStream_t st);
@@ -55,8 +56,18 @@ void launch_mid_out(const MidArgs& a, int rb, int nt, int wf, dim3 grid, hipStre
     else if (rb == 3) tiles<3, WF>(a, nt, grid, st);                                                           \
     else tiles<4, WF>(a, nt, grid, st);                                                                        \
   }                                                                                                            \
+  template <int WF>                                                                                            \
+  static void thin(const SkinnyArgs& a, int nt, dim3 grid, hipStream_t st) {                                   \
+    if (nt == 2) gemm_thin<2, EPI, WF><<<grid, 256, 0, st>>>(a);                                               \
+    else if (nt <= 4) gemm_thin<4, EPI, WF><<<grid, 256, 0, st>>>(a);                                          \
+    else gemm_thin<6, EPI, WF><<<grid, 256, 0, st>>>(a);                                                       \
+  }                                                                                                            \
   void NAME(const SkinnyArgs& a, int rb, int nt, int wf, dim3 grid, hipStream_t st) {                          \
-    if (FORMATS > 2 && wf == 2) rows<(FORMATS > 2 ? 2 : 0)>(a, rb, nt, grid, st);                              \
+    if (rb == 0) {                                                                                             \
+      if (FORMATS > 2 && wf == 2) thin<(FORMATS > 2 ? 2 : 0)>(a, nt, grid, st);                                \
+      else if (FORMATS > 1 && wf == 1) thin<(FORMATS > 1 ? 1 : 0)>(a, nt, grid, st);                           \
+      else thin<0>(a, nt, grid, st);                                                                           \
+    } else if (FORMATS > 2 && wf == 2) rows<(FORMATS > 2 ? 2 : 0)>(a, rb, nt, grid, st);                              \
     else if (FORMATS > 1 && wf == 1) rows<(FORMATS > 1 ? 1 : 0)>(a, rb, nt, grid, st);                         \
     else rows<0>(a, rb, nt, grid, st);                                                                         \
   }
