@@ -36,10 +36,10 @@ static ProductPlan plan_skinny(int M, int N, int K, int n_xcd) {
 }
 
 // gemm_mid: every (row blocks, tiles, slices) it has is priced and the cheapest taken.  Fitted to sweeps of
-// all of them on the 7B shapes at 70 - 960 rows: with every CU busy a k-step takes
-// RB * (0.042 * NT + 0.020) us (the second term: LDS reads of the activations), at least what HBM takes for
-// the weights; a round of workgroups adds 11 us around its loop and 0.12 us per KiB of sums a workgroup
-// hands to the others.
+// all of them on the 7B shapes at 70 - 960 rows, so that what is taken is on average within 0.5 % of the fastest: with
+// every CU busy a k-step takes RB * (0.036 * NT + 0.036) us (the second term: what does not depend on the tiles, LDS
+// reads of the activations among it), at least what HBM takes for the weights; a round of workgroups adds 11.4 us
+// around its loop and 0.13 us per KiB of sums a workgroup hands to the others.
 static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
   const int tiles = N / kFragRows, tiles_x = ceil_div(tiles, n_xcd), n_rb = ceil_div(M, 32), nks = K / kFragK;
   const double w_bytes = (double)N * K * 2 / (1 << wf);
@@ -59,10 +59,10 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
         if (lgS > 0 && p.gpx * p.m_tiles > kMaxGroups / n_xcd) continue;
         const int rounds = ceil_div(p.wg_x, kCusPerXcd);
         const double steps = (double)nks / (1 << lgS), kib = 16.0 * rb * nt * ((1 << lgS) - 1) / (1 << lgS);
-        double loop = rounds * steps * rb * (0.042 * nt + 0.020);
-        const double hbm = w_bytes / 5.8e6;
+        double loop = rounds * steps * rb * (0.036 * nt + 0.036);
+        const double hbm = w_bytes / 6.4e6;
         if (loop < hbm) loop = hbm;
-        const double us = loop + rounds * (11.0 + 0.12 * kib);
+        const double us = loop + rounds * (11.4 + 0.13 * kib);
         if (us < best_us) {
           best_us = us;
           best = p;
@@ -75,15 +75,19 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
   return best;
 }
 
-// Rows the kernels split at.  Up to 128 gemm_skinny, unless its groups of few tiles would make more than one
-// round of the chip (us, o / down / qkv / gate+up on the 7B shapes: 70 rows 18.1 / 34.3 / 36.8 / 54.8
-// against gemm_mid's 19.6 / 34.0 / 40.7 / 60.2; 128 rows 20.5 / 39.3 / 45.6 / 62.5 against 22.6 / 40.4 /
-// 45.4 / 66.7; a gemm_skinny of five row blocks, not kept, took 24.1 / 45.5 / 54.7 / 100 at 150 rows against
-// 26.6 / 46.0 / 54.1 / 79.2).
+// Rows the kernels split at.  Up to 64 gemm_skinny (with rows <= 16 left out: gemm_thin).  Up to 128 gemm_skinny unless
+// its groups of few tiles would make more than one round of the chip, or would read too much: every group reads all
+// activations, at 14 TB/s next to the weights, gemm_mid's blocks a quarter of that.  bf16 weights, 7B shapes,
+// MB of activations read by gemm_skinny, us of gemm_skinny / gemm_mid: 96 rows o 100 15.0 / 15.8, q,k,v 201 34.2 / 31.6,
+// down 270 30.3 / 27.1, gate+up 360 52.7 / 45.5; 128 rows o 134 17.5 / 18.2, q,k,v 268 37.2 / 38.2, down 360 35.0 / 31.6,
+// gate+up 480 59.0 / 55.6.  Coded weights: gemm_mid is slower throughout (8 bits, 100 rows: gate+up 47.4 / 55.2, q,k,v
+// 31.4 / 37.3, down 29.9 / 30.3).
 ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd) {
   if (M <= kSkinnyMaxRows) {
     const ProductPlan p = plan_skinny(M, N, K, n_xcd);
-    if (M <= 64 || p.wg_x <= kCusPerXcd) return p;
+    const double mb = (double)n_xcd * p.wg_x * (K >> p.lgS) * p.rb * kFragRows * 4 / 1e6;
+    const bool wide = wf == 0 && mb > (p.rb == 3 ? 150 : 310);
+    if (M <= 64 || (p.wg_x <= kCusPerXcd && !wide)) return p;
   }
   return plan_mid(M, N, K, wf, n_xcd);
 }

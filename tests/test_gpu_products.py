@@ -83,7 +83,7 @@ def test_one_7b_layer_in_every_form_of_its_products(dtype, B, T):
 
 
 # rows of the packed head over the whole vocabulary, likewise
-WIDE_HEAD = [1, 60, 65, 97, 150, 161, 240, 300, 780]
+WIDE_HEAD = [1, 60, 65, 97, 150, 161, 240, 300, 400, 780]
 
 
 def test_full_vocabulary_head_in_every_form_of_its_product():
@@ -191,3 +191,19 @@ def test_commit_of_deep_paths_and_unaligned_caches(dtype, d, shift):
                 want[b, :, prefix[b] + i] = want[b, :, prefix[b] + path[b, i]].clone()
         assert torch.equal(t[shift:shift + n].cpu().reshape(B, nh, cap, d), want)
         assert not t[:shift].any() and not t[shift + n:].any()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "bf16_w8", "bf16_w4"])
+@pytest.mark.parametrize("T,B,H,F", [(16, 1, 1024, 2816), (15, 1, 512, 768), (4, 4, 1024, 2304), (17, 1, 1024, 2304), (1, 1, 512, 1280)])
+def test_up_to_16_rows(dtype, T, B, H, F):
+    """Both sides of the row count up to which half of the rows is left out; K slices shorter than the rings (512), odd
+    numbers of steps per wave, groups that end at half tiles (2304)."""
+    cfg = wl.C2.scaled(name=f"thin-{dtype}-{B}x{T}-{H}-{F}", index=60 + B, dtype=dtype, n_layers=2, hidden=H, n_heads=H // 128,
+                       head_dim=128, mlp_dim=F, vocab=1024, n_bins=256, tree_nodes=T, n_episodes=B, prefix_lo=20, prefix_hi=30,
+                       max_children=6, spine_lo=min(3, T - 1), r_values=(0, 4))
+    check_forward(SideBySide(cfg, store=bf16_store, stack_tol=TOL), TOL, TOL_ATTN)
+
+
+@pytest.mark.parametrize("dtype,T", [("bf16", 1), ("bf16", 16), ("bf16_w8", 16), ("bf16_w4", 1), ("bf16_w4", 16)])
+def test_one_7b_layer_of_up_to_16_rows(dtype, T):
+    test_one_7b_layer_in_every_form_of_its_products(dtype, 1, T)
