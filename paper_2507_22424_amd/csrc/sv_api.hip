@@ -122,8 +122,8 @@ static WorkspaceLayout workspace_layout(const sv_model_cfg& c, int m_rows, int n
     L.head_ssq = o; o = align_up(o + (size_t)L.m_pad * (H / 256) * 4, kAlign);
     L.head_xch = o; o = align_up(o + xch, kAlign);
   }
-  // (Once gemm_mid's ring has used up its weights it goes on reading behind its fragments, a KiB per weight tile at
-  // most: that lies inside the exchange region, which has 12 KiB per tile and more.)
+  // (Once a product's ring has used up its weights it goes on reading the first of its activation fragments, a KiB per
+  // weight tile of the workgroup: twelve at most, and the fragments of 32 rows have 32 KiB and more.)
   L.total = o;
   return L;
 }

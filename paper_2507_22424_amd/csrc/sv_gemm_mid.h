@@ -117,11 +117,8 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   const int g16 = lane >> 4, i16 = lane & 15, in_frag = i16 + 32 * (g16 & 1);
   wptr_t wp = (wptr_t)((gptr_t)a.Wp + ((size_t)c0 * CW * n_tiles + t_begin) * 64);
   const unsigned w_row = n_tiles * 64u;
-  size_t w_step = (size_t)CW * w_row * WU;
-  unsigned w_off[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)       // (beyond the group's tiles: the last one again, dropped at the end)
-    w_off[t] = ((unsigned)min(wave * NT + t, t_count - 1) * 64u + in_frag) * WU + (WF == 2 ? g16 >> 1 : (g16 >> 1) * w_row);
+  const size_t w_step = (size_t)CW * w_row * WU;
+  unsigned w_lane = in_frag * WU + (WF == 2 ? g16 >> 1 : (g16 >> 1) * w_row);
   gptr_t xp = (gptr_t)a.Xs + (size_t)c0 * CK * a.e.n_rb * 128;
   const unsigned x_step = CK * a.e.n_rb * 128u;
   unsigned x_off[LX];
@@ -143,15 +140,13 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   };
   auto issue_w = [&](int d) {
 #pragma unroll
-    for (int t = 0; t < 2 * NT; ++t) wr[d][t] = __builtin_nontemporal_load(wp + (w_off[t / 2] + (t & 1) * 16 * WU));
-    if (--wl > 0) {
-      wp += w_step;
-    } else {
-      wp = (wptr_t)a.Xs;
-      w_step = 0;
-#pragma unroll
-      for (int t = 0; t < NT; ++t) w_off[t] = i16;
+    for (int t = 0; t < 2 * NT; ++t) {   // (beyond the group's tiles: the last one again, dropped at the end)
+      const unsigned piece = (min(wave * NT + t / 2, t_count - 1) * 64u + (t & 1) * 16u) * WU;
+      wr[d][t] = __builtin_nontemporal_load(wp + piece + w_lane);
     }
+    const bool more = --wl > 0;
+    wp = more ? wp + w_step : (wptr_t)a.Xs;
+    w_lane = more ? w_lane : (unsigned)i16;
   };
   auto put_x = [&](int d, int buf) {
 #pragma unroll
