@@ -109,6 +109,10 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   const int u0 = ws * a.uq + min(ws, a.urem);
   const int n_units = a.uq + (ws < a.urem ? 1 : 0);
 
+  constexpr int kRows = RB * 32;
+  SsqSums<kRows, (EPI == EPI_OUT ? 8 : (RB > 2 ? 64 : 32))> rows(a.e, EPI == EPI_OUT ? m0 : 0, tid);
+  if (EPI == EPI_OUT) rows.request();
+
   // Rings.  Every step issues exactly as many loads as it has used - from the activations' first fragments,
   // which the caches hold, once nothing is left - so that the number of younger loads behind any slot is
   // a compile-time constant and the waits are exact.
@@ -189,10 +193,8 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
 
   // What the epilogue needs to know of the rows: row sums of x^2 - thread (row, part) adds its share of the
   // planes - and rotary positions.  Requested here, answered while the sums meet.  (Requested and waited for
-  // ahead of the loop they held it up by 2.5 us, by 9 us at 128 rows.)
-  constexpr int kRows = RB * 32;
-  SsqSums<kRows, (RB > 2 ? 64 : 32)> rows(a.e, EPI == EPI_OUT ? m0 : 0, tid);
-  if (EPI != EPI_RESID) rows.request();
+  // ahead of the loop they held it up by 2.5 us, by 9 us at 128 rows.  The head's few planes are requested there.)
+  if (epi_pairs(EPI)) rows.request();
   EpiRow er;
   if (EPI == EPI_QKV) er = epi_row_fetch(a.e, min(tid % kRows, a.e.M - 1));
 
