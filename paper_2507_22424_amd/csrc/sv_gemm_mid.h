@@ -1,16 +1,17 @@
 // The layer's products for more than 128 rows of activations.
 //
-// With this many rows the matrix cores set the time, at the clock they hold on real data: in their main
-// loop these kernels issue 1.3 - 1.4 PFLOP/s (hi and lo half of the activations counted), above what a
-// large bf16 product of the vendor's library sustains on the same card (1.16).  What is left to lose is
-// around the loop and in work on rows that do not exist (7B layer of 150 rows: 305 us for the four products
-// and their helper launches before, 207 now; 960 rows: 775 and 775), hence:
+// With this many rows the matrix cores set the time, at the clock that their power leaves on real data.  On random
+// data, all CUs, nothing but matrix instructions, v_mfma_f32_32x32x16_bf16 sustains 1.75 - 1.8 PFLOP/s in any order of
+// its operands, 16x16x32 1.7 with the weight tiles outermost, 2.06 with the rows outermost, 2.25 where besides both
+// parts of a row are added to the same sums one after the other; hence that instruction in that order.  The main
+// loop issues 1.5 PFLOP/s (hi and lo half of the activations counted; 1.35 with 32x32x16), a large bf16 product of the
+// vendor's library 1.16 on the same card.  What is left to lose is around the loop and in work on rows that do not
+// exist (7B layer, four products and attention: 3 x 50 rows 210 us with 32x32x16, 194 now; 16 x 60 rows 787, 705), hence:
 //   * blocks of RB = 3, 4 or 5 row blocks of 32 rows x 4 waves x NT weight tiles; the host weighs rows that
-//     are only padding against whole rounds of the chip (150 rows: 160 are multiplied in the down projection,
-//     192 in the other three: two blocks of 3 fill the chip with half the K slices, and so less exchange, than
-//     one of 5 would need);
+//     are only padding against whole rounds of the chip (150 rows: 192 are multiplied, two blocks of 3, which fill
+//     the chip with half the K slices, and so less exchange, than one of 5 would need);
 //   * a weight tile belongs to one wave: its fragments go from memory straight into operand registers,
-//     through a ring of D chunks.  The activations of a chunk (two k-steps; four with 4-bit weights) are
+//     through a ring of D chunks.  The activations of a chunk (two k-steps; four with coded weights) are
 //     fetched once per workgroup, each wave loading a quarter of the fragments into registers and writing
 //     them to LDS one chunk ahead of their use; one barrier per chunk, three LDS buffers.  Every load is
 //     one the compiler knows of, in a fixed order, so its waits are exact;
