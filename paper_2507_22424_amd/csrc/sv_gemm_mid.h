@@ -83,6 +83,11 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   typedef MidShape<RB, NT, WF> Sh;
   constexpr int KK = Sh::KK, CK = Sh::CK, LX = Sh::LX, D = Sh::D, R = 2 * RB;
   constexpr int E = KK * R, PD = NT == 1 ? 4 : 2;              // steps (16 rows) of a chunk; operands are read PD steps ahead
+  // LDS operations end in order: a wave's writes of the next chunk have ended once no more operations are under way
+  // than the reads that it has issued behind them, two for each of the E - PD steps up to the barrier.  A wait for
+  // 2 * PD of them, all that are needed later, covers the writes only if that is no more (RB = 3, NT = 1: 4, not 8).
+  constexpr int kBehind = 2 * (E - PD), kUnderWay = 2 * PD < kBehind ? 2 * PD : kBehind;
+  static_assert(E > PD && kUnderWay <= kBehind && kUnderWay <= 15, "the barrier's wait has to cover the LDS writes");
   constexpr int kChunk = CK * RB * 2;                          // activation fragments of a chunk
   constexpr bool PAIR = epi_pairs(EPI);
   constexpr int NI = mid_items(RB, NT), NQ = 2 * NI;           // items, quads of a wave
@@ -193,8 +198,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const int kk = e / R, r = e % R;
-          // (own LDS writes are older than the 2 * PD reads that may still be under way)
-          if (e == E - PD) asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(2 * PD) : "memory");
+          if (e == E - PD) asm volatile("s_waitcnt lgkmcnt(%0)\n\ts_barrier" ::"n"(kUnderWay) : "memory");
           if (e + PD < E) get((e + PD) % (PD + 1), buf, e + PD);
           else get((e + PD) % (PD + 1), nb, e + PD - E);
           if (r == 0) {
