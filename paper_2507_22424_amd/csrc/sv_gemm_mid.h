@@ -62,18 +62,23 @@ constexpr int mid_planes(int rb, int nt, int lgS) {
 // float4 a workgroup may send (4 waves, padded so that the regions do not share memory channels)
 constexpr int mid_unit_stride(int rb, int nt) { return (4 * (rb * nt * 4 + 1) + 5) * 64; }
 
-// A chunk is KK matrix instructions deep (32 k-values each): one with bf16 weights, two with codes.
+// A chunk is KK matrix instructions deep (32 k-values each): one with bf16 weights, two with codes - but one for E4M3
+// where accumulators (240 of 512 registers) and a ring of two such chunks leave too little for the operands:
+// gemm_mid<5, 3, *, 1> then kept 300 registers in scratch memory, 7B, 8 bits, us a layer of 300 / 600 / 1800 rows
+// 538 / 1236 / 2910, 279 / 454 / 1274 with one.  Elsewhere two are faster (400 rows 370 / 383, 960 rows 692 / 700).
+constexpr int mid_kk(int rb, int nt, int wf) { return wf == 2 || (wf == 1 && rb * nt < 15) ? 2 : 1; }
+constexpr int mid_chunk_k(int rb, int nt, int wf) { return 32 * mid_kk(rb, nt, wf); }
 template <int RB, int NT, int WF>
 struct MidShape {
-  static constexpr int KK = WF ? 2 : 1, CK = 2 * KK;           // matrix instructions, k-steps of a chunk
+  static constexpr int KK = mid_kk(RB, NT, WF), CK = 2 * KK;   // matrix instructions, k-steps of a chunk
+  static constexpr int CW = CK >> WF, WU = 2 / CW;             // weight units of a chunk; loads in a 16-byte piece
   static constexpr int LW = 2 * NT, LX = CK * RB / 2;          // loads of a wave per chunk
   // chunks in flight: what the load counter (63) and the registers hold, 12 k-steps at most
-  static constexpr int kCnt = 60 / (LW + LX), kReg = (416 - 16 * RB * NT) / (4 * LX + (WF == 2 ? 2 : 4) * LW);
+  static constexpr int kCnt = 60 / (LW + LX), kReg = (416 - 16 * RB * NT) / (4 * LX + 4 / WU * LW);
   static constexpr int D0 = kCnt < kReg ? kCnt : kReg;
   static constexpr int D = D0 > 12 / CK ? 12 / CK : D0;
   static_assert(D >= 2, "ring too short");
 };
-constexpr int mid_chunk_k(int wf) { return wf ? 64 : 32; }
 
 // grid = (n_xcd, gpx * m_tiles * S), block = 256, one workgroup per CU: x is the XCD; in y the S slices of
 // an output block follow each other, then the blocks of rows of a column group, which read the same
@@ -114,17 +119,17 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
 
   // Lane (i, g) = (lane % 16, lane / 16) of v_mfma_f32_16x16x32_bf16 holds eight k-values of weight row (or
   // activation row) i.  Out of the 32-row fragments: k-half g % 2 of k-step KK * (g / 2) + kk, whichever way round
-  // as long as both operands agree.  Coded weights: a 16-byte piece covers two k-steps (E4M3) or four (int4,
-  // of which a lane fetches its two).
+  // as long as both operands agree.  Coded weights: a 16-byte piece covers two k-steps (E4M3) or four (int4);
+  // where it is all that a chunk takes (CW = 1), a lane fetches its half of it.
   typedef const __attribute__((address_space(1))) u32x4_t* gptr_t;
-  typedef typename std::conditional<WF == 2, u32x2_t, u32x4_t>::type wload_t;
+  typedef typename std::conditional<Sh::WU == 2, u32x2_t, u32x4_t>::type wload_t;
   typedef const __attribute__((address_space(1))) wload_t* wptr_t;
-  constexpr int CW = WF == 2 ? 1 : 2, WU = WF == 2 ? 2 : 1;    // weight units of a chunk; loads in a 16-byte piece
+  constexpr int CW = Sh::CW, WU = Sh::WU;
   const int g16 = lane >> 4, i16 = lane & 15, in_frag = i16 + 32 * (g16 & 1);
   wptr_t wp = (wptr_t)((gptr_t)a.Wp + ((size_t)c0 * CW * n_tiles + t_begin) * 64);
   const unsigned w_row = n_tiles * 64u;
   const size_t w_step = (size_t)CW * w_row * WU;
-  unsigned w_lane = in_frag * WU + (WF == 2 ? g16 >> 1 : (g16 >> 1) * w_row);
+  unsigned w_lane = in_frag * WU + (WU == 2 ? g16 >> 1 : (g16 >> 1) * w_row);
   gptr_t xp = (gptr_t)a.Xs + (size_t)c0 * CK * a.e.n_rb * 128;
   const unsigned x_step = CK * a.e.n_rb * 128u;
   unsigned x_off[LX];

@@ -49,7 +49,7 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
   for (int rb = 3; rb <= kMidMaxRows; ++rb)
     for (int nt = 1; nt <= kMidMaxTiles; ++nt)
       for (int lgS = 0; lgS <= 3; ++lgS) {
-        if (lgS > 0 && K / mid_chunk_k(wf) < (4 << lgS)) continue;
+        if (lgS > 0 && K / mid_chunk_k(rb, nt, wf) < (4 << lgS)) continue;
         ProductPlan p;
         memset(&p, 0, sizeof(p));
         p.mid = true; p.rb = rb; p.nt = nt; p.lgS = lgS;
@@ -127,7 +127,7 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
   if (p.mid) {
     MidArgs a;
     memset(&a, 0, sizeof(a));
-    const int chunks = K / mid_chunk_k(wf);
+    const int chunks = K / mid_chunk_k(p.rb, p.nt, wf);
     a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd; a.m_tiles = p.m_tiles;
     a.tq = tiles / groups; a.trem = tiles % groups;
     a.cq = chunks >> p.lgS; a.crem = chunks & ((1 << p.lgS) - 1);

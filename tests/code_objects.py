@@ -54,3 +54,12 @@ def instructions():
             lines = re.findall(r"^\t(\S.*?)\s*// ([0-9A-F]+): [0-9A-F ]+(?:<\S+?(?:\+0x([0-9a-f]+))?>)?\s*$", body, re.M)
             start = int(lines[0][1], 16) if lines else 0
             yield short_name(symbol), [(int(a, 16), op, start + int(t or "0", 16) if "branch" in op else None) for op, a, t in lines]
+
+
+def scratch_bytes():
+    """Of every kernel: (name, bytes of scratch memory a lane needs)."""
+    for text in _tool("llvm-readelf", "--notes"):
+        for part in re.split(r"^  - ", text, flags=re.M):
+            symbol = re.search(r"^\s+\.symbol:\s+(\S+)\.kd$", part, re.M)
+            if symbol:
+                yield short_name(symbol[1]), int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", part)[1])

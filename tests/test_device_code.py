@@ -57,3 +57,10 @@ def test_lds_writes_end_before_the_barrier_that_publishes_them():
             bad[name] = n
     assert {"gemm_mid", "gemm_skinny", "gemm_thin", "tree_attention_mfma", "f32_product", "tree_build_kernel"} <= seen
     assert not bad
+
+
+def test_no_kernel_keeps_registers_in_memory():
+    """Scratch memory means spilled registers, whose loads also come between those that the product kernels count."""
+    used = dict(co.scratch_bytes())
+    assert {n.split("<")[0] for n in used} >= {"gemm_mid", "gemm_skinny", "gemm_thin", "tree_attention_mfma", "f32_product"}
+    assert not {n: b for n, b in used.items() if b}

@@ -63,15 +63,15 @@ def test_every_finite_e4m3_code(T, B, monkeypatch):
 
 
 # One layer of the 7B shape.  Episodes and nodes for which the planner gives each product, up to 960 rows of bf16
-# weights and 240 of the others, every form it has (tests/test_plan_coverage.py holds the lists to that).
+# weights and 640 of the others, every form it has (tests/test_plan_coverage.py holds the lists to that).
 # Here the softmax often picks one key, and 4096 terms make large keys: appended values that round to the
 # neighbour of the oracle's (0.1 - 1 % of them, after 1e-6 .. 1e-5 of error) move x by up to 3.5e-4 and the logits
 # by 3.7e-4 in an emulation; dropping the low parts 3.3e-3 and 4.3e-3.
 TOL_WIDE = 8e-4
 TOL_WIDE_ATTN = 2.0 ** -7        # a picked value passes whole: one unit in its last place
 WIDE_LAYERS = {"bf16": [(1, 65), (3, 50), (7, 23), (4, 60), (5, 60), (3, 107), (5, 77), (13, 37), (9, 57), (6, 107), (10, 77)],
-               "bf16_w8": [(1, 65), (1, 128), (3, 50), (7, 23), (4, 60)],
-               "bf16_w4": [(1, 65), (1, 128), (3, 50), (7, 23), (4, 60)]}
+               "bf16_w8": [(1, 65), (1, 128), (3, 50), (7, 23), (4, 60), (3, 93), (3, 107), (5, 77), (13, 37), (9, 57)],
+               "bf16_w4": [(1, 65), (1, 128), (3, 50), (7, 23), (4, 60), (3, 93), (3, 107), (5, 77), (13, 37), (9, 57)]}
 WIDE_ELSEWHERE = {"bf16": [26, 60, 128, 960], "bf16_w8": [26, 60], "bf16_w4": [26, 60]}   # rows, in test_gpu_parity.py
 
 
