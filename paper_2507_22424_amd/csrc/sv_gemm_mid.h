@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256, 1) void gemm_mid(const MidArgs a) {
   for (int d = 0; d < D; ++d) {
     issue_x(d);
     issue_w(d);
-    __builtin_amdgcn_sched_barrier(0);                         // (in this order: see skinny_body)
+    __builtin_amdgcn_sched_barrier(0);                         // (in this order: see SkinnyRing)
   }
   f32x4_t acc[R][2 * NT];                                      // 16 activation rows x 16 weight rows each
 #pragma unroll

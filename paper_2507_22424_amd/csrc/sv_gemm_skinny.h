@@ -84,6 +84,12 @@ struct SkinnyRing {
   static constexpr int DW = WF == 2 ? 2 : (kFit > kMost ? kMost : kFit);
   static constexpr int DX = WF == 2 ? (RB > 2 ? 4 : 8) : DW * UK;
   static_assert(DW >= 2 && (DW * UK) % DX == 0, "ring");
+  // Whether the loads ahead of the loop keep their order: the waits in the loop hold for both ways into it, so a slot
+  // asked for last there is waited for as the last one in every round; against that stands what the scheduler gains by
+  // mixing them with the set-up.  us of a layer, scheduler's order / this: 8 bits, 32 rows 7B 83.9 / 80.9, H = 5120
+  // 106.1 / 99.8; 4 bits 32 rows H = 5120 92.1 / 87.6, 96 rows 7B 123.0 / 116.5; but bf16, 60 rows 7B 119.9 / 127.5,
+  // H = 2048 69.2 / 72.3; 8 bits 33 - 128 rows the same within 1 %.
+  static constexpr bool kInOrder = WF == 2 || (WF == 1 && RB == 1);
 };
 
 template <int RB, int NT, int EPI, int WF>
@@ -152,9 +158,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   for (int d = 0; d < DX || d < DW; ++d) {
     if (d < DX) issue_x(d);
     if (d < DW) issue_w(d);
-    // (in this order: the waits in the loop hold for both ways into it, so a slot asked for last here would
-    // be waited for as the last one in every round)
-    __builtin_amdgcn_sched_barrier(0);
+    if (Ring::kInOrder) __builtin_amdgcn_sched_barrier(0);
   }
   f32x16_t acc[NT][RB];
 #pragma unroll
@@ -180,13 +184,9 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
                 acc[t][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, __builtin_bit_cast(bf16x8_t, xr[xs][2 * rb + hl]), acc[t][rb], 0, 0, 0);
           }
         }
-        // (the loads stay where they are: left alone the scheduler moves them to their use, for some forms)
-        __builtin_amdgcn_sched_barrier(0);
         issue_x(xs);
-        __builtin_amdgcn_sched_barrier(0);
       }
       issue_w(d);
-      __builtin_amdgcn_sched_barrier(0);
     }
     left -= DW;
   }

@@ -107,7 +107,7 @@ __device__ __forceinline__ void thin_body(const SkinnyArgs& a, f32x4_t* lds, flo
 #pragma unroll
     for (int t = 0; t < 2 * NT; ++t) issue_w(d, t);
     next_w();
-    __builtin_amdgcn_sched_barrier(0);                    // (in this order: see skinny_body)
+    __builtin_amdgcn_sched_barrier(0);                    // (in this order: see SkinnyRing)
   }
 
   f32x4_t acc[2 * NT];                                    // 16 activation rows x 16 weight rows each
