@@ -49,7 +49,9 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
   for (int rb = 3; rb <= kMidMaxRows; ++rb)
     for (int nt = 1; nt <= kMidMaxTiles; ++nt)
       for (int lgS = 0; lgS <= 3; ++lgS) {
-        if (lgS > 0 && K / mid_chunk_k(rb, nt, wf) < (4 << lgS)) continue;
+        // at least 128 k-values a slice (4-bit weights 256); 256 for 8-bit weights too, whose chunk is 64, cost H = 512,
+        // 400 rows, 5 % of a layer (63.3 / 66.6 us)
+        if (lgS > 0 && K < ((wf == 2 ? 256 : 128) << lgS)) continue;
         ProductPlan p;
         memset(&p, 0, sizeof(p));
         p.mid = true; p.rb = rb; p.nt = nt; p.lgS = lgS;

@@ -30,6 +30,8 @@ TOL_ATTN = 2e-3
     ("bf16", 65, 1, 1024, 2816), ("bf16", 96, 1, 512, 768), ("bf16", 97, 1, 1024, 2816), ("bf16", 64, 2, 512, 1280),
     ("bf16", 43, 3, 1024, 2816), ("bf16", 80, 2, 512, 768), ("bf16", 23, 7, 1024, 2816), ("bf16", 64, 5, 512, 1280),
     ("bf16_w8", 1, 1, 512, 768), ("bf16_w8", 64, 1, 1024, 2816), ("bf16_w8", 97, 1, 512, 1280), ("bf16_w8", 43, 3, 1024, 2816),
+    # two chunks of 64 k-values in a slice
+    ("bf16_w8", 64, 5, 512, 1280), ("bf16_w8", 64, 4, 1024, 2816),
     # gate/up groups of 2.25 weight tiles: they end at half tiles (not at 33 rows)
     ("bf16", 1, 1, 1024, 2304), ("bf16", 32, 1, 1024, 2304), ("bf16", 8, 3, 1024, 2304), ("bf16", 33, 1, 1024, 2304),
     ("bf16_w4", 1, 1, 512, 768), ("bf16_w4", 64, 1, 1024, 2816), ("bf16_w4", 97, 1, 512, 1280), ("bf16_w4", 43, 3, 1024, 2816),

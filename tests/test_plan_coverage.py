@@ -34,6 +34,15 @@ def test_every_form_of_the_heads_product_has_a_test():
     assert {_head_form(M, 32000) for M in range(1, 961)} <= {_head_form(M, 32000) for M in WIDE_HEAD}
 
 
+@pytest.mark.parametrize("H,F", [(512, 1536), (1024, 2816)])
+def test_8_bit_weights_split_along_k_as_far_as_bf16_weights(H, F):
+    cfgs = [sv.model_cfg(dtype, H, H // 128, 128, F, 1024) for dtype in ("bf16", "bf16_w8")]
+    for rows in range(129, 961):
+        for which in LAYER:
+            bf16, w8 = (sv.sv_product_plan(c, rows, which)[3] for c in cfgs)
+            assert w8 >= bf16, (rows, which)
+
+
 def test_the_timed_cases_lie_in_the_range_that_is_tested():
     for case in cases.listed():
         rows = case["episodes"] * case["nodes"]
