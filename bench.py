@@ -301,7 +301,7 @@ def main():
     n_xcd = max(1, min(8, torch.cuda.get_device_properties(0).multi_processor_count // 32))
     plans = {k: sv.sv_product_plan(vp.cfg, M, which, n_xcd=n_xcd)
              for k, which in (("qkv", sv.SV_PLAN_QKV), ("o", sv.SV_PLAN_OUT), ("gate_up", sv.SV_PLAN_GATE_UP), ("down", sv.SV_PLAN_DOWN))}
-    rows_issued = {k: 32 * p[1] * p[5] for k, p in plans.items()}
+    rows_issued = {k: 16 if p[0] == sv.SV_KERNEL_THIN else 32 * p[1] * p[5] for k, p in plans.items()}
     issued_flops = 2.0 * L * sum(gemm_flops[k] * rows_issued[k] / M for k in plans)
     mfma_tflops = issued_flops / (gemm_ms_raw * 1e-3) / 1e12
     kv_bytes = sum(2 * cfg.n_heads * (int(p) + T) * cfg.head_dim * 2 for p in prefix_len)   # all episodes, one layer

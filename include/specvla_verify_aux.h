@@ -28,10 +28,10 @@ int sv_workspace_region(const sv_model_cfg *cfg, int B, int T, int n_scored, int
 
 /* Host-only inspection aid for tests and benchmarks: how a product of a bf16 model is split over a device of
  * n_xcd XCDs (1 .. 8) for n_rows rows of activations.  which: SV_PLAN_*; n_scored: rows of the packed head
- * (SV_PLAN_HEAD only).  plan: [host, out] int32[6]: kernel (0 gemm_skinny, 1 gemm_mid), 32-row blocks of
- * activations a workgroup multiplies, weight tiles of the kernel instance (per workgroup, gemm_mid: per wave),
- * slices along K, column groups per XCD, workgroups that share the rows of a column group out.  Rows multiplied,
- * padding included: 32 * plan[1] * plan[5].
+ * (SV_PLAN_HEAD only).  plan: [host, out] int32[6]: kernel (0 gemm_skinny, 1 gemm_mid, 2 gemm_thin), 32-row
+ * blocks of activations a workgroup multiplies (gemm_thin: half of the one), weight tiles of the kernel instance (per
+ * workgroup, gemm_mid: per wave), slices along K, column groups per XCD, workgroups that share the rows of a column
+ * group out.  Rows multiplied, padding included: 32 * plan[1] * plan[5], gemm_thin: 16.
  * SV_ERR_DTYPE for SV_F32, SV_ERR_SHAPE for other sizes out of range. */
 #define SV_PLAN_QKV 0
 #define SV_PLAN_OUT 1

@@ -31,6 +31,7 @@ EXPORTS = ("sv_version", "sv_strerror", "sv_tree_build_masks", "sv_packed_layer_
            "sv_commit_path", "sv_advance_prefix", "sv_tree_build_device")
 SV_N_TIMING_EVENTS = 9
 SV_PLAN_QKV, SV_PLAN_OUT, SV_PLAN_GATE_UP, SV_PLAN_DOWN, SV_PLAN_HEAD = range(5)
+SV_KERNEL_SKINNY, SV_KERNEL_MID, SV_KERNEL_THIN = range(3)
 
 
 class SvError(RuntimeError):
@@ -248,7 +249,7 @@ def sv_workspace_region(cfg: ModelCfg, B: int, T: int, n_scored: int, which: int
 
 
 def sv_product_plan(cfg: ModelCfg, n_rows: int, which: int, n_scored: int = 0, n_xcd: int = 8) -> Tuple[int, ...]:
-    """(kernel, row blocks, weight tiles, K slices, column groups per XCD, blocks of rows): see the header."""
+    """(kernel (SV_KERNEL_*), row blocks, weight tiles, K slices, column groups per XCD, blocks of rows): see the header."""
     plan = (C.c_int32 * 6)()
     _check(lib().sv_product_plan(C.byref(cfg), n_rows, which, n_scored, n_xcd, plan), "sv_product_plan")
     return tuple(plan)

@@ -543,7 +543,7 @@ int sv_workspace_bytes(const sv_model_cfg* cfg, int B, int T, int n_scored, size
   const int rc = check_workspace_sizes(cfg, B, T, n_scored);
   if (rc != SV_OK) return rc;
   size_t most = workspace_layout(*cfg, B * T, n_scored).total;
-  for (int rows = 32; cfg->dtype != SV_F32 && rows < B * T; rows += 32) {      // (plans follow from the 32-row blocks)
+  for (int rows = 32; cfg->dtype != SV_F32 && rows < B * T; rows += 32) {      // (what a plan takes follows from the 32-row blocks)
     const size_t n = workspace_layout(*cfg, rows, n_scored).total;
     most = n > most ? n : most;
   }
@@ -729,7 +729,7 @@ int sv_product_plan(const sv_model_cfg* cfg, int n_rows, int which, int n_scored
     const LayerPlan l = plan_layer(*cfg, n_rows, n_xcd);
     p = which == SV_PLAN_QKV ? l.qkv : (which == SV_PLAN_OUT ? l.o : (which == SV_PLAN_GATE_UP ? l.gu : l.down));
   }
-  const int32_t v[6] = {p.mid ? 1 : 0, p.rb, p.nt, 1 << p.lgS, p.gpx, p.m_tiles};
+  const int32_t v[6] = {p.kernel, p.rb, p.nt, 1 << p.lgS, p.gpx, p.m_tiles};
   memcpy(plan, v, sizeof(v));
   return SV_OK;
 }

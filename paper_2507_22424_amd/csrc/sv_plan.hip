@@ -5,13 +5,14 @@
 
 namespace sv {
 
-// Up to 128 rows.  As many K slices as leave a group at most skinny_max_tiles tiles while groups x slices
+// Up to 128 rows, up to 16 with half of the rows left out.  As many K slices as leave a group at most skinny_max_tiles tiles while groups x slices
 // make one round of the chip: fewer groups mean that fewer workgroups read the activations.  A wave gets
 // at least 64 k-values (four waves per slice).
 static ProductPlan plan_skinny(int M, int N, int K, int n_xcd) {
   const int tiles = N / kFragRows, tiles_x = ceil_div(tiles, n_xcd);
   ProductPlan p;
   memset(&p, 0, sizeof(p));
+  p.kernel = M <= kThinRows ? PRODUCT_THIN : PRODUCT_SKINNY;
   p.rb = ceil_div(M, kFragRows);
   const int most = skinny_max_tiles(p.rb);
   int nt = 0;
@@ -54,7 +55,7 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
         if (lgS > 0 && K < ((wf == 2 ? 256 : 128) << lgS)) continue;
         ProductPlan p;
         memset(&p, 0, sizeof(p));
-        p.mid = true; p.rb = rb; p.nt = nt; p.lgS = lgS;
+        p.kernel = PRODUCT_MID; p.rb = rb; p.nt = nt; p.lgS = lgS;
         p.m_tiles = ceil_div(n_rb, rb);
         p.gpx = ceil_div(tiles_x, 4 * nt);
         p.wg_x = (p.gpx * p.m_tiles) << lgS;
@@ -77,7 +78,7 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
   return best;
 }
 
-// Rows the kernels split at.  Up to 64 gemm_skinny (with rows <= 16 left out: gemm_thin).  Up to 128 gemm_skinny unless
+// Rows the kernels split at.  Up to 16 gemm_thin, up to 64 gemm_skinny.  Up to 128 gemm_skinny unless
 // its groups of few tiles would make more than one round of the chip, or would read too much: every group reads all
 // activations, at 14 TB/s next to the weights, gemm_mid's blocks a quarter of that.  bf16 weights, 7B shapes,
 // MB of activations read by gemm_skinny, us of gemm_skinny / gemm_mid: 96 rows o 100 15.0 / 15.8, q,k,v 201 34.2 / 31.6,
@@ -111,7 +112,7 @@ ProductPlan plan_head(int M, int N, int K, int n_xcd) {
       if (nt > skinny_max_tiles(rb)) continue;
       ProductPlan p;
       memset(&p, 0, sizeof(p));
-      p.rb = rb; p.lgS = lgS; p.gpx = gpx; p.m_tiles = m_tiles;
+      p.kernel = PRODUCT_SKINNY; p.rb = rb; p.lgS = lgS; p.gpx = gpx; p.m_tiles = m_tiles;
       p.nt = nt <= 2 ? 2 : (rb > 2 ? 3 : (nt <= 4 ? 4 : 6));
       p.wg_x = (gpx * m_tiles) << lgS;
       p.unit_stride = kSkinnyUnitStride;
@@ -125,8 +126,9 @@ ProductPlan plan_head(int M, int N, int K, int n_xcd) {
 void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint4* Xs, const uint4* Wp, int N, int K,
                     const ProductScratch& s, const EpiArgs& e, hipStream_t st) {
   const int tiles = N / kFragRows, groups = n_xcd * p.gpx;
-  const dim3 grid(n_xcd, p.mid ? p.wg_x : p.gpx << p.lgS, p.mid ? 1 : p.m_tiles);
-  if (p.mid) {
+  const bool mid = p.kernel == PRODUCT_MID;
+  const dim3 grid(n_xcd, mid ? p.wg_x : p.gpx << p.lgS, mid ? 1 : p.m_tiles);
+  if (mid) {
     MidArgs a;
     memset(&a, 0, sizeof(a));
     const int chunks = K / mid_chunk_k(p.rb, p.nt, wf);
@@ -142,7 +144,7 @@ void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint
   } else {
     SkinnyArgs a;
     memset(&a, 0, sizeof(a));
-    const bool thin = e.M <= kThinRows && p.m_tiles == 1;
+    const bool thin = p.kernel == PRODUCT_THIN;
     const int units = K / (thin ? thin_step_k(wf) : kFragK << wf), waves = 4 << p.lgS;
     a.Xs = Xs; a.Wp = Wp; a.N = N; a.lgS = p.lgS; a.gpx = p.gpx; a.n_xcd = n_xcd;
     // Groups end at half tiles where that makes the largest group smaller, the weight bytes set the time (up to

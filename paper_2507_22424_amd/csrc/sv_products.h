@@ -9,10 +9,12 @@
 
 namespace sv {
 
+// (the numbers that sv_product_plan reports)
+enum ProductKernel { PRODUCT_SKINNY = 0, PRODUCT_MID = 1, PRODUCT_THIN = 2 };
 // How one product [M, K] x [N, K]^T is split over the chip.
 struct ProductPlan {
-  bool mid;                  // gemm_mid, else gemm_skinny
-  int rb, nt;                // row blocks and tiles of the kernel instance
+  ProductKernel kernel;
+  int rb, nt;                // row blocks (PRODUCT_THIN: half of one) and tiles of the kernel instance
   int lgS, gpx, m_tiles;     // K slices, column groups per XCD, blocks of rows
   int wg_x;                  // workgroups per XCD
   int unit_stride;           // float4 of exchange scratch per workgroup

@@ -74,6 +74,7 @@ TOL_WIDE_ATTN = 2.0 ** -7        # a picked value passes whole: one unit in its 
 WIDE_LAYERS = {"bf16": [(1, 65), (3, 50), (7, 23), (4, 60), (5, 60), (3, 107), (5, 77), (13, 37), (9, 57), (6, 107), (10, 77)],
                "bf16_w8": [(1, 65), (1, 128), (3, 50), (7, 23), (4, 60), (3, 93), (3, 107), (5, 77), (13, 37), (9, 57)],
                "bf16_w4": [(1, 65), (1, 128), (3, 50), (7, 23), (4, 60), (3, 93), (3, 107), (5, 77), (13, 37), (9, 57)]}
+UP_TO_16 = {"bf16": [1, 16], "bf16_w8": [16], "bf16_w4": [1, 16]}    # nodes of one episode, likewise
 WIDE_ELSEWHERE = {"bf16": [26, 60, 128, 960], "bf16_w8": [26, 60], "bf16_w4": [26, 60]}   # rows, in test_gpu_parity.py
 
 
@@ -85,7 +86,7 @@ def test_one_7b_layer_in_every_form_of_its_products(dtype, B, T):
 
 
 # rows of the packed head over the whole vocabulary, likewise
-WIDE_HEAD = [1, 60, 65, 97, 150, 161, 240, 300, 400, 780]
+WIDE_HEAD = [1, 26, 60, 65, 97, 150, 161, 240, 300, 400, 780]
 
 
 def test_full_vocabulary_head_in_every_form_of_its_product():
@@ -206,6 +207,6 @@ def test_up_to_16_rows(dtype, T, B, H, F):
     check_forward(SideBySide(cfg, store=bf16_store, stack_tol=TOL), TOL, TOL_ATTN)
 
 
-@pytest.mark.parametrize("dtype,T", [("bf16", 1), ("bf16", 16), ("bf16_w8", 16), ("bf16_w4", 1), ("bf16_w4", 16)])
+@pytest.mark.parametrize("dtype,T", [(dtype, T) for dtype, nodes in UP_TO_16.items() for T in nodes])
 def test_one_7b_layer_of_up_to_16_rows(dtype, T):
     test_one_7b_layer_in_every_form_of_its_products(dtype, 1, T)

@@ -4,7 +4,7 @@ import pytest
 
 from paper_2507_22424_amd import binding as sv
 from perf import cases
-from test_gpu_products import WIDE_ELSEWHERE, WIDE_HEAD, WIDE_LAYERS
+from test_gpu_products import UP_TO_16, WIDE_ELSEWHERE, WIDE_HEAD, WIDE_LAYERS
 
 LAYER = (sv.SV_PLAN_QKV, sv.SV_PLAN_OUT, sv.SV_PLAN_GATE_UP, sv.SV_PLAN_DOWN)
 
@@ -17,19 +17,23 @@ def _forms(dtype, rows):
     return {(which,) + sv.sv_product_plan(_cfg(dtype), rows, which)[:4] for which in LAYER}
 
 
+def _layer_rows(dtype):
+    return [B * T for B, T in WIDE_LAYERS[dtype]] + UP_TO_16[dtype] + WIDE_ELSEWHERE[dtype]
+
+
 def _head_form(rows, n):
     return sv.sv_product_plan(_cfg("bf16"), rows, sv.SV_PLAN_HEAD, n)[:4]
 
 
 @pytest.mark.parametrize("dtype,most", [("bf16", 960), ("bf16_w8", 640), ("bf16_w4", 640)])
 def test_every_form_of_a_layers_products_has_a_test(dtype, most):
-    tested = set().union(*(_forms(dtype, M) for M in [B * T for B, T in WIDE_LAYERS[dtype]] + WIDE_ELSEWHERE[dtype]))
+    tested = set().union(*(_forms(dtype, M) for M in _layer_rows(dtype)))
     missing = {M: _forms(dtype, M) - tested for M in range(1, most + 1)}
     assert not {M: f for M, f in missing.items() if f}
 
 
 def test_every_form_of_the_heads_product_has_a_test():
-    layers = [B * T for B, T in WIDE_LAYERS["bf16"]] + WIDE_ELSEWHERE["bf16"]      # (their logits: 256 action rows)
+    layers = _layer_rows("bf16")                     # (their logits: 256 action rows)
     assert {_head_form(M, 256) for M in range(1, 961)} <= {_head_form(M, 256) for M in layers}
     assert {_head_form(M, 32000) for M in range(1, 961)} <= {_head_form(M, 32000) for M in WIDE_HEAD}
 
@@ -41,6 +45,15 @@ def test_8_bit_weights_split_along_k_as_far_as_bf16_weights(H, F):
         for which in LAYER:
             bf16, w8 = (sv.sv_product_plan(c, rows, which)[3] for c in cfgs)
             assert w8 >= bf16, (rows, which)
+
+
+def test_half_of_the_rows_is_left_out_up_to_16_rows():
+    """... and the query tells that kernel from gemm_skinny: without a test of its own, its forms have none."""
+    for dtype in ("bf16", "bf16_w8", "bf16_w4"):
+        for which in LAYER:
+            kernels = [sv.sv_product_plan(_cfg(dtype), rows, which)[0] for rows in (1, 16, 17, 64)]
+            assert kernels == [sv.SV_KERNEL_THIN] * 2 + [sv.SV_KERNEL_SKINNY] * 2, (dtype, which)
+    assert _head_form(16, 256)[0] == _head_form(16, 32000)[0] == sv.SV_KERNEL_THIN
 
 
 def test_the_timed_cases_lie_in_the_range_that_is_tested():
