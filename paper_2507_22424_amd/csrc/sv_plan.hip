@@ -8,11 +8,13 @@ namespace sv {
 // Up to 128 rows, up to 16 with half of the rows left out.  As many K slices as leave a group at most skinny_max_tiles tiles while groups x slices
 // make one round of the chip: fewer groups mean that fewer workgroups read the activations.  A wave gets
 // at least 64 k-values (four waves per slice).
-static ProductPlan plan_skinny(int M, int N, int K, int n_xcd) {
+// 4-bit weights have gemm_thin only where a wave has two of its steps of 64 k-values and more: its ring asks for four
+// steps whatever there is.  One row, us of a layer, gemm_skinny / gemm_thin: H = 512 36.0 / 37.1, H = 1024 38.1 / 39.9;
+// 7B, two steps and more everywhere, 70.0 / 67.1.  (The other formats' steps are half as deep: faster throughout.)
+static ProductPlan plan_skinny(int M, int N, int K, int wf, int n_xcd) {
   const int tiles = N / kFragRows, tiles_x = ceil_div(tiles, n_xcd);
   ProductPlan p;
   memset(&p, 0, sizeof(p));
-  p.kernel = M <= kThinRows ? PRODUCT_THIN : PRODUCT_SKINNY;
   p.rb = ceil_div(M, kFragRows);
   const int most = skinny_max_tiles(p.rb);
   int nt = 0;
@@ -27,6 +29,7 @@ static ProductPlan plan_skinny(int M, int N, int K, int n_xcd) {
     p.gpx = ceil_div(tiles_x, most);
     nt = ceil_div(tiles, n_xcd * p.gpx);
   }
+  p.kernel = M <= kThinRows && (wf != 2 || K >= (512 << p.lgS)) ? PRODUCT_THIN : PRODUCT_SKINNY;
   p.nt = nt <= 2 ? 2 : (p.rb > 2 ? 3 : (nt <= 4 ? 4 : 6));
   p.m_tiles = 1;
   p.wg_x = p.gpx << p.lgS;
@@ -87,7 +90,7 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
 // 31.4 / 37.3, down 29.9 / 30.3).
 ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd) {
   if (M <= kSkinnyMaxRows) {
-    const ProductPlan p = plan_skinny(M, N, K, n_xcd);
+    const ProductPlan p = plan_skinny(M, N, K, wf, n_xcd);
     const double mb = (double)n_xcd * p.wg_x * (K >> p.lgS) * p.rb * kFragRows * 4 / 1e6;
     const bool wide = wf == 0 && mb > (p.rb == 3 ? 150 : 310);
     if (M <= 64 || (p.wg_x <= kCusPerXcd && !wide)) return p;

@@ -210,3 +210,12 @@ def test_up_to_16_rows(dtype, T, B, H, F):
 @pytest.mark.parametrize("dtype,T", [(dtype, T) for dtype, nodes in UP_TO_16.items() for T in nodes])
 def test_one_7b_layer_of_up_to_16_rows(dtype, T):
     test_one_7b_layer_in_every_form_of_its_products(dtype, 1, T)
+
+
+@pytest.mark.parametrize("T,H,heads,F", [(16, 4096, 2, 256), (9, 4096, 10, 2048), (16, 512, 4, 4096)])
+def test_4_bit_weights_of_few_tiles_up_to_16_rows(T, H, heads, F):
+    """gemm_thin takes 4-bit weights from two steps a wave on: its forms of two and four tiles, with exactly two."""
+    cfg = wl.C2.scaled(name=f"thin-w4-{T}-{H}-{heads}-{F}", index=70, dtype="bf16_w4", n_layers=1, hidden=H, n_heads=heads,
+                       head_dim=128, mlp_dim=F, vocab=1024, n_bins=256, tree_nodes=T, n_episodes=1, prefix_lo=20, prefix_hi=30,
+                       max_children=6, spine_lo=3, r_values=(0, 4))
+    check_forward(SideBySide(cfg, store=bf16_store, stack_tol=TOL_WIDE), TOL_WIDE, TOL_WIDE_ATTN)

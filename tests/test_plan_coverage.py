@@ -56,6 +56,14 @@ def test_half_of_the_rows_is_left_out_up_to_16_rows():
     assert _head_form(16, 256)[0] == _head_form(16, 32000)[0] == sv.SV_KERNEL_THIN
 
 
+def test_4_bit_weights_leave_rows_out_where_a_wave_has_two_steps():
+    for H, F in ((512, 1536), (1024, 2816), (2048, 5632), (4096, 11008), (5120, 13824)):
+        cfg = sv.model_cfg("bf16_w4", H, H // 128, 128, F, 1024)
+        for which, K in zip(LAYER, (H, H, H, F)):
+            kernel, _, _, slices, _, _ = sv.sv_product_plan(cfg, 16, which)
+            assert (kernel == sv.SV_KERNEL_THIN) == (K // slices >= 2 * 4 * 64), (H, which)
+
+
 def test_the_timed_cases_lie_in_the_range_that_is_tested():
     for case in cases.listed():
         rows = case["episodes"] * case["nodes"]
