@@ -81,18 +81,23 @@ static ProductPlan plan_mid(int M, int N, int K, int wf, int n_xcd) {
   return best;
 }
 
-// Rows the kernels split at.  Up to 16 gemm_thin, up to 64 gemm_skinny.  Up to 128 gemm_skinny unless
-// its groups of few tiles would make more than one round of the chip, or would read too much: every group reads all
-// activations, at 14 TB/s next to the weights, gemm_mid's blocks a quarter of that.  bf16 weights, 7B shapes,
-// MB of activations read by gemm_skinny, us of gemm_skinny / gemm_mid: 96 rows o 100 15.0 / 15.8, q,k,v 201 34.2 / 31.6,
-// down 270 30.3 / 27.1, gate+up 360 52.7 / 45.5; 128 rows o 134 17.5 / 18.2, q,k,v 268 37.2 / 38.2, down 360 35.0 / 31.6,
-// gate+up 480 59.0 / 55.6.  Coded weights: gemm_mid is slower throughout (8 bits, 100 rows: gate+up 47.4 / 55.2, q,k,v
-// 31.4 / 37.3, down 29.9 / 30.3).
+// Rows the kernels split at.  Up to 16 gemm_thin, up to 64 gemm_skinny.  Up to 128 gemm_skinny unless its groups of few
+// tiles would make more than one round of the chip, or read too much of the activations: a group reads all rows of its
+// K slice, so those that do not split K and those of two tiles or less, with 3 bytes of activations and more to a byte
+// of weights, wait for them.  bf16 weights, us of gemm_skinny / gemm_mid (blocks of 12 tiles and more) at 80 and 112
+// rows: one slice: gate+up of H = 3072 34 / 28, 39 / 33, of 7B 52 / 45, 60 / 54, q,k,v of H = 8192 99 / 78, 115 / 93; two
+// tiles: down of 7B (271 and 361 MB read) 32.0 / 30.0, 36.5 / 33.6, output of H = 8192 45.4 / 41.1, 52.6 / 47.8, but
+// output of 7B (101, 134 MB) 17.3 / 18.8, 19.2 / 20.6, down of H = 2048 (69, 92 MB) 14.7 / 17.4, 16.4 / 18.8; hence the
+// 250 MB.  Slices and more tiles: q,k,v of 7B 33.4 / 33.5, 37.7 / 39.0, down of H = 5120 47.0 / 47.8, 53.0 / 54.6, output of
+// H = 6144 28.2 / 29.6, 32.1 / 33.6.  Over H = 512 .. 8192 (32 products, 65 - 128 rows) what is taken is nowhere more than
+// 1 % slower than gemm_skinny.  Coded weights: gemm_mid is slower or the same but where there is one slice (8 bits,
+// q,k,v of H = 5120 40 / 36), which was not taken up.
 ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd) {
   if (M <= kSkinnyMaxRows) {
     const ProductPlan p = plan_skinny(M, N, K, wf, n_xcd);
-    const double mb = (double)n_xcd * p.wg_x * (K >> p.lgS) * p.rb * kFragRows * 4 / 1e6;
-    const bool wide = wf == 0 && mb > (p.rb == 3 ? 150 : 310);
+    const int groups = n_xcd * p.gpx;
+    const double mb = (double)groups * K * p.rb * kFragRows * 4 / 1e6;       // activations read
+    const bool wide = wf == 0 && mb > 250 && (p.lgS == 0 || N / kFragRows <= 2 * groups);
     if (M <= 64 || (p.wg_x <= kCusPerXcd && !wide)) return p;
   }
   return plan_mid(M, N, K, wf, n_xcd);

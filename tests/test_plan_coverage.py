@@ -64,6 +64,15 @@ def test_4_bit_weights_leave_rows_out_where_a_wave_has_two_steps():
             assert (kernel == sv.SV_KERNEL_THIN) == (K // slices >= 2 * 4 * 64), (H, which)
 
 
+@pytest.mark.parametrize("H,F,mid", [(512, 1536, ()), (2048, 5632, ()), (3072, 8192, (sv.SV_PLAN_GATE_UP,)),
+                                     (4096, 11008, (sv.SV_PLAN_GATE_UP, sv.SV_PLAN_DOWN)), (5120, 13824, (sv.SV_PLAN_QKV, sv.SV_PLAN_GATE_UP)),
+                                     (6144, 16384, (sv.SV_PLAN_QKV, sv.SV_PLAN_GATE_UP)), (8192, 28672, LAYER)])
+def test_products_of_65_to_128_rows_on_the_kernel_that_was_faster(H, F, mid):
+    cfg = sv.model_cfg("bf16", H, H // 128, 128, F, 1024)
+    for rows in (65, 80, 96, 97, 112, 128):
+        assert tuple(which for which in LAYER if sv.sv_product_plan(cfg, rows, which)[0] == sv.SV_KERNEL_MID) == mid, rows
+
+
 def test_the_timed_cases_lie_in_the_range_that_is_tested():
     for case in cases.listed():
         rows = case["episodes"] * case["nodes"]
