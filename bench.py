@@ -62,6 +62,16 @@ class HipEvents:
         return out.value
 
 
+def product_kernels(sv, plans):
+    """The kernels that the four products of a layer run on, as text, and whether all of them are on gemm_mid, whose
+    loops the matrix cores bound (the others stream the weights)."""
+    names = {sv.SV_KERNEL_SKINNY: "gemm_skinny", sv.SV_KERNEL_MID: "gemm_mid", sv.SV_KERNEL_THIN: "gemm_thin"}
+    products = {"qkv": "q/k/v", "o": "o", "gate_up": "gate/up", "down": "down"}
+    used = [k for k in names if any(p[0] == k for p in plans.values())]
+    parts = [", ".join(t for n, t in products.items() if plans[n][0] == k) for k in used]
+    return f"{', '.join(names[k] for k in used)} (4 launches per layer: {'; '.join(parts)})", used == [sv.SV_KERNEL_MID]
+
+
 def host_cores():
     """(logical cores the process may run on, threads the BLAS pool behind numpy uses)."""
     from threadpoolctl import threadpool_info
@@ -309,10 +319,10 @@ def main():
     step_bytes = weights_total + kv_bytes * L + cfg.n_bins * H * 2 + 2 * cfg.n_heads * M * cfg.head_dim * 2 * L
     step_flops = sum(gemm_flops.values()) * L
 
-    mfma_bound = plans["gate_up"][0] == 1    # gemm_mid: the products are bound by the matrix cores
+    kernels, mfma_bound = product_kernels(sv, plans)
     key = (args.config, args.weights)
     if mfma_bound:
-        roofline = {"bound": "mfma", "kernel": "gemm_mid (4 launches per layer: q/k/v, o, gate/up, down)",
+        roofline = {"bound": "mfma", "kernel": kernels,
                     "achieved": mfma_tflops, "peak": MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": mfma_tflops / MFMA_PEAK_TFLOPS,
                     "traffic": TRAFFIC_BYTES_PER_LAUNCH.get(key),
@@ -324,7 +334,7 @@ def main():
                     "avg_launch_us": gemm_ms_raw * 1e3 / (4 * L)}
     else:
         roofline = {"bound": "hbm",
-                    "kernel": "gemm_skinny (4 launches per layer: q/k/v, o, gate/up, down)",
+                    "kernel": kernels,
                     "achieved": gemm_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": gemm_gbs / HBM_PEAK_GBS,
                     "traffic": TRAFFIC_BYTES_PER_LAUNCH.get(key),

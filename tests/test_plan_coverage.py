@@ -2,6 +2,7 @@
 weight format - is held to the oracle by a GPU test: the listed sizes reach all forms of the declared range."""
 import pytest
 
+import bench
 from paper_2507_22424_amd import binding as sv
 from perf import cases
 from test_gpu_products import UP_TO_16, WIDE_ELSEWHERE, WIDE_HEAD, WIDE_LAYERS
@@ -89,6 +90,14 @@ def test_groups_that_share_sums_fit_the_counters(H, F):
             for which in LAYER + (sv.SV_PLAN_HEAD,):
                 _, _, _, slices, groups, blocks = sv.sv_product_plan(cfg, rows, which, 32000, n_xcd)
                 assert slices == 1 or groups * blocks <= 4096 // n_xcd, (n_xcd, rows, which)
+
+
+@pytest.mark.parametrize("dtype,rows,label,mfma_bound", [
+    ("bf16", 1, "gemm_thin (4 launches per layer: q/k/v, o, gate/up, down)", False), ("bf16", 60, "gemm_skinny (4 launches per layer: q/k/v, o, gate/up, down)", False),
+    ("bf16", 128, "gemm_skinny, gemm_mid (4 launches per layer: q/k/v, o; gate/up, down)", False), ("bf16", 960, "gemm_mid (4 launches per layer: q/k/v, o, gate/up, down)", True)])
+def test_the_benchmark_names_the_kernels_that_run(dtype, rows, label, mfma_bound):
+    plans = {n: sv.sv_product_plan(_cfg(dtype), rows, which) for n, which in zip(("qkv", "o", "gate_up", "down"), LAYER)}
+    assert bench.product_kernels(sv, plans) == (label, mfma_bound)
 
 
 def test_plan_queries_check_their_arguments():
