@@ -51,6 +51,9 @@ __device__ __forceinline__ void thin_body(const SkinnyArgs& a, f32x4_t* lds, flo
   const int u0 = ws * a.uq + min(ws, a.urem);
   const int n_units = a.uq + (ws < a.urem ? 1 : 0);
 
+  SsqSums<kThinRows, 8> rows(a.e, 0, tid);
+  if (EPI == EPI_OUT) rows.request();
+
   // Lane (i16, g16) of v_mfma_f32_16x16x32_bf16 holds eight k-values of weight (or activation) row i16.  Out of the
   // 32-row fragments: k-half g16 % 2 of k-step KK * (g16 / 2) + kk.  Coded weights: a 16-byte piece covers two
   // k-steps (E4M3) or four (int4), of which a lane fetches its own 8 bytes.
@@ -162,9 +165,8 @@ __device__ __forceinline__ void thin_body(const SkinnyArgs& a, f32x4_t* lds, flo
     left -= D;
   }
 
-  // what the epilogue needs to know of the rows: see skinny_body
-  SsqSums<kThinRows, 8> rows(a.e, 0, tid);
-  if (EPI != EPI_RESID) rows.request();
+  // what the epilogue needs to know of the rows: see skinny_body (the head's planes too)
+  if (epi_pairs(EPI)) rows.request();
   EpiRow er;
   if (EPI == EPI_QKV) er = epi_row_fetch(a.e, min(tid % kThinRows, a.e.M - 1));
 

@@ -109,6 +109,10 @@ ProductPlan plan_product(int M, int N, int K, int wf, int n_xcd) {
 // H = 4096, without / with this at 65, 150, 240, 480, 960 rows: 16.1 / 14.7, 22.4 / 17.8, 24.6 / 21.0, 30.5 / 26.9,
 // 39.6 / 35.9; H = 1024: 13.8 / 12.8, 16.6 / 14.0, 17.2 / 13.8, 19.0 / 16.0, 23.3 / 21.7; 512 columns: the same or
 // up to 20 % less; from 1024 columns on: 10 % less to 11 % more.
+// Up to 16 rows gemm_thin only where a wave has the four steps of 32 k-values that its ring asks for.  us of the call, 8
+// rows, gemm_skinny / gemm_thin: H = 1024 (two steps) 256 columns 10.2 / 10.6, 1024 columns 10.6 / 11.1; H = 4096 (four)
+// 11.7 / 11.2, 12.1 / 11.2; 32000 columns of H = 1024 (eight) 23.5 / 22.2.  (The layers' short products gain by it all the same:
+// they exchange their sums more often.  One row, H = 512, a layer 36.4 / 34.6.)
 ProductPlan plan_head(int M, int N, int K, int n_xcd) {
   const int tiles = N / kFragRows, tiles_x = ceil_div(tiles, n_xcd), n_rb = ceil_div(M, kFragRows);
   for (int lgS = 3; M > 64 && tiles_x <= 2 && lgS >= 0; --lgS) {
@@ -128,7 +132,9 @@ ProductPlan plan_head(int M, int N, int K, int n_xcd) {
       return p;
     }
   }
-  return plan_product(M, N, K, 0, n_xcd);
+  ProductPlan p = plan_product(M, N, K, 0, n_xcd);
+  if (p.kernel == PRODUCT_THIN && K < (512 << p.lgS)) p.kernel = PRODUCT_SKINNY;
+  return p;
 }
 
 void launch_product(const ProductPlan& p, int epi, int wf, int n_xcd, const uint4* Xs, const uint4* Wp, int N, int K,

@@ -57,6 +57,14 @@ def test_half_of_the_rows_is_left_out_up_to_16_rows():
     assert _head_form(16, 256)[0] == _head_form(16, 32000)[0] == sv.SV_KERNEL_THIN
 
 
+def test_heads_leave_rows_out_where_a_wave_has_four_steps():
+    for H in (512, 1024, 2048, 4096):
+        cfg = sv.model_cfg("bf16", H, H // 128, 128, 2816, 32000)
+        for n in (256, 1024, 32000):
+            kernel, _, _, slices, _, _ = sv.sv_product_plan(cfg, 16, sv.SV_PLAN_HEAD, n)
+            assert (kernel == sv.SV_KERNEL_THIN) == (H // slices >= 4 * 4 * 32), (H, n)
+
+
 def test_4_bit_weights_leave_rows_out_where_a_wave_has_two_steps():
     for H, F in ((512, 1536), (1024, 2816), (2048, 5632), (4096, 11008), (5120, 13824)):
         cfg = sv.model_cfg("bf16_w4", H, H // 128, 128, F, 1024)
