@@ -57,7 +57,7 @@ struct SsqSums {
   __device__ void request(int first = 0) {
 #pragma unroll
     for (int i0 = 0; i0 < BATCH; i0 += 8) {
-      if (kParts * (first + i0) >= n) break;
+      if (i0 && kParts * (first + i0) >= n) break;       // (there is one at least)
 #pragma unroll
       for (int i = i0; i < i0 + 8; ++i) v[i] = src[(size_t)(min(part + kParts * (first + i), n - 1)) * stride];
     }
@@ -67,7 +67,7 @@ struct SsqSums {
     for (int first = 0;;) {
 #pragma unroll
       for (int i0 = 0; i0 < BATCH; i0 += 8) {
-        if (kParts * (first + i0) >= n) break;
+        if (i0 && kParts * (first + i0) >= n) break;
 #pragma unroll
         for (int i = i0; i < i0 + 8; ++i) s += part + kParts * (first + i) < n ? v[i] : 0.f;
       }

@@ -88,8 +88,9 @@ struct SkinnyRing {
   // asked for last there is waited for as the last one in every round; against that stands what the scheduler gains by
   // mixing them with the set-up.  us of a layer, scheduler's order / this: 8 bits, 32 rows 7B 83.9 / 80.9, H = 5120
   // 106.1 / 99.8; 4 bits 32 rows H = 5120 92.1 / 87.6, 96 rows 7B 123.0 / 116.5; but bf16, 60 rows 7B 119.9 / 127.5,
-  // H = 2048 69.2 / 72.3; 8 bits 33 - 128 rows the same within 1 %.
-  static constexpr bool kInOrder = WF == 2 || (WF == 1 && RB == 1);
+  // H = 2048 69.2 / 72.3; 8 bits 33 - 128 rows the same within 1 %.  The head, 256 columns of H = 4096, 17, 60 and 240 rows
+  // 11.5 / 11.2, 13.5 / 13.0, 20.4 / 19.8.
+  static constexpr bool in_order(int epi) { return epi == EPI_OUT || WF == 2 || (WF == 1 && RB == 1); }
 };
 
 template <int RB, int NT, int EPI, int WF>
@@ -158,7 +159,7 @@ __device__ __forceinline__ void skinny_body(const SkinnyArgs& a, f32x4_t* lds, f
   for (int d = 0; d < DX || d < DW; ++d) {
     if (d < DX) issue_x(d);
     if (d < DW) issue_w(d);
-    if (Ring::kInOrder) __builtin_amdgcn_sched_barrier(0);
+    if (Ring::in_order(EPI)) __builtin_amdgcn_sched_barrier(0);
   }
   f32x16_t acc[NT][RB];
 #pragma unroll
