@@ -23,10 +23,10 @@ MFMA_PEAK_TFLOPS = 2500.0           # dense bf16
 # then WRITE_SIZE, each calibrated with a transfer of known size in the same run) whose summaries
 # are under profiles/: fetched + written bytes, averaged over the four products of a layer.
 TRAFFIC_BYTES_PER_LAUNCH = {
-    ("C3", "bf16"): 131.35e6,
-    ("C3", "w8"): 80.83e6,
-    ("C4", "bf16"): 376.82e6,
-    ("C5", "bf16"): 140.61e6,
+    ("C3", "bf16"): 131.33e6,
+    ("C3", "w8"): 80.84e6,
+    ("C4", "bf16"): 375.21e6,
+    ("C5", "bf16"): 163.64e6,
 }
 TRAFFIC_SOURCE = {
     ("C3", "bf16"): "rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, profiles/c3_step_hbm_traffic.txt",
