@@ -65,9 +65,10 @@ __device__ inline float silu_fast(float x) {
 //   WF = 1: 8 bytes of E4M3 codes per k-step, one hardware conversion per pair (gfx950; scale 1).  Exact, every E4M3
 //           value is a bf16 value.
 //   WF = 2: integers -8 .. 7 in 4-bit two's complement, one 32-bit word per k-step, value i of a word in bits
-//           4i .. 4i+3.  v_cvt_off_f32_i4 takes the low four bits of a byte and gives a sixteenth of the integer; the sixteen is in the packed row scales.  Exact.  (Bit-field
-//           extract, integer conversion and a flip of the top bits, as before, are 21 instead of 13
-//           instructions for eight weights, next to four matrix instructions at up to 64 rows.)
+//           4i .. 4i+3.  v_cvt_off_f32_i4 takes the low four bits of a byte and gives a sixteenth of the integer; the
+//           sixteen is in the packed row scales.  Exact.  (Bit-field extract, integer conversion and a flip of the
+//           top bits, as before, are 21 instead of 13 instructions for eight weights, next to four matrix
+//           instructions at up to 64 rows.)
 constexpr float kInt4Unit = 16.0f;
 // Word j (two weights) of it; odd: scratch that the words 0 .. 3 of an operand share (int4: the odd nibbles).
 template <int WF, typename T>

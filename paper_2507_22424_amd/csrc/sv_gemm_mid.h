@@ -1,4 +1,4 @@
-// The layer's products for more than 128 rows of activations.
+// The layer's products for more than 128 rows of activations, and some of 65 - 128 rows of bf16 weights (plan_product).
 //
 // With this many rows the matrix cores set the time, at the clock that their power leaves on real data.  On random
 // data, all CUs, nothing but matrix instructions, v_mfma_f32_32x32x16_bf16 sustains 1.75 - 1.8 PFLOP/s in any order of
@@ -11,7 +11,7 @@
 //     are only padding against whole rounds of the chip (150 rows: 192 are multiplied, two blocks of 3, which fill
 //     the chip with half the K slices, and so less exchange, than one of 5 would need);
 //   * a weight tile belongs to one wave: its fragments go from memory straight into operand registers,
-//     through a ring of D chunks.  The activations of a chunk (two k-steps; four with coded weights) are
+//     through a ring of D chunks.  The activations of a chunk (two k-steps; four with coded weights, see mid_kk) are
 //     fetched once per workgroup, each wave loading a quarter of the fragments into registers and writing
 //     them to LDS one chunk ahead of their use; one barrier per chunk, three LDS buffers.  Every load is
 //     one the compiler knows of, in a fixed order, so its waits are exact;

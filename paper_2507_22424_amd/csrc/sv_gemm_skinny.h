@@ -1,4 +1,4 @@
-// The layer's products for up to 128 rows of activations: every weight byte is needed once per step,
+// The layer's products for up to 128 rows of activations (up to 16 see sv_gemm_thin.h): every weight byte is needed once per step,
 // so the products are bound by HBM (above 64 rows by HBM and the matrix cores alike), and what is kept
 // small is everything around the weight stream.
 //
@@ -13,10 +13,10 @@
 //     fetched by one wave of the workgroup only.  The four sums meet in LDS.
 //   * S workgroups share the tiles along K (same XCD, same L2).  A workgroup keeps 1/S of its sums
 //     and sends the rest to the others as float32.
-//     60 rows of the 7B shape, us for gate+up / q,k,v / down / output: 40 / 29 / 26 / 14; the form before
+//     60 rows of the 7B shape, us for gate+up / q,k,v / down / output: 39.0 / 27.2 / 25.1 / 14.5; the form before
 //     this one (activations staged in LDS, therefore eight slices of 512 k-values, 16-bit partial
-//     tiles) 47 / 31.5 / 31 / 16.  128 rows: 62.5 / 45.6 / 39.3 / 20.5 against 60 / 36 / 41 / 19 of float32
-//     partial planes plus 60 of the split, norm and reduction launches they needed.
+//     tiles) 47 / 31.5 / 31 / 16.  128 rows, q,k,v / output: 38.2 / 19.0 (the other two are gemm_mid's) against 36 / 19
+//     of float32 partial planes plus the split, norm and reduction launches they needed, 60 over the four.
 //   * The weights are packed load-major: at one k-step all tiles lie next to each other, so what the
 //     chip reads at a time is spread over all memory channels (tile-major, with the tiles 256 KiB
 //     apart, the same stream reached 4.1 instead of 6.0 TB/s where four tiles are read per wave).

@@ -6,10 +6,10 @@
 // activations that every workgroup reads through the same paths, the sums in exchange and the matrix work - which,
 // with the conversions of coded weights, costs power and with it clock - are halved.  The weights are the same
 // packed tiles: a lane's eight k-values are half of a 32-row fragment's k-step, taken from two k-steps.
-// 7B layer, four products, us, 32x32x16 / this: one row 82.4 / 79.5 (bf16), 60.1 / 57.6 (8 bits), 49.7 / 47.5
-// (4 bits); 16 rows 85.4 / 83.2, 60.9 / 58.6, 53.8 / 48.8.  The same form with more rows was slower than
-// gemm_skinny (32 rows 86.2 / 89.6, 62.2 / 68.1, 55.0 / 57.8): its steps are twice as deep, so more is in flight
-// that the next phase has to wait for.
+// One layer of the 7B shape, attention included, us, gemm_skinny / this: one row 102.4 / 97.1 (bf16), 80.8 / 71.8 (8 bits),
+// 71.7 / 67.9 (4 bits); 16 rows 102.9 / 97.9, 81.2 / 73.5, 72.0 / 68.6.  The same form with more rows, four products: 32 rows
+// 86.2 / 89.6, 62.2 / 68.1, 55.0 / 57.8 - its steps are twice as deep, so more is in flight that the next phase has to wait
+// for -, 48 rows of coded weights 86 / 81.5, 78 / 73; only this one is built.
 #ifndef SV_GEMM_THIN_H
 #define SV_GEMM_THIN_H
 
